@@ -143,6 +143,8 @@ struct hub_ctx {
     double* d_st_tab_dn = nullptr;           // spin-down orbitals (spin-dependent contexts)
     double* d_nbar_ws = nullptr;
     size_t nbar_cap = 0;
+    double* d_coul = nullptr;                // scratch of the Coulomb tensors (kept while small)
+    size_t coul_cap = 0;
     // Workspaces of the call in flight come from the buffers above (grown
     // with hipMalloc on demand) unless ws_fixed points at slices of the
     // static scratch array (hub_step_noalloc), which are used as they are.
@@ -235,9 +237,9 @@ void release(hub_ctx* c) {
     f(c->d_chunks); f(c->d_all); f(c->d_gidx); f(c->d_img); f(c->d_phi); f(c->d_gphi); f(c->d_phase);
     f(c->d_site_chunk_ptr); f(c->d_site_chunk_ids); f(c->d_orb_site); f(c->d_site_L); f(c->d_site_orb0);
     f(c->d_site_species); f(c->d_species_orb_ptr); f(c->d_species_orb_ids); f(c->d_kw); f(c->d_ueff_fixed);
-    f(c->d_tensor); f(c->d_part); f(c->d_grad); f(c->d_nbar_ws); f(c->d_sink); f(c->d_occ_ws);
+    f(c->d_tensor); f(c->d_coul); f(c->d_part); f(c->d_grad); f(c->d_nbar_ws); f(c->d_sink); f(c->d_occ_ws);
     f(c->d_pg); f(c->d_mphi); f(c->d_images); f(c->d_kred);
-    c->part_cap = c->grad_cap = c->nbar_cap = c->sink_cap = c->occ_cap = 0;
+    c->part_cap = c->coul_cap = c->grad_cap = c->nbar_cap = c->sink_cap = c->occ_cap = 0;
     f(c->d_phi2); f(c->d_gphi_dn); f(c->d_mphi_dn);
     f(c->d_st_chunks); f(c->d_st_all); f(c->d_st_gidx); f(c->d_st_site_ptr); f(c->d_st_site_ids); f(c->d_st_tab); f(c->d_st_tab_dn);
     f(c->d_gchunks); f(c->d_gall); f(c->d_gall_m); f(c->d_gmom); f(c->d_ggidx); f(c->d_gf_orb); f(c->d_gf_img); f(c->d_gred_ptr);
@@ -991,6 +993,117 @@ int step_impl(hub_ctx* c, const hub_step_io* io, int mode, double* jcur) {
 }
 
 
+// Coulomb tensors of some sites: the plan's tables go up in one copy beside
+// the scratch, whose slices start on 256-byte boundaries.
+constexpr size_t kCoulombBatch = size_t(512) << 20;    // bytes of densities and offsets per batch
+constexpr size_t kCoulombKeep = size_t(32) << 20;      // scratch kept for the next call
+
+int coulomb_batch(hub_ctx* c, const std::vector<int>& sites) {
+    CoulombPlan P;
+    hub_coulomb_plan(c->T, sites, P);
+    const int ns = static_cast<int>(P.sites.size());
+    // sites whose kernel planes fit in LDS run together by density width,
+    // the others one by one on a table in device memory
+    size_t table = 0;
+    int maxplanes = 1, maxpair = 1;
+    auto big = [](const CoulombSite& S) {
+        return static_cast<size_t>(S.n[1]) * S.n[2] * sizeof(double) > HUB_COUL_LDS;
+    };
+    for (const CoulombSite& S : P.sites) {
+        maxplanes = std::max(maxplanes, S.n[0]);
+        maxpair = std::max(maxpair, S.L * (S.L + 1) / 2);
+        if (big(S)) table = std::max(table, static_cast<size_t>(S.n[0]) * S.n[1] * S.n[2]);
+    }
+    std::vector<CoulombItem> items;
+    items.reserve(P.items.size());
+    struct Launch {
+        int item0, nitems, npad, plane, site;          // site >= 0: from the table of that site
+    };
+    std::vector<Launch> launches;
+    auto take = [&](int i) { items.insert(items.end(), P.items.begin() + P.item_ptr[i], P.items.begin() + P.item_ptr[i + 1]); };
+    for (int npad : {32, 16}) {
+        Launch l{static_cast<int>(items.size()), 0, npad, 0, -1};
+        for (int i = 0; i < ns; ++i) {
+            const CoulombSite& S = P.sites[i];
+            if (S.npad != npad || big(S)) continue;
+            take(i);
+            l.plane = std::max(l.plane, S.n[1] * S.n[2]);
+        }
+        l.nitems = static_cast<int>(items.size()) - l.item0;
+        if (l.nitems) launches.push_back(l);
+    }
+    for (int i = 0; i < ns; ++i)
+        if (big(P.sites[i])) {
+            const int i0 = static_cast<int>(items.size());
+            take(i);
+            launches.push_back({i0, static_cast<int>(items.size()) - i0, P.sites[i].npad, 0, i});
+        }
+    // one buffer: scratch, then the tables in the order they are copied
+    std::vector<char> host;
+    auto add = [&](const auto& v) {
+        const size_t at = host.size();
+        const size_t nb = v.size() * sizeof(v[0]);
+        host.resize(at + (nb + 255) / 256 * 256);
+        std::memcpy(host.data() + at, v.data(), nb);
+        return at;
+    };
+    const size_t o_sites = add(P.sites), o_items = add(items), o_lines = add(P.lines), o_planes = add(P.planes);
+    const size_t n_rho = slice256(P.rho), n_part = slice256(P.part), n_yz = slice256(P.slots), n_tab = slice256(table);
+    const size_t need = n_rho + n_part + n_yz + n_tab + host.size() / sizeof(double);
+    if (c->coul_cap < need) {
+        if (c->d_coul) (void)hipFree(c->d_coul);
+        c->d_coul = nullptr;
+        c->coul_cap = 0;
+        HUB_TRY(dev_malloc(c, &c->d_coul, need * sizeof(double)));
+        c->coul_cap = need;
+    }
+    double* w = c->d_coul;
+    char* tabs = reinterpret_cast<char*>(w + n_rho + n_part + n_yz + n_tab);
+    CoulombArgs a{};
+    a.sites = reinterpret_cast<CoulombSite*>(tabs + o_sites);
+    a.lines = reinterpret_cast<HubInt2*>(tabs + o_lines);
+    a.planes = reinterpret_cast<HubInt2*>(tabs + o_planes);
+    a.chunks = c->d_chunks;
+    a.chunk_ids = c->d_site_chunk_ids;
+    a.gidx = c->d_gidx;
+    a.images = c->d_images;
+    a.phi = c->d_phi;
+    a.rho = w;
+    a.part = w + n_rho;
+    a.yz = reinterpret_cast<HubInt2*>(w + n_rho + n_part);
+    a.tensor = c->d_tensor;
+    for (int i = 0; i < 3; ++i) {
+        a.ngrid[i] = c->ngrid[i];
+        a.h[i] = c->cell[i] / c->ngrid[i];
+    }
+    a.g0 = hub_g0_cell_average(a.h);
+    a.dV = a.h[0] * a.h[1] * a.h[2];
+    const CoulombItem* d_items = reinterpret_cast<CoulombItem*>(tabs + o_items);
+    hipError_t e = hipMemcpyAsync(tabs, host.data(), host.size(), hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess) e = launch_coulomb_prepare(a, ns, maxplanes, c->stream);
+    for (const Launch& l : launches) {
+        CoulombArgs b = a;
+        if (l.site >= 0) {
+            b.ktab = w + n_rho + n_part + n_yz;
+            if (e == hipSuccess) e = launch_coulomb_table(b, P.sites[l.site], c->stream);
+        }
+        if (e == hipSuccess) e = launch_coulomb_pair(b, d_items + l.item0, l.nitems, l.npad, l.plane, c->stream);
+    }
+    if (e == hipSuccess) e = launch_coulomb_sum(a, ns, maxpair, c->stream);
+    // the copied host tables end with this call, and the scratch is free for
+    // the next one on any stream
+    const hipError_t es = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess) e = es;
+    if (c->coul_cap * sizeof(double) > kCoulombKeep) {
+        (void)hipFree(c->d_coul);
+        c->d_coul = nullptr;
+        c->coul_cap = 0;
+    }
+    if (e != hipSuccess) return map_err(e);
+    for (int s : sites) c->have_tensor[s] = 1;
+    return HUB_OK;
+}
+
 }  // namespace
 
 // =====================================================================  ABI
@@ -1365,51 +1478,31 @@ int hub_coulomb(hub_ctx* c, int site, double* tensor) {
     if (site == -1 && tensor) return HUB_EINVAL;
     // sites with spin-dependent orbitals take a fixed U_eff (no ACBN0 tensor)
     if (site >= 0 && std::isfinite(c->sites[site].zeta_dn)) return HUB_EINVAL;
-    const int s0 = site < 0 ? 0 : site, s1 = site < 0 ? ns : site + 1;
-    size_t maxp = 1;
-    for (int s = s0; s < s1; ++s) maxp = std::max(maxp, c->T.spheres[s].g.size());
-    int32_t* d_ijk = nullptr;
-    double *d_phi = nullptr, *d_rho = nullptr, *d_W = nullptr;
-    hipError_t e = dev_malloc(c, &d_ijk, maxp * 3 * sizeof(int32_t));
-    if (e == hipSuccess) e = dev_malloc(c, &d_phi, maxp * 7 * sizeof(double));
-    if (e == hipSuccess) e = dev_malloc(c, &d_rho, maxp * 28 * sizeof(double));
-    if (e == hipSuccess) e = dev_malloc(c, &d_W, maxp * 28 * sizeof(double));
-    double h[3];
-    for (int i = 0; i < 3; ++i) h[i] = c->cell[i] / c->ngrid[i];
-    const double g0 = hub_g0_cell_average(h);
-    for (int s = s0; s < s1 && e == hipSuccess; ++s) {
-        if (std::isfinite(c->sites[s].zeta_dn)) continue;
-        const SiteSphere& sp = c->T.spheres[s];
-        const int L = c->T.site_L[s];
-        e = hipMemcpyAsync(d_ijk, sp.ijk.data(), sp.ijk.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(d_phi, sp.phi.data(), sp.phi.size() * sizeof(double), hipMemcpyHostToDevice, c->stream);
-        if (e != hipSuccess) break;
-        CoulombArgs a{};
-        a.ijk = d_ijk;
-        a.phi = d_phi;
-        a.P = static_cast<int>(sp.g.size());
-        a.L = L;
-        a.npair = L * (L + 1) / 2;
-        a.rho = d_rho;
-        a.W = d_W;
-        a.tensor = c->d_tensor + static_cast<size_t>(s) * 2401;
-        for (int i = 0; i < 3; ++i) a.h[i] = h[i];
-        a.g0 = g0;
-        a.dV = h[0] * h[1] * h[2];
-        e = launch_coulomb(a, c->stream);
-        if (e == hipSuccess && tensor)
-            e = hipMemcpyAsync(tensor, a.tensor, static_cast<size_t>(L) * L * L * L * sizeof(double),
-                               hipMemcpyDeviceToDevice, c->stream);
-        // host arrays are reused next iteration: wait for the copies
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        if (e == hipSuccess) c->have_tensor[s] = 1;
+    int st = HUB_OK;
+    try {
+        std::vector<int> todo;
+        for (int s = site < 0 ? 0 : site; s < (site < 0 ? ns : site + 1); ++s)
+            if (!std::isfinite(c->sites[s].zeta_dn)) todo.push_back(s);
+        // sites in batches, so that the scratch of many large spheres stays bounded
+        for (size_t i = 0; i < todo.size() && !st;) {
+            std::vector<int> batch;
+            size_t bytes = 0;
+            while (i < todo.size() && (batch.empty() || bytes < kCoulombBatch)) {
+                bytes += c->T.spheres[todo[i]].g.size() * (c->T.site_L[todo[i]] > 5 ? 264 : 136);
+                batch.push_back(todo[i++]);
+            }
+            st = coulomb_batch(c, batch);
+        }
+    } catch (...) {                                  // host tables: out of memory
+        st = HUB_ENOMEM;
     }
-    if (d_ijk) (void)hipFree(d_ijk);
-    if (d_phi) (void)hipFree(d_phi);
-    if (d_rho) (void)hipFree(d_rho);
-    if (d_W) (void)hipFree(d_W);
-    return map_err(e);
+    if (!st && tensor) {
+        const int L = c->T.site_L[site];
+        st = map_err(hipMemcpyAsync(tensor, c->d_tensor + static_cast<size_t>(site) * 2401,
+                                    static_cast<size_t>(L) * L * L * L * sizeof(double), hipMemcpyDeviceToDevice,
+                                    c->stream));
+    }
+    return st;
 }
 
 int hub_get_coulomb(hub_ctx* c, int site, double* tensor) {

@@ -41,8 +41,14 @@ struct SiteDef {
     double zeta_dn;      // spin-down exponent of spinor orbitals; NaN: zeta
 };
 
+struct alignas(8) HubInt2 {
+    int32_t x, y;
+};
+
 // Host copy of one site's sphere, points sorted by (g, image).
 struct SiteSphere {
+    int32_t lo[3] = {}, n[3] = {};           // lowest unfolded coordinates and extents of the points
+    std::vector<HubInt2> lines;              // [n[0]][n[1]] (points, lowest z - lo[2]) along z; no gaps
     std::vector<int32_t> g;      // folded grid index
     std::vector<int32_t> img3;   // lattice image (3 per point)
     std::vector<int32_t> ijk;    // unfolded integer coordinates (3 per point)
@@ -137,6 +143,44 @@ struct StencilTables {
 // Host builder (sphere.cpp).  Returns HUB_OK or a negative status.
 int hub_build_host(const double cell[3], const int ngrid[3], const std::vector<SiteDef>& sites,
                    int chunk_entries, HostTables& out);
+
+// Work list of the Coulomb tensors (k_coulomb.hip): each site's sphere points
+// sorted into planes of constant x, in a plane by (y, z), every plane padded
+// to a multiple of 16 slots.  Slots count from the site's first one.
+struct CoulombSite {
+    int32_t index;           // site of the context
+    int32_t L, npad;         // orbitals; pair densities L (L + 1) / 2 padded to 16 or 32
+    int32_t n[3], lo[3];     // extents and lowest unfolded coordinates of its points
+    int32_t chunk0, chunk1;  // its chunks in site_chunk_ids
+    int32_t line0;           // lines[line0 + x * n[1] + y] = (first slot, lowest z)
+    int32_t plane0;          // planes[plane0 + x] = (first slot, points)
+    int32_t nitems;
+    int64_t slot0;           // first slot in the launch's point arrays
+    int64_t rho0, part0;     // first double of its densities and of its items' sums
+};
+// Targets: nblk blocks of 16 slots of plane x from slot on; sources: slots
+// [s0, s1) of the planes x0..x1 <= x.
+struct CoulombItem {
+    int32_t site;            // position in the plan's sites
+    int32_t x, slot, nblk, x0, x1, s0, s1;
+    int32_t part;            // position among the site's items
+};
+struct CoulombPlan {
+    std::vector<CoulombSite> sites;
+    std::vector<CoulombItem> items;          // site by site
+    std::vector<HubInt2> lines, planes;
+    std::vector<int32_t> item_ptr;           // items of sites[i]: [item_ptr[i], item_ptr[i + 1])
+    int64_t slots = 0, rho = 0, part = 0;    // points, densities and partial sums (doubles)
+};
+// Least 16 x 16 x 4 products per wave that a work item is split to.
+#define HUB_COUL_MINCOST 512
+#define HUB_COUL_MAXBLK 16                   // target blocks per work item, four per wave
+// LDS for a plane of the kernel (|dy| x |dz| doubles); larger planes are read
+// from a table in device memory.
+#define HUB_COUL_LDS 65536
+
+// Plan for the sites which[0..] of the context (sphere.cpp).
+void hub_coulomb_plan(const HostTables& T, const std::vector<int>& which, CoulombPlan& out);
 
 // Closed-form average of 1/|r| over one grid cell centred at the origin.
 double hub_g0_cell_average(const double h[3]);

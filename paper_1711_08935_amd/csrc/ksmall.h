@@ -109,12 +109,20 @@ struct GaugeArgs {
 };
 
 struct CoulombArgs {
-    const int32_t* ijk;        // unfolded integer coordinates of the site's points [P][3]
-    const double* phi;         // [P][L]
-    int P; int L; int npair;
-    double* rho;               // scratch [P][npair]
-    double* W;                 // scratch [P][npair]
-    double* tensor;            // output [L^4]
+    const CoulombSite* sites;                // the plan's tables on the device
+    const HubInt2* lines;
+    const HubInt2* planes;
+    const HubChunk* chunks;                  // per-site work list and its orbital table
+    const int32_t* chunk_ids;
+    const int32_t* gidx;
+    const int32_t* images;
+    const double* phi;
+    int ngrid[3];
+    double* rho;                             // scratch [slot][npad] pair densities
+    HubInt2* yz;                             // scratch [slot] (y, z) as byte offsets into a kernel plane
+    double* part;                            // scratch [item][npad][npad] partial sums
+    double* ktab;                            // kernel planes in device memory, or null: in LDS
+    double* tensor;                          // output [site][2401], L^4 used
     double h[3]; double g0; double dV;
 };
 
@@ -129,7 +137,17 @@ hipError_t launch_energy(const EnergyArgs& a, hipStream_t st);
 hipError_t launch_forces(const ForceArgs& a, hipStream_t st);
 hipError_t launch_fll(const FllArgs& a, hipStream_t st);
 hipError_t launch_gauge_tables(const GaugeArgs& a, hipStream_t st);
-hipError_t launch_coulomb(const CoulombArgs& a, hipStream_t st);
+// Pair densities and offsets of the points of a.sites[0..nsites).
+hipError_t launch_coulomb_prepare(const CoulombArgs& a, int nsites, int maxplanes, hipStream_t st);
+// Kernel planes of one site into a.ktab.
+hipError_t launch_coulomb_table(const CoulombArgs& a, const CoulombSite& S, hipStream_t st);
+// Partial sums of nitems items, all of sites with npad densities; plane: the
+// largest |dy| x |dz| plane among them (a.ktab: one site's, from
+// launch_coulomb_table).
+hipError_t launch_coulomb_pair(const CoulombArgs& a, const CoulombItem* items, int nitems, int npad, int plane,
+                               hipStream_t st);
+// Tensors of a.sites[0..nsites) from their items' sums.
+hipError_t launch_coulomb_sum(const CoulombArgs& a, int nsites, int maxpair, hipStream_t st);
 // p[r * ld + i] = 0 for every row r < rows and scalar i < ncol (elem_bytes 4
 // or 8): clears the used columns of a state-layout buffer, padding untouched.
 hipError_t launch_zero_cols(void* p, int elem_bytes, int64_t rows, int64_t ld, int ncol, hipStream_t st);

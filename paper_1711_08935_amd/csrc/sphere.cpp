@@ -8,6 +8,7 @@
 // and Fig. 1); sphere truncation radius (Sec. II, radius discussion).
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <map>
 #include <numeric>
@@ -146,11 +147,17 @@ int hub_build_host(const double cell[3], const int ngrid[3], const std::vector<S
             hi[i] = static_cast<int64_t>(std::ceil((S.R[i] + S.rc) / h[i])) + 1;
         }
         std::vector<Pt>& P = pts[s];
+        struct Line {
+            int64_t x, y, z;
+            int32_t n;
+        };
+        std::vector<Line> lines;                     // every (x, y) with points, and its lowest z
         for (int64_t jx = lo[0]; jx <= hi[0]; ++jx) {
             const double dx = static_cast<double>(jx) * h[0] - S.R[0];
             for (int64_t jy = lo[1]; jy <= hi[1]; ++jy) {
                 const double dy = static_cast<double>(jy) * h[1] - S.R[1];
                 const double dxy = dx * dx + dy * dy;
+                const size_t first = P.size();
                 for (int64_t jz = lo[2]; jz <= hi[2]; ++jz) {
                     const double dz = static_cast<double>(jz) * h[2] - S.R[2];
                     const double d2 = dxy + dz * dz;
@@ -168,6 +175,8 @@ int hub_build_host(const double cell[3], const int ngrid[3], const std::vector<S
                     p.d[0] = dx; p.d[1] = dy; p.d[2] = dz;
                     P.push_back(p);
                 }
+                if (P.size() > first)
+                    lines.push_back({jx, jy, P[first].ijk[2], static_cast<int32_t>(P.size() - first)});
             }
         }
         if (P.empty()) return HUB_EINVAL;   // a sphere with no grid point has no orbital
@@ -178,6 +187,24 @@ int hub_build_host(const double cell[3], const int ngrid[3], const std::vector<S
         const int L = T.site_L[s];
         SiteSphere& sp = T.spheres[s];
         const size_t np = P.size();
+        {
+            int64_t l0[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, l1[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
+            for (const Line& l : lines) {
+                const int64_t a[3] = {l.x, l.y, l.z}, b[3] = {l.x, l.y, l.z + l.n - 1};
+                for (int i = 0; i < 3; ++i) {
+                    l0[i] = std::min(l0[i], a[i]);
+                    l1[i] = std::max(l1[i], b[i]);
+                }
+            }
+            for (int i = 0; i < 3; ++i) {
+                sp.lo[i] = static_cast<int32_t>(l0[i]);
+                sp.n[i] = static_cast<int32_t>(l1[i] - l0[i] + 1);
+            }
+            sp.lines.assign(static_cast<size_t>(sp.n[0]) * sp.n[1], HubInt2{0, 0});
+            for (const Line& l : lines)
+                sp.lines[static_cast<size_t>(l.x - l0[0]) * sp.n[1] + (l.y - l0[1])] =
+                    HubInt2{l.n, static_cast<int32_t>(l.z - l0[2])};
+        }
         sp.g.resize(np);
         sp.img3.resize(3 * np);
         sp.ijk.resize(3 * np);
@@ -583,6 +610,84 @@ int hub_build_host(const double cell[3], const int ngrid[3], const std::vector<S
             }
     }
     return HUB_OK;
+}
+
+void hub_coulomb_plan(const HostTables& T, const std::vector<int>& which, CoulombPlan& out) {
+    out = CoulombPlan();
+    for (int s : which) {
+        const SiteSphere& sp = T.spheres[s];
+        CoulombSite S{};
+        S.index = s;
+        S.L = T.site_L[s];
+        S.npad = S.L * (S.L + 1) / 2 <= 16 ? 16 : 32;
+        for (int i = 0; i < 3; ++i) {
+            S.lo[i] = sp.lo[i];
+            S.n[i] = sp.n[i];
+        }
+        S.chunk0 = T.site_chunk_ptr[s];
+        S.chunk1 = T.site_chunk_ptr[s + 1];
+        S.line0 = static_cast<int32_t>(out.lines.size());
+        S.plane0 = static_cast<int32_t>(out.planes.size());
+        S.slot0 = out.slots;
+        out.lines.insert(out.lines.end(), sp.lines.begin(), sp.lines.end());
+        HubInt2* ln = &out.lines[S.line0];
+        int32_t slot = 0;
+        for (int x = 0; x < S.n[0]; ++x) {
+            const int32_t first = slot;
+            for (int y = 0; y < S.n[1]; ++y) {
+                HubInt2& l = ln[static_cast<size_t>(x) * S.n[1] + y];
+                const int32_t cnt = l.x;
+                l.x = slot;
+                slot += cnt;
+            }
+            out.planes.push_back(HubInt2{first, slot - first});
+            slot = (slot + 15) / 16 * 16;
+        }
+        S.rho0 = out.rho;
+        out.slots += slot;
+        out.rho += static_cast<int64_t>(slot) * S.npad;
+        out.sites.push_back(S);
+    }
+    for (size_t i = 0; i < out.sites.size(); ++i) {
+        CoulombSite& S = out.sites[i];
+        const int64_t slots = (i + 1 < out.sites.size() ? out.sites[i + 1].slot0 : out.slots) - S.slot0;
+        // A wave's products per item: about 1024 items for a site (4 per CU),
+        // not below MINCOST, where an item's kernel planes and its final sum
+        // would show.  The split depends on the site alone: its tensor has
+        // the same bits whichever sites a call computes.
+        const int64_t budget = std::max<int64_t>(HUB_COUL_MINCOST, slots * slots / 2 / 64 * (S.npad / 16) / 4 / 1024);
+        out.item_ptr.push_back(static_cast<int32_t>(out.items.size()));
+        const HubInt2* pl = &out.planes[S.plane0];
+        for (int x = 0; x < S.n[0]; ++x) {
+            const int nb = (pl[x].y + 15) / 16;
+            const int32_t nsrc = pl[x].x + nb * 16;                    // every slot of the planes 0..x
+            // groups of equal blocks per wave
+            const int nw = (nb + 3) / 4, ng = (4 * nw + HUB_COUL_MAXBLK - 1) / HUB_COUL_MAXBLK;
+            for (int g = 0, b = 0; g < ng; ++g) {
+                const int nblk = std::min(4 * ((nw * (g + 1)) / ng - (nw * g) / ng), nb - b);
+                const int64_t cost = static_cast<int64_t>((nblk + 3) / 4) * (S.npad / 16) * (nsrc / 4);
+                const int32_t ns = static_cast<int32_t>(std::min<int64_t>((cost + budget - 1) / budget, nsrc / 16));
+                for (int32_t t = 0; t < ns; ++t) {
+                    CoulombItem it{};
+                    it.site = static_cast<int32_t>(i);
+                    it.x = x;
+                    it.slot = pl[x].x + 16 * b;
+                    it.nblk = nblk;
+                    it.s0 = static_cast<int32_t>(static_cast<int64_t>(nsrc / 16) * t / ns) * 16;
+                    it.s1 = static_cast<int32_t>(static_cast<int64_t>(nsrc / 16) * (t + 1) / ns) * 16;
+                    while (it.x0 < x && pl[it.x0 + 1].x <= it.s0) ++it.x0;
+                    it.x1 = it.x0;
+                    while (it.x1 < x && pl[it.x1 + 1].x < it.s1) ++it.x1;
+                    it.part = S.nitems++;
+                    out.items.push_back(it);
+                }
+                b += nblk;
+            }
+        }
+        S.part0 = out.part;
+        out.part += static_cast<int64_t>(S.nitems) * S.npad * S.npad;
+    }
+    out.item_ptr.push_back(static_cast<int32_t>(out.items.size()));
 }
 
 int hub_build_stencil(const double cell[3], const int ngrid[3], const std::vector<SiteDef>& sites,
