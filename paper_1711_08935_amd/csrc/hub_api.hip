@@ -76,7 +76,7 @@ struct hub_ctx {
     std::vector<SiteDef> sites;
     int chunk_entries = 512;
     int tune_cpl[2] = {0, 0};
-    int tune_waves[2] = {4, 4};
+    int tune_waves[2] = {0, 0};              // 0: automatic
     int tune_layout[2] = {-1, -1};
     bool built_host = false, built_dev = false;
     HostTables T;
@@ -346,6 +346,24 @@ int pick_wide(const hub_ctx* c, int ncol, int cpl, int which) {
     return ncol >= 64 * cpl ? 1 : 0;
 }
 
+int apply_waves(const hub_ctx* c) { return c->tune_waves[1] ? c->tune_waves[1] : 4; }
+
+// Waves per work-group of a projection launch: one when the launch has
+// enough work-groups of one wave to fill the chip (six waves per CU; no sum
+// over waves, no barrier), four when it has not and the entries of a chunk
+// are better split.  The line lies between 788 work-groups (64 shells' eighth,
+// 1024 FP32 columns: 76 us with one wave, 68 with four) and 1828 (32 d
+// shells, 512 FP32 columns: 154 and 166; the lattice of 64 shells: 530 and
+// 542).  Gradient and moment tables hold 3 L functions per entry, and two
+// waves keep half the sum in registers at a loss of at most 3 % where one is
+// best (fcc 194 / 200 us, nine f/d/p shells in FP64 222 / 176).
+int pick_waves(const hub_ctx* c, int nchunks, int ncol, int cpl, int wide, bool grad) {
+    if (c->tune_waves[0]) return c->tune_waves[0];
+    const int64_t cg = (ncol + cpl - 1) / cpl, nq = c->nsets();
+    const int64_t tiles = wide ? nq * ((cg + HUB_WAVE - 1) / HUB_WAVE) : (nq * cg + HUB_WAVE - 1) / HUB_WAVE;
+    return nchunks * tiles < 1536 ? 4 : (grad ? 2 : 1);
+}
+
 bool built(const hub_ctx* c) { return c && c->built_dev; }
 
 // Batched launches use the grouped work list when it exists.
@@ -548,7 +566,10 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
                 b.chunk_list = list;
                 const int cpl = clamp_cpl(c, pick_cpl(c, psi, ld, 0, ncol), hub_cls_nfmax(k));
                 b.wide = pick_wide(c, ncol, cpl, 0);
-                return launch_project(b, nch, nq, c->precision, c->is_complex, cpl, c->tune_waves[0], k, s);
+                // by the whole list and every state set, so that each class and
+                // each range of sets sums in the same order
+                const int waves = pick_waves(c, static_cast<int>(GT.chunks.size()), ncol, cpl, b.wide, false);
+                return launch_project(b, nch, nq, c->precision, c->is_complex, cpl, waves, k, s);
             });
             if (st) return st;
         }
@@ -584,13 +605,17 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     int cpl = pick_cpl(c, psi, ld, 0, ncol);
     // gradient tiles hold 3L functions, spin-dependent tiles 2L
     if ((grad || spindep) && cpl * c->ncplx() > 4) cpl = 4 / c->ncplx();
+    // 3L functions of four values per lane spill; with two the projection of
+    // 32 d shells (512 FP32 columns) takes 201 us against 213
+    if (grad && !c->tune_cpl[0] && cpl * c->ncplx() > 2) cpl = 2 / c->ncplx();
     a.wide = pick_wide(c, ncol, cpl, 0);
-    const int waves = c->tune_waves[0];
+    const int list = stencil_table(table) ? c->stencil_nchunks : static_cast<int>(c->T.chunks.size());
+    const int waves = per_site ? (c->tune_waves[0] ? c->tune_waves[0] : 4)
+                               : pick_waves(c, list, ncol, cpl, a.wide, grad);
     {
     StageTimer tm(c, grad ? HUB_STAGE_GRADPROJ : HUB_STAGE_PROJECT);
     if (!per_site) {
-        const int nch = stencil_table(table) ? c->stencil_nchunks : static_cast<int>(c->T.chunks.size());
-        HUB_TRY(launch_project(a, nch, nq, c->precision, c->is_complex, cpl, waves, 0, c->stream));
+        HUB_TRY(launch_project(a, list, nq, c->precision, c->is_complex, cpl, waves, 0, c->stream));
     } else {
         for (int s = 0; s < c->T.nsites; ++s) {
             ProjArgs b = a;
@@ -824,8 +849,12 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
         return run_classes(c, [&](int k, const int32_t* list, int nch, hipStream_t s) {
             ApplyArgs b = a;
             b.chunk_list = list;
-            const int cpl = clamp_cpl(c, pick_cpl(c, hpsi, ld, 1, ncol), hub_cls_nfmax(k));
-            return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, c->tune_waves[1], k, s);
+            // one column per lane: the most waves in flight and the fewest idle
+            // lanes in narrow rows (64 complex FP32 columns: 377 us, 452 with
+            // two; in five passes 1.43 ms, 2.48; 1024 real FP32 columns:
+            // 1260 us, 1272 with four)
+            const int cpl = c->tune_cpl[1] ? clamp_cpl(c, pick_cpl(c, hpsi, ld, 1, ncol), hub_cls_nfmax(k)) : 1;
+            return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, apply_waves(c), k, s);
         }, true);
     }
     int cpl = pick_cpl(c, hpsi, ld, 1, ncol);
@@ -837,7 +866,7 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
         if (cpl * c->ncplx() > 4) cpl = 4 / c->ncplx();
     }
     a.wide = pick_wide(c, ncol, cpl, 1);
-    const int waves = c->tune_waves[1];
+    const int waves = apply_waves(c);
     const int ns = c->T.nsites;
     StageTimer tm(c, HUB_STAGE_APPLY);
     for (int lay = 0; lay < c->T.nlayers; ++lay) {
