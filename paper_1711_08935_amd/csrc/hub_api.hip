@@ -348,21 +348,21 @@ int pick_wide(const hub_ctx* c, int ncol, int cpl, int which) {
 
 int apply_waves(const hub_ctx* c) { return c->tune_waves[1] ? c->tune_waves[1] : 4; }
 
-// Waves per work-group of a projection launch: one when the launch has
-// enough work-groups of one wave to fill the chip (six waves per CU; no sum
-// over waves, no barrier), four when it has not and the entries of a chunk
-// are better split.  The line lies between 788 work-groups (64 shells' eighth,
-// 1024 FP32 columns: 76 us with one wave, 68 with four) and 1828 (32 d
-// shells, 512 FP32 columns: 154 and 166; the lattice of 64 shells: 530 and
-// 542).  Gradient and moment tables hold 3 L functions per entry, and two
-// waves keep half the sum in registers at a loss of at most 3 % where one is
-// best (fcc 194 / 200 us, nine f/d/p shells in FP64 222 / 176).
-int pick_waves(const hub_ctx* c, int nchunks, int ncol, int cpl, int wide, bool grad) {
-    if (c->tune_waves[0]) return c->tune_waves[0];
+// Work-groups of a projection launch over nchunks chunks and every state set
+// of the context (a range of sets and a function-count class take the shape
+// of the whole, and so sum in its order).
+int64_t proj_groups(const hub_ctx* c, int nchunks, int ncol, int cpl, int wide) {
     const int64_t cg = (ncol + cpl - 1) / cpl, nq = c->nsets();
-    const int64_t tiles = wide ? nq * ((cg + HUB_WAVE - 1) / HUB_WAVE) : (nq * cg + HUB_WAVE - 1) / HUB_WAVE;
-    return nchunks * tiles < 1536 ? 4 : (grad ? 2 : 1);
+    return nchunks * (wide ? nq * ((cg + HUB_WAVE - 1) / HUB_WAVE) : (nq * cg + HUB_WAVE - 1) / HUB_WAVE);
 }
+// From this many work-groups a launch fills the chip with one or two waves
+// each; below it the entries of a chunk are split over four.  One wave saves
+// the sum over waves: 64 shells, 1024 FP32 columns (6060 work-groups) 572 us
+// with one and four; 32 d shells, 512 FP32 columns (1830) 191 and 200 us; an
+// eighth of the lattice (792) 89 and 78 us.  Gradient tables (3 L functions)
+// take two: the same 32 d shells 216, 221 and 237 us with one, two and four,
+// p/d/f shells in FP64 (2082) 220, 178 and 171 us.
+constexpr int64_t kFullLaunch = 1536;
 
 bool built(const hub_ctx* c) { return c && c->built_dev; }
 
@@ -497,6 +497,7 @@ ReduceArgs reduce_args(hub_ctx* c, const double* part, double* out, int ncol, in
     r.nspin = c->nspin();
     r.spinor = c->spin_mode == HUB_SPINOR;
     r.dV = (c->cell[0] / c->ngrid[0]) * (c->cell[1] / c->ngrid[1]) * (c->cell[2] / c->ngrid[2]);
+    r.chunks_per_site = static_cast<int>(c->T.chunks.size()) / c->T.nsites;
     return r;
 }
 
@@ -566,9 +567,8 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
                 b.chunk_list = list;
                 const int cpl = clamp_cpl(c, pick_cpl(c, psi, ld, 0, ncol), hub_cls_nfmax(k));
                 b.wide = pick_wide(c, ncol, cpl, 0);
-                // by the whole list and every state set, so that each class and
-                // each range of sets sums in the same order
-                const int waves = pick_waves(c, static_cast<int>(GT.chunks.size()), ncol, cpl, b.wide, false);
+                const int64_t groups = proj_groups(c, static_cast<int>(GT.chunks.size()), ncol, cpl, b.wide);
+                const int waves = c->tune_waves[0] ? c->tune_waves[0] : (groups < kFullLaunch ? 4 : 1);
                 return launch_project(b, nch, nq, c->precision, c->is_complex, cpl, waves, k, s);
             });
             if (st) return st;
@@ -605,13 +605,16 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     int cpl = pick_cpl(c, psi, ld, 0, ncol);
     // gradient tiles hold 3L functions, spin-dependent tiles 2L
     if ((grad || spindep) && cpl * c->ncplx() > 4) cpl = 4 / c->ncplx();
-    // 3L functions of four values per lane spill; with two the projection of
-    // 32 d shells (512 FP32 columns) takes 201 us against 213
-    if (grad && !c->tune_cpl[0] && cpl * c->ncplx() > 2) cpl = 2 / c->ncplx();
     a.wide = pick_wide(c, ncol, cpl, 0);
     const int list = stencil_table(table) ? c->stencil_nchunks : static_cast<int>(c->T.chunks.size());
-    const int waves = per_site ? (c->tune_waves[0] ? c->tune_waves[0] : 4)
-                               : pick_waves(c, list, ncol, cpl, a.wide, grad);
+    const bool full = !per_site && proj_groups(c, list, ncol, cpl, a.wide) >= kFullLaunch;
+    // gradients in a launch that does not fill the chip: two values per lane
+    // instead of four (4 d shells, 512 FP32 columns: 42 us against 45)
+    if (grad && !full && !c->tune_cpl[0] && cpl * c->ncplx() > 2) {
+        cpl = 2 / c->ncplx();
+        a.wide = pick_wide(c, ncol, cpl, 0);
+    }
+    const int waves = c->tune_waves[0] ? c->tune_waves[0] : (full ? (grad ? 2 : 1) : 4);
     {
     StageTimer tm(c, grad ? HUB_STAGE_GRADPROJ : HUB_STAGE_PROJECT);
     if (!per_site) {
@@ -638,6 +641,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
         r.chunks = c->d_st_chunks;
         r.site_chunk_ptr = c->d_st_site_ptr;
         r.site_chunk_ids = c->d_st_site_ids;
+        r.chunks_per_site = c->stencil_nchunks / c->T.nsites;
         r.prows = c->stencil_part_rows * 3;
     }
     StageTimer tm(c, HUB_STAGE_REDUCE);

@@ -13,75 +13,22 @@ constexpr int NB = 256;   // threads of the per-site kernels
 constexpr int TILE = 64;  // (k-point, state) pairs staged per LDS tile in k_occ_part
 
 // ---------------------------------------------------------------- reduction
-// out[q][r][col] = dV * sum over the chunks of the row's site of
-// exp(+i k.T_chunk) part[q][chunk.part0 * mult + (r - orb0 * mult)][col]
-// (the Bloch phase of Fig. 1, shared by all entries of a chunk).
-__global__ void __launch_bounds__(256) k_reduce(const ReduceArgs a) {
-    const int col = blockIdx.x * blockDim.x + threadIdx.x;
-    const int r = blockIdx.y;
-    const int q = blockIdx.z;
-    if (col >= a.ncol) return;
-    const int site = a.orb_site[r / a.mult];
-    const int local = r - a.site_orb0[site] * a.mult;
-    const int NC = a.ncplx;
-    const int k = a.spinor ? a.q0 + q : (a.q0 + q) / a.nspin;
-    const double* ph = a.phase + static_cast<int64_t>(k) * a.nimg * 2;
-    double s0 = 0.0, s1 = 0.0;
-    // gradient or moment tables of spin-dependent orbitals: one launch per
-    // spin component, each writing the columns of its component
-    if (a.colpar >= 0 && (col & 1) != a.colpar) return;
-    // spin-dependent orbitals: column 2s + sigma of orbital m is the partial
-    // row sigma L + m of the chunk (the orbital of its spin component)
-    const int srow = a.spindep ? (col & 1) * a.site_L[site] + local : local;
-    for (int t = a.site_chunk_ptr[site]; t < a.site_chunk_ptr[site + 1]; ++t) {
-        const HubChunk& C = a.chunks[a.site_chunk_ids[t]];
-        const int64_t row = static_cast<int64_t>(q) * a.prows + static_cast<int64_t>(C.part0) * a.pmult + srow;
-        const double* p = a.part + (row * a.ncol + col) * NC;
-        if (NC == 2) {
-            const double pr = ph[2 * C.img], pi = ph[2 * C.img + 1];
-            s0 += pr * p[0] - pi * p[1];
-            s1 += pr * p[1] + pi * p[0];
-        } else {
-            s0 += p[0];
-        }
-    }
-    double* o = a.out + ((static_cast<int64_t>(q) * a.nrows + r) * a.ncol + col) * NC;
-    o[0] = a.dV * s0;
-    if (NC == 2) o[1] = a.dV * s1;
-}
-
-// Grouped work list: out[q][j][col] = dV sum over the workspace rows that
-// belong to orbital j of exp(+i k.T_row) part[q][row][col].  A work-group
-// serves 64 columns of one (j, q); each of its RW waves takes a contiguous
-// range of the orbital's rows and walks it in batches of 8: the batch's row
-// indexes and images are uniform (scalar loads), its 8 row values are in
-// flight together (one 8- or 16-byte load per lane each), then added in row
-// order.  The waves' sums are combined in wave order through LDS.  RW
-// follows the rows per orbital.
-template <int RW, int NC>
-__global__ void __launch_bounds__(RW * 64) k_reduce_grouped(const ReduceGroupedArgs a) {
+// Sum over n workspace rows of exp(+i k.T_row) times the lane's value (the
+// Bloch phase of Fig. 1, shared by all entries of a chunk): RW waves of 64
+// columns take contiguous ranges of the rows and walk them in batches of 8;
+// a batch's row indexes and images are uniform (scalar loads) and its 8 row
+// values are in flight together (one 8- or 16-byte load per lane each), then
+// added in row order; the waves' sums are combined in wave order through LDS.
+// row(t): the lane's value of row t; img(t): its image.  The result is in
+// wave 0.
+template <int RW, int NC, typename Row, typename Img>
+__device__ __forceinline__ void reduce_rows(int n, const double* __restrict__ ph, Row&& row, Img&& img, double& r0,
+                                            double& r1) {
     constexpr int NBATCH = 8;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int col = blockIdx.x * 64 + lane;
-    const int j = blockIdx.y;
-    const int ncomp = a.ncomp > 1 ? a.ncomp : 1;
-    const int comp = blockIdx.z % ncomp;
-    const int q = blockIdx.z / ncomp;
-    const bool active = col < a.ncol;
-    const int k = a.spinor ? a.q0 + q : (a.q0 + q) / a.nspin;
-    const double* __restrict__ ph = a.phase + static_cast<int64_t>(k) * a.nimg * 2;
-    // spin-dependent orbitals: spinor column 2s + sigma reads the rows of the
-    // orbital of its spin component
-    const int64_t shift = (a.spin_shift && (col & 1)) ? a.spin_shift[j] : 0;
-    const double* __restrict__ base = a.part + comp * a.pplane +
-                                      (static_cast<int64_t>(q) * a.prows + shift) * a.ncol * NC +
-                                      static_cast<int64_t>(active ? col : 0) * NC;
-    const int t0 = a.red_ptr[j], t1 = a.red_ptr[j + 1];
     int lo, len;
-    hub_wave_range(t1 - t0, RW, wave, lo, len);
-    const int32_t* __restrict__ rows = a.red_row + t0 + lo;
-    const int32_t* __restrict__ imgs = a.red_img + t0 + lo;
+    hub_wave_range(n, RW, wave, lo, len);
     double s0 = 0.0, s1 = 0.0;
     for (int b = 0; b < len; b += NBATCH) {
         const int nb = len - b < NBATCH ? len - b : NBATCH;
@@ -92,13 +39,13 @@ __global__ void __launch_bounds__(RW * 64) k_reduce_grouped(const ReduceGroupedA
             // rows past the wave's range re-read its last row; their values
             // are replaced by zeros below (branch-free, so that every load of
             // the batch is issued before the first add)
-            const int t = b + (u < nb ? u : nb - 1);
-            const double* p = base + static_cast<int64_t>(rows[t]) * a.ncol * NC;
+            const int t = lo + b + (u < nb ? u : nb - 1);
+            const double* p = row(t);
             if constexpr (NC == 2) {
                 const hub_d2 x = *reinterpret_cast<const hub_d2*>(p);
                 v[u][0] = x[0];
                 v[u][1] = x[1];
-                const int im = imgs[t];
+                const int im = img(t);
                 pr[u] = ph[2 * im];
                 pi[u] = ph[2 * im + 1];
             } else {
@@ -122,12 +69,77 @@ __global__ void __launch_bounds__(RW * 64) k_reduce_grouped(const ReduceGroupedA
     red[wave][lane][0] = s0;
     red[wave][lane][1] = s1;
     __syncthreads();
-    if (wave != 0 || !active) return;
-    double r0 = 0.0, r1 = 0.0;
+    r0 = r1 = 0.0;
+    if (wave != 0) return;
     for (int w = 0; w < RW; ++w) {
         r0 += red[w][lane][0];
         r1 += red[w][lane][1];
     }
+}
+
+// Per-site work list: out[q][r][col] = dV * sum over the chunks of the row's
+// site of exp(+i k.T_chunk) part[q][chunk.part0 * mult + (r - orb0 * mult)][col],
+// a work-group per 64 columns of one (row, set).  (One thread per column
+// walking the chunks one by one took 60 us for 328 dilated chunks, 48 rows and
+// 16 sets of 27 complex columns, 15.6 us now, and 21.7 us for 914 chunks, 480
+// rows of 512 real columns, 14.5 us now.)
+template <int RW, int NC>
+__global__ void __launch_bounds__(RW * 64) k_reduce(const ReduceArgs a) {
+    const int col = blockIdx.x * 64 + (threadIdx.x & 63);
+    const int r = blockIdx.y;
+    const int q = blockIdx.z;
+    // gradient or moment tables of spin-dependent orbitals: one launch per
+    // spin component, each writing the columns of its component
+    const bool active = col < a.ncol && !(a.colpar >= 0 && (col & 1) != a.colpar);
+    const int site = a.orb_site[r / a.mult];
+    const int local = r - a.site_orb0[site] * a.mult;
+    const int k = a.spinor ? a.q0 + q : (a.q0 + q) / a.nspin;
+    // spin-dependent orbitals: column 2s + sigma of orbital m is the partial
+    // row sigma L + m of the chunk (the orbital of its spin component)
+    const int srow = a.spindep ? (col & 1) * a.site_L[site] + local : local;
+    const double* __restrict__ base = a.part + ((static_cast<int64_t>(q) * a.prows + srow) * a.ncol +
+                                                (active ? col : 0)) * NC;
+    const int t0 = a.site_chunk_ptr[site], t1 = a.site_chunk_ptr[site + 1];
+    const int32_t* __restrict__ ids = a.site_chunk_ids + t0;
+    const HubChunk* __restrict__ chunks = a.chunks;
+    double r0, r1;
+    reduce_rows<RW, NC>(
+        t1 - t0, a.phase + static_cast<int64_t>(k) * a.nimg * 2,
+        [&](int t) { return base + static_cast<int64_t>(chunks[ids[t]].part0) * a.pmult * a.ncol * NC; },
+        [&](int t) { return chunks[ids[t]].img; }, r0, r1);
+    if (threadIdx.x >= 64 || !active) return;
+    double* o = a.out + ((static_cast<int64_t>(q) * a.nrows + r) * a.ncol + col) * NC;
+    o[0] = a.dV * r0;
+    if (NC == 2) o[1] = a.dV * r1;
+}
+
+// Grouped work list: out[q][j][col] = dV sum over the workspace rows that
+// belong to orbital j of exp(+i k.T_row) part[q][row][col], a work-group per
+// 64 columns of one (j, q).  RW follows the rows per orbital.
+template <int RW, int NC>
+__global__ void __launch_bounds__(RW * 64) k_reduce_grouped(const ReduceGroupedArgs a) {
+    const int col = blockIdx.x * 64 + (threadIdx.x & 63);
+    const int j = blockIdx.y;
+    const int ncomp = a.ncomp > 1 ? a.ncomp : 1;
+    const int comp = blockIdx.z % ncomp;
+    const int q = blockIdx.z / ncomp;
+    const bool active = col < a.ncol;
+    const int k = a.spinor ? a.q0 + q : (a.q0 + q) / a.nspin;
+    // spin-dependent orbitals: spinor column 2s + sigma reads the rows of the
+    // orbital of its spin component
+    const int64_t shift = (a.spin_shift && (col & 1)) ? a.spin_shift[j] : 0;
+    const double* __restrict__ base = a.part + comp * a.pplane +
+                                      (static_cast<int64_t>(q) * a.prows + shift) * a.ncol * NC +
+                                      static_cast<int64_t>(active ? col : 0) * NC;
+    const int t0 = a.red_ptr[j], t1 = a.red_ptr[j + 1];
+    const int32_t* __restrict__ rows = a.red_row + t0;
+    const int32_t* __restrict__ imgs = a.red_img + t0;
+    double r0, r1;
+    reduce_rows<RW, NC>(
+        t1 - t0, a.phase + static_cast<int64_t>(k) * a.nimg * 2,
+        [&](int t) { return base + static_cast<int64_t>(rows[t]) * a.ncol * NC; }, [&](int t) { return imgs[t]; },
+        r0, r1);
+    if (threadIdx.x >= 64 || !active) return;
     double* o = comp == 0 ? a.out + ((static_cast<int64_t>(q) * a.J + j) * a.ncol + col) * NC
                           : a.mout + ((static_cast<int64_t>(q) * a.J * 3 + 3 * j + comp - 1) * a.ncol + col) * NC;
     o[0] = a.dV * r0;
@@ -914,8 +926,15 @@ hipError_t launch_gauge_tables(const GaugeArgs& a, hipStream_t st) {
 
 hipError_t launch_reduce(const ReduceArgs& a, int nq, hipStream_t st) {
     if (a.nrows <= 0 || nq <= 0 || a.ncol <= 0) return hipSuccess;
-    dim3 grid((a.ncol + 255) / 256, a.nrows, nq);
-    hipLaunchKernelGGL(k_reduce, grid, dim3(256), 0, st, a);
+    dim3 grid((a.ncol + 63) / 64, a.nrows, nq);
+    const bool wide = a.chunks_per_site >= 64;
+    if (a.ncplx == 2) {
+        if (wide) hipLaunchKernelGGL((k_reduce<16, 2>), grid, dim3(16 * 64), 0, st, a);
+        else hipLaunchKernelGGL((k_reduce<4, 2>), grid, dim3(4 * 64), 0, st, a);
+    } else {
+        if (wide) hipLaunchKernelGGL((k_reduce<16, 1>), grid, dim3(16 * 64), 0, st, a);
+        else hipLaunchKernelGGL((k_reduce<4, 1>), grid, dim3(4 * 64), 0, st, a);
+    }
     return hipGetLastError();
 }
 

@@ -18,6 +18,7 @@ struct ReduceArgs {
     int nspin; int spinor;                // state set -> k-point
     int q0;                               // context index of the first state set of the launch
     double dV;
+    int chunks_per_site;                  // average (host)
 };
 
 struct ReduceGroupedArgs {
