@@ -143,6 +143,7 @@ struct hub_ctx {
     double* d_st_tab_dn = nullptr;           // spin-down orbitals (spin-dependent contexts)
     double* d_nbar_ws = nullptr;
     size_t nbar_cap = 0;
+    unsigned char* d_cover = nullptr;        // [G] 1: in the grouped list (covered by a sphere)
     double* d_coul = nullptr;                // scratch of the Coulomb tensors (kept while small)
     size_t coul_cap = 0;
     // Workspaces of the call in flight come from the buffers above (grown
@@ -237,7 +238,7 @@ void release(hub_ctx* c) {
     f(c->d_chunks); f(c->d_all); f(c->d_gidx); f(c->d_img); f(c->d_phi); f(c->d_gphi); f(c->d_phase);
     f(c->d_site_chunk_ptr); f(c->d_site_chunk_ids); f(c->d_orb_site); f(c->d_site_L); f(c->d_site_orb0);
     f(c->d_site_species); f(c->d_species_orb_ptr); f(c->d_species_orb_ids); f(c->d_kw); f(c->d_ueff_fixed);
-    f(c->d_tensor); f(c->d_coul); f(c->d_part); f(c->d_grad); f(c->d_nbar_ws); f(c->d_sink); f(c->d_occ_ws);
+    f(c->d_tensor); f(c->d_cover); f(c->d_coul); f(c->d_part); f(c->d_grad); f(c->d_nbar_ws); f(c->d_sink); f(c->d_occ_ws);
     f(c->d_pg); f(c->d_mphi); f(c->d_images); f(c->d_kred);
     c->part_cap = c->coul_cap = c->grad_cap = c->nbar_cap = c->sink_cap = c->occ_cap = 0;
     f(c->d_phi2); f(c->d_gphi_dn); f(c->d_mphi_dn);
@@ -800,9 +801,11 @@ int do_acbn0(hub_ctx* c, const double* n, const double* pbar, double* U, double*
 // only); nq < 0: every set of the context.
 // occ: when not null, each column is also weighted by w_k f_s of its state
 // (f: [nsets][nstates] of the context, kw: the k-point weights).
+// overwrite (grouped list): the covered rows are written, not added to; the
+// first pass holds every covered point once, later passes add to it.
 int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, int nstates, const double* colscale,
              double alpha, void* hpsi, int64_t ld, bool per_site, int q0 = 0, int nq = -1,
-             const double* occ = nullptr) {
+             const double* occ = nullptr, bool overwrite = false) {
     if (nq < 0) nq = c->nsets();
     const int ncol = c->ncol(nstates);
     double* sink = c->ws_fixed ? c->ws_fixed->sink : nullptr;
@@ -849,16 +852,33 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
         a.f_orb = c->d_gf_orb;
         a.f_img = c->d_gf_img;
         StageTimer tm(c, HUB_STAGE_APPLY);
-        // one launch per function-count class; the classes hold disjoint points
-        return run_classes(c, [&](int k, const int32_t* list, int nch, hipStream_t s) {
+        auto launch = [&](int k, const int32_t* list, int nch, hipStream_t s, bool store) {
             ApplyArgs b = a;
             b.chunk_list = list;
             // one column per lane: the most waves in flight and the fewest idle
             // lanes in narrow rows (64 complex FP32 columns: 377 us, 452 with
             // two; in five passes 1.43 ms, 2.48; 1024 real FP32 columns:
             // 1260 us, 1272 with four)
-            const int cpl = c->tune_cpl[1] ? clamp_cpl(c, pick_cpl(c, hpsi, ld, 1, ncol), hub_cls_nfmax(k)) : 1;
-            return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, apply_waves(c), k, s);
+            int cpl = 1;
+            if (c->tune_cpl[1] || store) cpl = clamp_cpl(c, pick_cpl(c, hpsi, ld, 1, ncol), hub_cls_nfmax(k));
+            // rows that are only written: 16 bytes per lane where that leaves
+            // no more lanes idle (512 real FP32 columns 237 us, 325 with one
+            // column; 64 complex ones 244 with one column, 311 with two)
+            auto lanes = [&](int v) { return (ncol + 64 * v - 1) / (64 * v) * v; };
+            while (!c->tune_cpl[1] && cpl > 1 && lanes(cpl / 2) < lanes(cpl)) cpl /= 2;
+            return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, apply_waves(c), k, store, s);
+        };
+        if (overwrite) {
+            const GroupTables& GT = c->T.grouped;
+            const int merged = GT.nfmax <= 8 ? HUB_MERGED8 : HUB_MERGED16;
+            for (int p = 0; p < GT.npass; ++p)
+                HUB_TRY(launch(merged, c->d_gall_m + c->gpass_ptr[p], c->gpass_ptr[p + 1] - c->gpass_ptr[p],
+                               c->stream, p == 0));
+            return HUB_OK;
+        }
+        // one launch per function-count class; the classes hold disjoint points
+        return run_classes(c, [&](int k, const int32_t* list, int nch, hipStream_t s) {
+            return launch(k, list, nch, s, false);
         }, true);
     }
     int cpl = pick_cpl(c, hpsi, ld, 1, ncol);
@@ -1392,6 +1412,9 @@ int hub_finalize(hub_ctx* c, void* stream) {
         c->nmom = static_cast<int>(mom.size());
         up(&c->d_gmom, mom);
         up(&c->d_ggidx, T.grouped.gidx);
+        std::vector<unsigned char> cover(static_cast<size_t>(c->G()), 0);
+        for (int32_t g : T.grouped.gidx) cover[g] = 1;
+        up(&c->d_cover, cover);
         up(&c->d_gtab, T.grouped.tab);
         up(&c->d_gf_orb, T.grouped.f_orb);
         up(&c->d_gf_img, T.grouped.f_img);
@@ -1764,16 +1787,25 @@ int hub_energy_gradient(hub_ctx* c, const void* psi, int64_t ld, int nstates, co
     if (grad_psi && !valid_states(c, grad_psi, ldg, nstates)) return HUB_EINVAL;
     if (grad_R && !valid_states(c, psi, ld, nstates)) return HUB_EINVAL;
     if (grad_psi) {
-        // every used column of every row starts at zero (the apply writes
-        // sphere points only), then grad += scale 2 g_s dV w_k f V_U psi
+        // grad = scale 2 g_s dV w_k f V_U psi on the spheres, zero elsewhere.
+        // Grouped list: the rows of uncovered points are cleared and the
+        // apply writes the others without reading them; per-site layers: all
+        // rows are cleared and every layer adds to them.
         const int ncol = c->ncol(nstates);
-        HUB_TRY(launch_zero_cols(grad_psi, static_cast<int>(c->elem() / c->ncplx()),
-                                 static_cast<int64_t>(c->nsets()) * c->G(), ldg * c->ncplx(), ncol * c->ncplx(),
-                                 c->stream));
+        const bool overwrite = grouped(c);
+        const int64_t rows = static_cast<int64_t>(c->nsets()) * c->G();
+        if (overwrite) {
+            HUB_TRY(launch_zero_uncovered(grad_psi, c->d_cover, rows, c->G(),
+                                          ldg * static_cast<int64_t>(c->elem()), ncol * static_cast<int>(c->elem()),
+                                          c->stream));
+        } else {
+            HUB_TRY(launch_zero_cols(grad_psi, static_cast<int>(c->elem() / c->ncplx()), rows, ldg * c->ncplx(),
+                                     ncol * c->ncplx(), c->stream));
+        }
         const double gs = c->spin_mode == HUB_UNPOLARIZED ? 2.0 : 1.0;
         const double dV = (c->cell[0] / c->ngrid[0]) * (c->cell[1] / c->ngrid[1]) * (c->cell[2] / c->ngrid[2]);
         const int st = do_apply(c, Ueff, n, cc, nstates, nullptr, scale * 2.0 * gs * dV, grad_psi, ldg, false, 0, -1,
-                                f);
+                                f, overwrite);
         if (st) return st;
     }
     if (grad_R) return contract_moments(c, psi, ld, nstates, cc, f, Ueff, n, grad_R, TAB_GRAD, -scale);

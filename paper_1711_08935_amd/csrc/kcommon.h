@@ -170,6 +170,27 @@ __device__ __forceinline__ void store_row(T* __restrict__ p, const T (&v)[N]) {
     store_vec<T, N>(p, v);
 }
 
+template <typename T, int N>
+__device__ __forceinline__ void store_row_stream(T* __restrict__ p, const T (&v)[N]) {
+    if constexpr (sizeof(T) * N == 8 && sizeof(T) == 4) {
+        const hub_f2 t = {v[0], v[1]};
+        __builtin_nontemporal_store(t, reinterpret_cast<hub_f2*>(p));
+    } else if constexpr (sizeof(T) * N >= 16) {
+        constexpr int per = 16 / sizeof(T);
+        using V = typename std::conditional<sizeof(T) == 4, hub_f4, hub_d2>::type;
+#pragma unroll
+        for (int i = 0; i < N / per; ++i) {
+            V t;
+#pragma unroll
+            for (int k = 0; k < per; ++k) t[k] = v[i * per + k];
+            __builtin_nontemporal_store(t, reinterpret_cast<V*>(p + i * per));
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) __builtin_nontemporal_store(v[i], p + i);
+    }
+}
+
 // Rows per batch of the software-pipelined entry loops: the two batches of
 // U rows of NV values per lane stay within 32 values, and the orbital values
 // of one batch (U x NF doubles, uniform, held in scalar registers) within
@@ -253,6 +274,11 @@ hipError_t launch_apply_grouped_f32(const ApplyArgs& a, int nchunks, int nq, int
                                     int cls, hipStream_t st);
 hipError_t launch_apply_grouped_f64(const ApplyArgs& a, int nchunks, int nq, int cplx, int cpl, int waves,
                                     int cls, hipStream_t st);
+// the grouped apply with its rows overwritten (merged classes)
+hipError_t launch_store_grouped_f32(const ApplyArgs& a, int nchunks, int nq, int cplx, int cpl, int waves, int cls,
+                                    hipStream_t st);
+hipError_t launch_store_grouped_f64(const ApplyArgs& a, int nchunks, int nq, int cplx, int cpl, int waves, int cls,
+                                    hipStream_t st);
 
 // cls: function-count class of the chunks in a.chunk_list (0: per-site list)
 inline hipError_t launch_project(const ProjArgs& a, int nchunks, int nq, int prec, int cplx, int cpl, int waves,
@@ -266,7 +292,10 @@ inline hipError_t launch_apply(const ApplyArgs& a, int nchunks, int nq, int prec
                            : launch_apply_f32(a, nchunks, nq, cplx, cpl, waves, st);
 }
 inline hipError_t launch_apply_grouped(const ApplyArgs& a, int nchunks, int nq, int prec, int cplx, int cpl,
-                                       int waves, int cls, hipStream_t st) {
+                                       int waves, int cls, bool store, hipStream_t st) {
+    if (store)
+        return prec == HUB_F64 ? launch_store_grouped_f64(a, nchunks, nq, cplx, cpl, waves, cls, st)
+                               : launch_store_grouped_f32(a, nchunks, nq, cplx, cpl, waves, cls, st);
     return prec == HUB_F64 ? launch_apply_grouped_f64(a, nchunks, nq, cplx, cpl, waves, cls, st)
                            : launch_apply_grouped_f32(a, nchunks, nq, cplx, cpl, waves, cls, st);
 }

@@ -152,3 +152,7 @@ hipError_t launch_coulomb_sum(const CoulombArgs& a, int nsites, int maxpair, hip
 // p[r * ld + i] = 0 for every row r < rows and scalar i < ncol (elem_bytes 4
 // or 8): clears the used columns of a state-layout buffer, padding untouched.
 hipError_t launch_zero_cols(void* p, int elem_bytes, int64_t rows, int64_t ld, int ncol, hipStream_t st);
+// The first usedbytes of every row r < rows (of rowbytes each) whose grid
+// point r % G is not covered are set to zero.
+hipError_t launch_zero_uncovered(void* p, const unsigned char* cover, int64_t rows, int64_t G, int64_t rowbytes,
+                                 int usedbytes, hipStream_t st);
