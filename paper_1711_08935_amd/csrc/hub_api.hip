@@ -107,7 +107,8 @@ struct hub_ctx {
     std::vector<int> gpass_ptr;              // d_gall_m[gpass_ptr[p], gpass_ptr[p+1]): chunks of pass p
     int gcls_ptr[HUB_NCLASS + 1] = {};       // d_gall[gcls_ptr[k-1], gcls_ptr[k]): chunks of class k
     HubChunk* d_gchunks = nullptr;
-    int32_t *d_gall = nullptr, *d_ggidx = nullptr, *d_gf_orb = nullptr, *d_gf_img = nullptr;
+    int32_t *d_gall = nullptr, *d_ggidx = nullptr;
+    HubFun* d_gfun = nullptr;                // [chunk][HUB_GF_MAX] functions of the grouped chunks
     int32_t *d_gred_ptr = nullptr, *d_gred_row = nullptr, *d_gred_img = nullptr;
     int32_t* d_gspin_shift = nullptr;        // spin-dependent orbitals: L per orbital
     double* d_gtab = nullptr;
@@ -243,7 +244,7 @@ void release(hub_ctx* c) {
     c->part_cap = c->coul_cap = c->grad_cap = c->nbar_cap = c->sink_cap = c->occ_cap = 0;
     f(c->d_phi2); f(c->d_gphi_dn); f(c->d_mphi_dn);
     f(c->d_st_chunks); f(c->d_st_all); f(c->d_st_gidx); f(c->d_st_site_ptr); f(c->d_st_site_ids); f(c->d_st_tab); f(c->d_st_tab_dn);
-    f(c->d_gchunks); f(c->d_gall); f(c->d_gall_m); f(c->d_gmom); f(c->d_ggidx); f(c->d_gf_orb); f(c->d_gf_img); f(c->d_gred_ptr);
+    f(c->d_gchunks); f(c->d_gall); f(c->d_gall_m); f(c->d_gmom); f(c->d_ggidx); f(c->d_gfun); f(c->d_gred_ptr);
     f(c->d_gred_row); f(c->d_gred_img); f(c->d_gtab); f(c->d_gspin_shift); f(c->d_gd0); f(c->d_gfdel);
     drop_graph(c);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
@@ -365,6 +366,32 @@ int64_t proj_groups(const hub_ctx* c, int nchunks, int ncol, int cpl, int wide) 
 // p/d/f shells in FP64 (2082) 220, 178 and 171 us.
 constexpr int64_t kFullLaunch = 1536;
 
+// Work-groups that share a chunk's entries in one column tile: a launch of
+// few work-groups waits for one batch of rows after another, so its chunks
+// are split (by powers of two, waves of at least 8 entries) up to
+// kSplitGroups work-groups of four waves.  A projection then writes one
+// partial row per split, at most 16 MB of them (per function of an orbital),
+// which the reduction reads.  Up to 512, 1024 and none: one d shell's step
+// 37 / 40 / 52 us, a small spinor step 82 / 82 / 104 us, four d shells with
+// 512 columns 109 / 116 / 111 us.
+constexpr int64_t kSplitGroups = 512;
+int split_of(const hub_ctx* c, int64_t groups, double row_bytes) {
+    int s = 1;
+    while (s < 16 && groups * s * 2 <= kSplitGroups && s * 2 * 32 <= c->chunk_entries &&
+           row_bytes * s * 2 <= 16.0 * (1 << 20))
+        s *= 2;
+    return s;
+}
+int proj_split(const hub_ctx* c, int nchunks, int64_t rows, int ncol, int cpl, int wide) {
+    return split_of(c, proj_groups(c, nchunks, ncol, cpl, wide),
+                    8.0 * c->nsets() * rows * ncol * c->ncplx());
+}
+int ilog2(int v) {
+    int l = 0;
+    while (v > 1) v >>= 1, ++l;
+    return l;
+}
+
 bool built(const hub_ctx* c) { return c && c->built_dev; }
 
 // Batched launches use the grouped work list when it exists.
@@ -471,6 +498,7 @@ ProjArgs proj_args(hub_ctx* c, const void* psi, int64_t ld, int ncol, int table)
         a.prows = c->stencil_part_rows * 3;
     }
     a.pg = c->gauge ? c->d_pg : nullptr;
+    a.split = 1;
     return a;
 }
 
@@ -504,8 +532,12 @@ ReduceArgs reduce_args(hub_ctx* c, const double* part, double* out, int ncol, in
 
 // project + reduce into c (per_site: one projection launch per site)
 size_t part_need(const hub_ctx* c, int ncol, int mult) {
-    int64_t rows = std::max<int64_t>(c->T.part_rows * mult, c->T.grouped.ok ? c->T.grouped.part_rows : 0);
-    if (mult == 3) rows = std::max<int64_t>(rows, c->stencil_part_rows * 3);
+    // the split of the widest lanes, the largest
+    auto rows_of = [&](int nchunks, int64_t r) { return r * proj_split(c, nchunks, r, ncol, 4, 0); };
+    int64_t rows = rows_of(static_cast<int>(c->T.chunks.size()), c->T.part_rows) * mult;
+    if (c->T.grouped.ok)
+        rows = std::max<int64_t>(rows, rows_of(static_cast<int>(c->T.grouped.chunks.size()), c->T.grouped.part_rows));
+    if (mult == 3) rows = std::max<int64_t>(rows, rows_of(c->stencil_nchunks, c->stencil_part_rows) * 3);
     return static_cast<size_t>(c->nsets()) * rows * ncol * c->ncplx();
 }
 // the grouped projection with the three position-moment components as well
@@ -551,6 +583,12 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
         a.tabmult = 1;               // grouped chunks count their functions in C.L
         a.prows = GT.part_rows;
         const int64_t pplane = static_cast<int64_t>(nq) * GT.part_rows * ncol * c->ncplx();
+        const int nall = static_cast<int>(GT.chunks.size());
+        if (!mout) {
+            const int cpl = clamp_cpl(c, pick_cpl(c, psi, ld, 0, ncol), HUB_GF_MAX);
+            a.split = proj_split(c, nall, GT.part_rows, ncol, cpl, pick_wide(c, ncol, cpl, 0));
+            a.prows = GT.part_rows * a.split;
+        }
         if (mout) {
             // orbitals and position moments in one launch over every chunk
             a.chunk_list = c->d_gmom;
@@ -568,7 +606,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
                 b.chunk_list = list;
                 const int cpl = clamp_cpl(c, pick_cpl(c, psi, ld, 0, ncol), hub_cls_nfmax(k));
                 b.wide = pick_wide(c, ncol, cpl, 0);
-                const int64_t groups = proj_groups(c, static_cast<int>(GT.chunks.size()), ncol, cpl, b.wide);
+                const int64_t groups = proj_groups(c, nall, ncol, cpl, b.wide);
                 const int waves = c->tune_waves[0] ? c->tune_waves[0] : (groups < kFullLaunch ? 4 : 1);
                 return launch_project(b, nch, nq, c->precision, c->is_complex, cpl, waves, k, s);
             });
@@ -576,7 +614,8 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
         }
         ReduceGroupedArgs r{};
         r.part = part;
-        r.prows = GT.part_rows;
+        r.prows = a.prows;
+        r.split_log2 = ilog2(a.split);
         r.out = out;
         r.J = c->T.J;
         r.ncol = ncol;
@@ -616,6 +655,10 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
         a.wide = pick_wide(c, ncol, cpl, 0);
     }
     const int waves = c->tune_waves[0] ? c->tune_waves[0] : (full ? (grad ? 2 : 1) : 4);
+    if (!per_site) {
+        a.split = proj_split(c, list, stencil_table(table) ? c->stencil_part_rows : c->T.part_rows, ncol, cpl, a.wide);
+        a.prows *= a.split;
+    }
     {
     StageTimer tm(c, grad ? HUB_STAGE_GRADPROJ : HUB_STAGE_PROJECT);
     if (!per_site) {
@@ -636,15 +679,15 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
         // column 2s + sigma takes the rows of its spin component's orbitals
         r.pmult = 2;
         r.spindep = 1;
-        r.prows = c->T.part_rows * 2;
     }
     if (stencil_table(table)) {
         r.chunks = c->d_st_chunks;
         r.site_chunk_ptr = c->d_st_site_ptr;
         r.site_chunk_ids = c->d_st_site_ids;
         r.chunks_per_site = c->stencil_nchunks / c->T.nsites;
-        r.prows = c->stencil_part_rows * 3;
     }
+    r.prows = a.prows;
+    r.split_log2 = ilog2(a.split);
     StageTimer tm(c, HUB_STAGE_REDUCE);
     HUB_TRY(launch_reduce(r, nq, c->stream));
     return HUB_OK;
@@ -840,32 +883,36 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
     a.occ = occ;
     a.kw = c->d_kw;
     a.alpha = alpha;
-    a.orb_site = c->d_orb_site;
     a.site_orb0 = c->d_site_orb0;
     a.site_L = c->d_site_L;
+    a.split = 1;
     a.spindep = c->T.spindep ? 1 : 0;
     if (!per_site && grouped(c)) {
         a.wide = 1;
         a.chunks = c->d_gchunks;
         a.gidx = c->d_ggidx;
         a.tab = c->d_gtab;
-        a.f_orb = c->d_gf_orb;
-        a.f_img = c->d_gf_img;
+        a.fun = c->d_gfun;
         StageTimer tm(c, HUB_STAGE_APPLY);
         auto launch = [&](int k, const int32_t* list, int nch, hipStream_t s, bool store) {
             ApplyArgs b = a;
             b.chunk_list = list;
-            // one column per lane: the most waves in flight and the fewest idle
-            // lanes in narrow rows (64 complex FP32 columns: 377 us, 452 with
-            // two; in five passes 1.43 ms, 2.48; 1024 real FP32 columns:
-            // 1260 us, 1272 with four)
-            int cpl = 1;
-            if (c->tune_cpl[1] || store) cpl = clamp_cpl(c, pick_cpl(c, hpsi, ld, 1, ncol), hub_cls_nfmax(k));
-            // rows that are only written: 16 bytes per lane where that leaves
-            // no more lanes idle (512 real FP32 columns 237 us, 325 with one
-            // column; 64 complex ones 244 with one column, 311 with two)
+            // One column per lane where that gives the chip enough work-groups:
+            // the most waves in flight (1024 real FP32 columns, 24 000 groups:
+            // 1260 us, 1272 with four columns; 400 columns, 4865 groups: 232
+            // and 242).  Else, and for rows that are only written, 16 bytes per
+            // lane (four d shells, 512 columns, 944 groups: 53 us, 57 with one
+            // column; written rows of 32 d shells 237 and 325), but never with
+            // more lanes idle than narrower ones leave (64 complex FP32
+            // columns: 377 us with one column, 452 with two; in five passes
+            // 1.43 and 2.48 ms).
             auto lanes = [&](int v) { return (ncol + 64 * v - 1) / (64 * v) * v; };
+            const bool full = static_cast<int64_t>(nch) * nq * lanes(1) >= 4096;
+            int cpl = 1;
+            if (c->tune_cpl[1] || store || !full)
+                cpl = clamp_cpl(c, pick_cpl(c, hpsi, ld, 1, ncol), hub_cls_nfmax(k));
             while (!c->tune_cpl[1] && cpl > 1 && lanes(cpl / 2) < lanes(cpl)) cpl /= 2;
+            b.split = split_of(c, static_cast<int64_t>(nch) * nq * lanes(cpl) / cpl, 0.0);
             return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, apply_waves(c), k, store, s);
         };
         if (overwrite) {
@@ -1416,8 +1463,15 @@ int hub_finalize(hub_ctx* c, void* stream) {
         for (int32_t g : T.grouped.gidx) cover[g] = 1;
         up(&c->d_cover, cover);
         up(&c->d_gtab, T.grouped.tab);
-        up(&c->d_gf_orb, T.grouped.f_orb);
-        up(&c->d_gf_img, T.grouped.f_img);
+        std::vector<HubFun> fun(T.grouped.f_orb.size(), HubFun{});
+        for (size_t i = 0; i < fun.size(); ++i) {
+            if (T.grouped.f_orb[i] < 0) continue;
+            // orbitals of the spin-down component are stored as j + J
+            const int sg = T.grouped.f_orb[i] / T.J, j = T.grouped.f_orb[i] - sg * T.J;
+            const int site = T.orb_site[j], o0 = T.site_orb0[site];
+            fun[i] = HubFun{site, o0, T.site_L[site], j - o0, T.grouped.f_img[i], T.spindep ? sg : -1, {0, 0}};
+        }
+        up(&c->d_gfun, fun);
         up(&c->d_gred_ptr, T.grouped.red_ptr);
         up(&c->d_gred_row, T.grouped.red_row);
         up(&c->d_gred_img, T.grouped.red_img);

@@ -58,6 +58,13 @@ struct SiteSphere {
     std::vector<double> grad_dn; // [p][m][3], their gradients
 };
 
+// One function of a grouped chunk as the apply reads it: orbital m (first
+// orbital o0, L orbitals) of a site, seen through a lattice image; spin: the
+// component whose orbital it is (spin-dependent orbitals), else -1.
+struct alignas(32) HubFun {
+    int32_t site, o0, L, m, img, spin, pad[2];
+};
+
 // Largest number of functions (orbitals of all covering sites) a grouped
 // chunk may carry; the covers of a point with more are split over passes
 // of at most this many functions each.

@@ -45,21 +45,20 @@ namespace {
 // other spin component when the function is the orbital of component sgf
 // (spin-dependent orbitals; sgf < 0: both components).
 template <bool CPX, bool SPINOR, int CPL>
-__device__ __forceinline__ void coefficient(const ApplyArgs& a, int site, int ai, int img, int q, int col0,
-                                            double (&Bf)[CPL * (CPX ? 2 : 1)], int sgf = -1) {
+__device__ __forceinline__ void coefficient(const ApplyArgs& a, const HubFun& F, int q, int col0,
+                                            double (&Bf)[CPL * (CPX ? 2 : 1)]) {
     constexpr int NC = CPX ? 2 : 1;
     // q counts the launch's state sets; q0 + q is the context's set (k-point, spin)
     const int ch = SPINOR ? 0 : ((a.q0 + q) % a.nspin);
     const int k = a.spinor ? a.q0 + q : (a.q0 + q) / a.nspin;
-    const int o0 = a.site_orb0[site];
-    const int L = a.site_L[site];
-    const double U = a.ueff[site];
-    const double* __restrict__ nb = a.n + static_cast<int64_t>(site) * a.nblk * 98;
-    const double* __restrict__ cq = a.c + (static_cast<int64_t>(q) * a.J + o0) * a.ncol * NC;
+    const int L = F.L, ai = F.m, sgf = F.spin;
+    const double U = a.ueff[F.site];
+    const double* __restrict__ nb = a.n + static_cast<int64_t>(F.site) * a.nblk * 98;
+    const double* __restrict__ cq = a.c + (static_cast<int64_t>(q) * a.J + F.o0) * a.ncol * NC;
     double pr = 1.0, pi = 0.0;
     if constexpr (CPX) {
-        pr = a.phase[(static_cast<int64_t>(k) * a.nimg + img) * 2];
-        pi = -a.phase[(static_cast<int64_t>(k) * a.nimg + img) * 2 + 1];
+        pr = a.phase[(static_cast<int64_t>(k) * a.nimg + F.img) * 2];
+        pi = -a.phase[(static_cast<int64_t>(k) * a.nimg + F.img) * 2 + 1];
     }
 #pragma unroll
     for (int cc = 0; cc < CPL; ++cc) {
@@ -78,37 +77,42 @@ __device__ __forceinline__ void coefficient(const ApplyArgs& a, int site, int ai
         if (!ok || (sgf >= 0 && (col & 1) != sgf)) sc = 0.0;
         const int colc = ok ? col : 0;
         double br = 0.0, bi = 0.0;
-        if constexpr (!SPINOR) {
-            const double* __restrict__ nm = nb + ch * 98;
-#pragma unroll 1
-            for (int b = 0; b < L; ++b) {
-                // V_ab = U (delta_ab / 2 - n_ba)
-                const double vr = U * ((ai == b ? 0.5 : 0.0) - nm[(b * 7 + ai) * 2]);
-                const double cr = cq[(static_cast<int64_t>(b) * a.ncol + colc) * NC];
+        // The seven values of the largest shell are loaded together (a short
+        // shell re-reads its first one and leaves the copies out), so that a
+        // work-group waits for the projections once and not L times.
+        constexpr int NT = SPINOR ? 2 : 1;
+        const int sg = SPINOR ? (colc & 1) : 0;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            // spinor columns 2s + sigma; V^{sigma sigma'}_ab = U (dd/2 - n^{sigma' sigma}_ba):
+            // block (sigma' = t, sigma = sg); else V_ab = U (delta_ab / 2 - n_ba)
+            const double* __restrict__ nm = nb + (SPINOR ? (2 * t + sg) : ch) * 98;
+            const int64_t cl = SPINOR ? colc - sg + t : colc;
+            double v[HUB_LMAX][2], x[HUB_LMAX][2];
+#pragma unroll
+            for (int b = 0; b < HUB_LMAX; ++b) {
+                const int bb = b < L ? b : 0;
+                const double* __restrict__ np = nm + (bb * 7 + ai) * 2;
+                const double* __restrict__ cp = cq + (static_cast<int64_t>(bb) * a.ncol + cl) * NC;
+                v[b][0] = np[0];
+                x[b][0] = cp[0];
                 if constexpr (CPX) {
-                    const double vi = -U * nm[(b * 7 + ai) * 2 + 1];
-                    const double ci = cq[(static_cast<int64_t>(b) * a.ncol + colc) * NC + 1];
-                    br = fma(vr, cr, fma(-vi, ci, br));
-                    bi = fma(vr, ci, fma(vi, cr, bi));
-                } else {
-                    br = fma(vr, cr, br);
+                    v[b][1] = np[1];
+                    x[b][1] = cp[1];
                 }
             }
-        } else {
-            // spinor columns 2s + sigma; V^{sigma sigma'}_ab = U (dd/2 - n^{sigma' sigma}_ba)
-            const int sg = colc & 1;
-            const int base = colc - sg;
-#pragma unroll 1
-            for (int t = 0; t < 2; ++t) {
-                const double* __restrict__ nm = nb + (2 * t + sg) * 98;   // block (sigma' = t, sigma = sg)
-#pragma unroll 1
-                for (int b = 0; b < L; ++b) {
-                    const double vr = U * ((ai == b && t == sg) ? 0.5 : 0.0) - U * nm[(b * 7 + ai) * 2];
-                    const double vi = -U * nm[(b * 7 + ai) * 2 + 1];
-                    const double cr = cq[(static_cast<int64_t>(b) * a.ncol + base + t) * 2];
-                    const double ci = cq[(static_cast<int64_t>(b) * a.ncol + base + t) * 2 + 1];
-                    br = fma(vr, cr, fma(-vi, ci, br));
-                    bi = fma(vr, ci, fma(vi, cr, bi));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int b = 0; b < HUB_LMAX; ++b) {
+                if (b >= L) break;
+                const bool diag = ai == b && (!SPINOR || t == sg);
+                const double vr = SPINOR ? U * (diag ? 0.5 : 0.0) - U * v[b][0] : U * ((diag ? 0.5 : 0.0) - v[b][0]);
+                if constexpr (CPX) {
+                    const double vi = -U * v[b][1];
+                    br = fma(vr, x[b][0], fma(-vi, x[b][1], br));
+                    bi = fma(vr, x[b][1], fma(vi, x[b][0], bi));
+                } else {
+                    br = fma(vr, x[b][0], br);
                 }
             }
         }
@@ -124,7 +128,8 @@ __device__ __forceinline__ void coefficient(const ApplyArgs& a, int site, int ai
 }
 
 // Bs: LDS of the work-group, at least L * NV * HUB_WAVE doubles.
-// chunk: the chunk's index in the work-group's launch list; tile: column tile.
+// ci: the chunk's index; slot_tile: column tile times split plus the part of
+// the chunk's entries that the work-group takes.
 // L: functions per entry; SPINDEP: per-site chunks of spin-dependent orbitals,
 // function sigma * (L/2) + m is orbital m of spin component sigma, whose
 // coefficient is nonzero only in that component's columns.
@@ -134,7 +139,7 @@ __device__ __forceinline__ void coefficient(const ApplyArgs& a, int site, int ai
 // ordinary ones; 512 real columns the same).
 template <typename T, bool CPX, bool SPINOR, int CPL, int L, bool WIDE, bool GROUPED, bool GAUGE,
           bool SPINDEP = false, bool STORE = false>
-__device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C, int chunk_slot, int tile,
+__device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C, int ci, int slot_tile,
                                            const int32_t* __restrict__ gidx, const double* __restrict__ tab,
                                            const double* __restrict__ pg, T* __restrict__ hpsi, double* Bs) {
     constexpr int NC = CPX ? 2 : 1;
@@ -145,6 +150,7 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / HUB_WAVE);
     const int nw = blockDim.x / HUB_WAVE;
     const int cg = (a.ncol + CPL - 1) / CPL;
+    const int tile = slot_tile / a.split, part_of = slot_tile - tile * a.split;
     int q, col0;
     bool active;
     if constexpr (WIDE) {
@@ -162,27 +168,19 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C
     // coefficients: the waves split the functions (lanes past the last
     // column compute zeros for column 0 of their set and are then idle)
     for (int f = wave; f < L; f += nw) {
-        int site, ai, img;
-        int sgf = -1;
+        HubFun F;
         if constexpr (GROUPED) {
-            const int chunk = a.chunk_list[chunk_slot];
-            int j = a.f_orb[chunk * HUB_GF_MAX + f];
-            if (a.spindep) {
-                // function of the spin component sgf's orbital j (stored as j + sgf J)
-                sgf = j >= a.J ? 1 : 0;
-                j -= sgf * a.J;
-            }
-            img = a.f_img[chunk * HUB_GF_MAX + f];
-            site = a.orb_site[j];
-            ai = j - a.site_orb0[site];
+            F = a.fun[ci * HUB_GF_MAX + f];
         } else {
-            site = C.site;
-            ai = SPINDEP ? f % C.L : f;
-            img = C.img;
+            F.site = C.site;
+            F.o0 = a.site_orb0[C.site];
+            F.L = C.L;
+            F.m = SPINDEP ? f % C.L : f;
+            F.img = C.img;
+            F.spin = SPINDEP ? f / C.L : -1;
         }
         double Bf[NV];
-        if constexpr (SPINDEP) sgf = f / C.L;
-        coefficient<CPX, SPINOR, CPL>(a, site, ai, img, q, active ? col0 : a.ncol, Bf, sgf);
+        coefficient<CPX, SPINOR, CPL>(a, F, q, active ? col0 : a.ncol, Bf);
 #pragma unroll
         for (int v = 0; v < NV; ++v) Bs[(f * NV + v) * HUB_WAVE + lane] = Bf[v];
     }
@@ -197,7 +195,7 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C
     T* __restrict__ h_q = hpsi + static_cast<int64_t>(q) * a.qstride;
     // this wave's entries: e0 + [lo, lo + nj) of the chunk
     int lo, nj;
-    hub_wave_range(C.ne, nw, wave, lo, nj);
+    hub_entry_range(C.ne, nw * a.split, part_of * nw + wave, lo, nj);
     const int32_t* __restrict__ gi = gidx + C.e0 + lo;
     const double* __restrict__ tb = tab + (C.phi0 * (SPINDEP ? 2 : 1) + static_cast<int64_t>(lo) * L);
     const int lofs = col0 * NC;
@@ -298,10 +296,11 @@ __global__ void __launch_bounds__(256) k_apply(const ApplyArgs a, const int32_t*
     __shared__ double Bs[7 * M * NV * HUB_WAVE];
     const HubSlot slot = hub_slot(a.tiles);
     if (slot.chunk >= a.nchunks) return;
-    const HubChunk C = a.chunks[a.chunk_list[slot.chunk]];
+    const int ci = a.chunk_list[slot.chunk];
+    const HubChunk C = a.chunks[ci];
     switch (C.L) {
 #define HUB_PCALL(n) \
-    apply_body<T, CPX, SPINOR, CPL, M * n, WIDE, false, GAUGE, SPINDEP>(a, C, slot.chunk, slot.tile, gidx, tab, pg, \
+    apply_body<T, CPX, SPINOR, CPL, M * n, WIDE, false, GAUGE, SPINDEP>(a, C, ci, slot.tile, gidx, tab, pg, \
                                                                         hpsi, Bs)
     case 1: HUB_PCALL(1); break;
     case 3: HUB_PCALL(3); break;
@@ -327,9 +326,10 @@ k_apply_grouped(const ApplyArgs a, const int32_t* __restrict__ gidx,
     __shared__ double Bs[NFMAX * NV * HUB_WAVE];
     const HubSlot slot = hub_slot(a.tiles);
     if (slot.chunk >= a.nchunks) return;
-    const HubChunk C = a.chunks[a.chunk_list[slot.chunk]];
+    const int ci = a.chunk_list[slot.chunk];
+    const HubChunk C = a.chunks[ci];
 #define HUB_ACALL(n) \
-    apply_body<T, CPX, SPINOR, CPL, (n), WIDE, true, GAUGE, false, STORE>(a, C, slot.chunk, slot.tile, gidx, tab, pg, \
+    apply_body<T, CPX, SPINOR, CPL, (n), WIDE, true, GAUGE, false, STORE>(a, C, ci, slot.tile, gidx, tab, pg, \
                                                                           hpsi, Bs)
 #define HUB_ACASE(n)                      \
     case n:                               \
@@ -367,7 +367,7 @@ hipError_t launch_tg(const ApplyArgs& a, int nchunks, int nq, int waves, hipStre
         const int64_t cg = (a.ncol + CPL - 1) / CPL;
         ApplyArgs b = a;
         b.nchunks = nchunks;
-        b.tiles = static_cast<int>(static_cast<int64_t>(nq) * ((cg + HUB_WAVE - 1) / HUB_WAVE));
+        b.tiles = static_cast<int>(static_cast<int64_t>(nq) * ((cg + HUB_WAVE - 1) / HUB_WAVE)) * a.split;
         const dim3 grid(static_cast<unsigned>(hub_slot_grid(nchunks, b.tiles)));
         if (a.pg) {
             // velocity gauge: complex states, merged launch only
@@ -407,7 +407,7 @@ hipError_t launch_t(const ApplyArgs& a, int nchunks, int nq, int waves, hipStrea
     ApplyArgs b = a;
     b.nchunks = nchunks;
     b.tiles = static_cast<int>(a.wide ? static_cast<int64_t>(nq) * ((cg + HUB_WAVE - 1) / HUB_WAVE)
-                                      : (static_cast<int64_t>(nq) * cg + HUB_WAVE - 1) / HUB_WAVE);
+                                      : (static_cast<int64_t>(nq) * cg + HUB_WAVE - 1) / HUB_WAVE) * a.split;
     const dim3 grid(static_cast<unsigned>(hub_slot_grid(nchunks, b.tiles)));
     T* h = reinterpret_cast<T*>(b.hpsi);
     if (a.spindep) {

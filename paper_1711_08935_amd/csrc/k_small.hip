@@ -97,16 +97,19 @@ __global__ void __launch_bounds__(RW * 64) k_reduce(const ReduceArgs a) {
     // spin-dependent orbitals: column 2s + sigma of orbital m is the partial
     // row sigma L + m of the chunk (the orbital of its spin component)
     const int srow = a.spindep ? (col & 1) * a.site_L[site] + local : local;
-    const double* __restrict__ base = a.part + ((static_cast<int64_t>(q) * a.prows + srow) * a.ncol +
-                                                (active ? col : 0)) * NC;
+    const int sh = a.split_log2, sm = (1 << sh) - 1;               // rows per chunk row
+    const double* __restrict__ base = a.part + ((static_cast<int64_t>(q) * a.prows + (static_cast<int64_t>(srow) << sh)) *
+                                                    a.ncol + (active ? col : 0)) * NC;
     const int t0 = a.site_chunk_ptr[site], t1 = a.site_chunk_ptr[site + 1];
     const int32_t* __restrict__ ids = a.site_chunk_ids + t0;
     const HubChunk* __restrict__ chunks = a.chunks;
     double r0, r1;
     reduce_rows<RW, NC>(
-        t1 - t0, a.phase + static_cast<int64_t>(k) * a.nimg * 2,
-        [&](int t) { return base + static_cast<int64_t>(chunks[ids[t]].part0) * a.pmult * a.ncol * NC; },
-        [&](int t) { return chunks[ids[t]].img; }, r0, r1);
+        (t1 - t0) << sh, a.phase + static_cast<int64_t>(k) * a.nimg * 2,
+        [&](int t) {
+            return base + ((static_cast<int64_t>(chunks[ids[t >> sh]].part0) * a.pmult << sh) + (t & sm)) * a.ncol * NC;
+        },
+        [&](int t) { return chunks[ids[t >> sh]].img; }, r0, r1);
     if (threadIdx.x >= 64 || !active) return;
     double* o = a.out + ((static_cast<int64_t>(q) * a.nrows + r) * a.ncol + col) * NC;
     o[0] = a.dV * r0;
@@ -128,17 +131,18 @@ __global__ void __launch_bounds__(RW * 64) k_reduce_grouped(const ReduceGroupedA
     // spin-dependent orbitals: spinor column 2s + sigma reads the rows of the
     // orbital of its spin component
     const int64_t shift = (a.spin_shift && (col & 1)) ? a.spin_shift[j] : 0;
+    const int sh = a.split_log2, sm = (1 << sh) - 1;               // rows per chunk row
     const double* __restrict__ base = a.part + comp * a.pplane +
-                                      (static_cast<int64_t>(q) * a.prows + shift) * a.ncol * NC +
+                                      (static_cast<int64_t>(q) * a.prows + (shift << sh)) * a.ncol * NC +
                                       static_cast<int64_t>(active ? col : 0) * NC;
     const int t0 = a.red_ptr[j], t1 = a.red_ptr[j + 1];
     const int32_t* __restrict__ rows = a.red_row + t0;
     const int32_t* __restrict__ imgs = a.red_img + t0;
     double r0, r1;
     reduce_rows<RW, NC>(
-        t1 - t0, a.phase + static_cast<int64_t>(k) * a.nimg * 2,
-        [&](int t) { return base + static_cast<int64_t>(rows[t]) * a.ncol * NC; }, [&](int t) { return imgs[t]; },
-        r0, r1);
+        (t1 - t0) << sh, a.phase + static_cast<int64_t>(k) * a.nimg * 2,
+        [&](int t) { return base + ((static_cast<int64_t>(rows[t >> sh]) << sh) + (t & sm)) * a.ncol * NC; },
+        [&](int t) { return imgs[t >> sh]; }, r0, r1);
     if (threadIdx.x >= 64 || !active) return;
     double* o = comp == 0 ? a.out + ((static_cast<int64_t>(q) * a.J + j) * a.ncol + col) * NC
                           : a.mout + ((static_cast<int64_t>(q) * a.J * 3 + 3 * j + comp - 1) * a.ncol + col) * NC;
@@ -949,7 +953,7 @@ hipError_t launch_gauge_tables(const GaugeArgs& a, hipStream_t st) {
 hipError_t launch_reduce(const ReduceArgs& a, int nq, hipStream_t st) {
     if (a.nrows <= 0 || nq <= 0 || a.ncol <= 0) return hipSuccess;
     dim3 grid((a.ncol + 63) / 64, a.nrows, nq);
-    const bool wide = a.chunks_per_site >= 64;
+    const bool wide = a.chunks_per_site << a.split_log2 >= 64;
     if (a.ncplx == 2) {
         if (wide) hipLaunchKernelGGL((k_reduce<16, 2>), grid, dim3(16 * 64), 0, st, a);
         else hipLaunchKernelGGL((k_reduce<4, 2>), grid, dim3(4 * 64), 0, st, a);
@@ -965,7 +969,7 @@ hipError_t launch_reduce_grouped(const ReduceGroupedArgs& a, int nq, hipStream_t
     if (a.ncomp > 1 && !a.mout) return hipErrorInvalidValue;
     dim3 grid((a.ncol + 63) / 64, a.J, nq * (a.ncomp > 1 ? a.ncomp : 1));
     // many rows per orbital (overlapping spheres, small chunks): 16 waves
-    const bool wide = a.rows_per_orbital >= 64;
+    const bool wide = a.rows_per_orbital << a.split_log2 >= 64;
     if (a.ncplx == 2) {
         if (wide) hipLaunchKernelGGL((k_reduce_grouped<16, 2>), grid, dim3(16 * 64), 0, st, a);
         else hipLaunchKernelGGL((k_reduce_grouped<4, 2>), grid, dim3(4 * 64), 0, st, a);

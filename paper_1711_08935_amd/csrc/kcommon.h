@@ -24,10 +24,11 @@ struct ProjArgs {
     int tabmult;              // 1: phi, 3: grad phi or position moments
     int wide;                 // 1: one state set per wave; 0: sets packed across lanes
     int nchunks;              // chunks in chunk_list (set by the launcher)
-    int tiles;                // column tiles per chunk (set by the launcher)
+    int tiles;                // column tiles per chunk times split (set by the launcher)
+    int split;                // work-groups that share a chunk's entries in one tile
     const double* pg;         // velocity gauge: [G] exp(i A.r_g) (re, im), or null
-    double* part;             // [nq][prows][ncol] (x2 complex)
-    int64_t prows;            // rows per state set = part_rows * tabmult
+    double* part;             // [nq][prows][ncol] (x2 complex): chunk row r, split s in row r split + s
+    int64_t prows;            // rows per state set = part_rows * tabmult * split
     // position-moment launch (k_project_mom) only: per grouped point the
     // displacement d0[3] from its chunk's first cover, per chunk and function
     // the offset fdel[HUB_GF_MAX][3] to its own cover; component i (0: the
@@ -65,14 +66,12 @@ struct ApplyArgs {
     double alpha;
     int wide;                 // 1: one state set per wave; 0: sets packed across lanes
     int nchunks;              // chunks in chunk_list (set by the launcher)
-    int tiles;                // column tiles per chunk (set by the launcher)
+    int tiles;                // column tiles per chunk times split (set by the launcher)
+    int split;                // work-groups that share a chunk's entries in one tile
     const double* pg;         // velocity gauge: [G] exp(i A.r_g) (re, im), or null
     int spindep;              // per-site chunks with 2L functions [sigma][m] (spinor orbitals)
     int q0;                   // context index of the first state set of the launch (k-point, spin)
-    // grouped chunks: per chunk HUB_GF_MAX (orbital j, image) pairs
-    const int32_t* f_orb;
-    const int32_t* f_img;
-    const int32_t* orb_site;
+    const HubFun* fun;        // grouped chunks: [chunk][HUB_GF_MAX] functions
     const int32_t* site_orb0;
     const int32_t* site_L;
     // one row (ld x ncplx values) of scratch that the padding entries of a
@@ -252,6 +251,16 @@ __device__ __forceinline__ void hub_wave_range(int n, int nw, int w, int& lo, in
     lo = w * per;
     const int hi = lo + per < n ? lo + per : n;
     len = hi > lo ? hi - lo : 0;
+}
+
+// Entries [lo, lo + len) of part idx of the parts that share a chunk's n
+// entries (n a multiple of HUB_ENTRY_ALIGN): whole batches of the entry loops
+// (at most 8 entries).
+__device__ __forceinline__ void hub_entry_range(int n, int parts, int idx, int& lo, int& len) {
+    const int per = ((n + parts - 1) / parts + 7) & ~7;
+    lo = idx * per;
+    len = n - lo < per ? n - lo : per;
+    if (len < 0) lo = len = 0;
 }
 
 // Launchers, one translation unit per storage precision (and work list).

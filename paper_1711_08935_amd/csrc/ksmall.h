@@ -19,6 +19,7 @@ struct ReduceArgs {
     int q0;                               // context index of the first state set of the launch
     double dV;
     int chunks_per_site;                  // average (host)
+    int split_log2;                       // workspace rows per chunk row (the projection's split)
 };
 
 struct ReduceGroupedArgs {
@@ -28,7 +29,8 @@ struct ReduceGroupedArgs {
     const double* phase; int nimg; int nspin; int spinor;
     int q0;                   // context index of the first state set of the launch
     double dV;
-    int rows_per_orbital;     // average workspace rows per orbital (host)
+    int rows_per_orbital;     // average chunk rows per orbital (host)
+    int split_log2;           // workspace rows per chunk row (the projection's split)
     const int32_t* spin_shift;  // spin-dependent orbitals: per orbital, the rows from a
                                 // spin-up function to its spin-down one (L); else null
     // ncomp = 4: the workspace also holds the position-moment projections
