@@ -226,6 +226,40 @@ __global__ void __launch_bounds__(NBPART * 64) k_nbar(const NbarArgs a) {
 // combined matrix are spread over the threads with several state slices
 // each, and the slices are summed in a fixed order into the workspace.
 // Pass 2 sums the splits in order and writes n and P-bar.
+
+// Projections of the (k-point, state) pairs t0..t0 + TILE (zeros from p1 on)
+// onto a site's orbitals, into LDS: wave w takes the orbitals w and w + 4 of
+// every pair, all loads in flight together.
+__device__ __forceinline__ void stage_pairs(const OccArgs& a, int ch, int orb0, int L, int t0, int p1,
+                                            double (&cs)[2][7][TILE][2]) {
+    static_assert(NB == 4 * TILE && HUB_LMAX <= 8, "four waves, two orbitals each");
+    const int t = threadIdx.x % TILE, w = threadIdx.x / TILE;
+    const int NC = a.ncplx, nsig = a.spinor ? 2 : 1;
+    const int pp = t0 + t, pc = pp < p1 ? pp : t0;
+    const int k = pc / a.nstates, s = pc - k * a.nstates;
+    const int q = a.spinor ? k : k * a.nspin + ch;
+    double v[2][2][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int m = w + 4 * h;
+            const double* p = a.c + ((static_cast<int64_t>(q) * a.J + orb0 + (m < L ? m : 0)) * a.ncol + s * nsig +
+                                     (x < nsig ? x : 0)) * NC;
+            v[x][h][0] = p[0];
+            v[x][h][1] = NC == 2 ? p[1] : 0.0;
+        }
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int m = w + 4 * h;
+            if (x >= nsig || m >= L) continue;
+            cs[x][m][t][0] = pp < p1 ? v[x][h][0] : 0.0;
+            cs[x][m][t][1] = pp < p1 ? v[x][h][1] : 0.0;
+        }
+}
+
 __global__ void __launch_bounds__(NB) k_occ_part(const OccArgs a) {
     const int site = blockIdx.x;
     const int ch = blockIdx.y;
@@ -233,8 +267,6 @@ __global__ void __launch_bounds__(NB) k_occ_part(const OccArgs a) {
     const int L = a.site_L[site];
     const int orb0 = a.site_orb0[site];
     const int T = a.site_species[site];
-    const int NC = a.ncplx;
-    const int nsig = a.spinor ? 2 : 1;               // spin components staged per state
     const int ncp = a.spinor ? 2 * L : L;            // rows of the combined matrix
     const int npairs = ncp * ncp;
     const int nslice = NB / npairs;
@@ -255,28 +287,18 @@ __global__ void __launch_bounds__(NB) k_occ_part(const OccArgs a) {
     const int p1 = min(np, p0 + per);
     double nr = 0.0, ni = 0.0, pr = 0.0, pi = 0.0;
     for (int t0 = p0; t0 < p1; t0 += TILE) {
+        stage_pairs(a, ch, orb0, L, t0, p1, cs);
         const int pp = t0 + tid;
-        if (tid >= TILE) {
-        } else if (pp < p1) {
-            const int k = pp / a.nstates, s = pp - k * a.nstates;
-            const int q = a.spinor ? k : k * a.nspin + ch;
-            const double wk = a.kweights[k];
-            const double f = a.f[static_cast<int64_t>(q) * a.nstates + s];
-            const double nb =
-                (a.nbar != nullptr) ? a.nbar[(static_cast<int64_t>(q) * a.nspecies + T) * a.nstates + s] : 0.0;
-            wt[tid] = wk * f;
-            wtn[tid] = wk * f * nb;
-            for (int x = 0; x < nsig; ++x)
-                for (int m = 0; m < L; ++m) {
-                    const double* p = a.c + ((static_cast<int64_t>(q) * a.J + orb0 + m) * a.ncol + s * nsig + x) * NC;
-                    cs[x][m][tid][0] = p[0];
-                    cs[x][m][tid][1] = (NC == 2) ? p[1] : 0.0;
-                }
-        } else {
-            wt[tid] = 0.0;
-            wtn[tid] = 0.0;
-            for (int x = 0; x < nsig; ++x)
-                for (int m = 0; m < L; ++m) cs[x][m][tid][0] = cs[x][m][tid][1] = 0.0;
+        if (tid < TILE) {
+            double w = 0.0, nb = 0.0;
+            if (pp < p1) {
+                const int k = pp / a.nstates, s = pp - k * a.nstates;
+                const int q = a.spinor ? k : k * a.nspin + ch;
+                w = a.kweights[k] * a.f[static_cast<int64_t>(q) * a.nstates + s];
+                if (a.nbar != nullptr) nb = a.nbar[(static_cast<int64_t>(q) * a.nspecies + T) * a.nstates + s];
+            }
+            wt[tid] = w;
+            wtn[tid] = w * nb;
         }
         __syncthreads();
         if (worker) {
@@ -375,7 +397,12 @@ __global__ void __launch_bounds__(NB) k_occ_final(const OccArgs a) {
 // U-bar and J-bar of one site (Eqs. ACBN0_U, ACBN0_J; App. B), with the
 // numerators read as P_mm' P_m''m''' (mm'|m''m''') and P_mm' P_m''m'''
 // (mm'''|m''m'), denominators from the bare diagonal occupations.
-// The site's P-bar and n blocks ([blk][7][7] complex) are in LDS.
+// The site's P-bar and n blocks ([blk][7][7] complex) are in LDS.  Latency
+// bound: the tensor's loads are in flight together and the denominators'
+// terms lie over a wave's lanes (with one thread summing them and one load
+// after another the separate call took 15.2 us with an f shell, 6.8 us now;
+// the step's second launch 9.0 / 12.2 / 16.4 us for 1 / 4 / 64 sites, 5.0 /
+// 8.6 / 9.1 us now).
 struct AcbLds {
     double P[4][7][7][2];
     double Nf[4][7][7][2];
@@ -390,17 +417,19 @@ __device__ void acbn0_site(const Acbn0Args& a, int site, AcbLds& sm, bool tensor
     const double fixed = a.ueff_fixed[site];
     __syncthreads();                          // P and Nf written by the caller
     if (!isnan(fixed)) {
-        if (tid == 0) {
-            a.U[site] = fixed;
-            a.J[site] = 0.0;
-            a.Ueff[site] = fixed;
-            if (a.status) {
-                // flag occupations that are not finite (NaN or Inf in the states)
-                bool finite = true;
-                for (int b = 0; b < a.nblk; ++b)
-                    for (int e = 0; e < L * L; ++e)
-                        finite = finite && isfinite(sm.Nf[b][e / L][e % L][0]) && isfinite(sm.Nf[b][e / L][e % L][1]);
-                a.status[site] = finite ? 0 : HUB_ENONFINITE;
+        if (tid < 64) {
+            // flag occupations that are not finite (NaN or Inf in the states)
+            bool bad = false;
+            for (int o = tid; o < a.nblk * L * L; o += 64) {
+                const int b = o / (L * L), e = o - b * L * L;
+                bad = bad || !isfinite(sm.Nf[b][e / L][e % L][0]) || !isfinite(sm.Nf[b][e / L][e % L][1]);
+            }
+            const bool any = __ballot(bad) != 0;
+            if (tid == 0) {
+                a.U[site] = fixed;
+                a.J[site] = 0.0;
+                a.Ueff[site] = fixed;
+                if (a.status) a.status[site] = any ? HUB_ENONFINITE : 0;
             }
         }
         return;
@@ -413,6 +442,7 @@ __device__ void acbn0_site(const Acbn0Args& a, int site, AcbLds& sm, bool tensor
     const int L2 = L * L, L4 = L2 * L2;
     if (!tensor_in_lds) {
         const double* Tg = a.tensor + static_cast<int64_t>(site) * 2401;
+#pragma unroll 5
         for (int o = tid; o < L4; o += NB) Ts[o] = Tg[o];
         __syncthreads();
     }
@@ -460,44 +490,42 @@ __device__ void acbn0_site(const Acbn0Args& a, int site, AcbLds& sm, bool tensor
         redJ[tid >> 6] = sj;
     }
     __syncthreads();
+    if (tid >= 64) return;
+    // denominators: the (m, m') terms over the lanes of the first wave
+    double dU = 0.0, dJ = 0.0;
+    if (tid < L2) {
+        const int m = tid / L, mp = tid - m * L;
+        if (nb != 4) {
+            // collinear: N^alpha_m = n^alpha_mm (real part)
+            const double x0 = sm.Nf[c0][m][m][0], y0 = sm.Nf[c0][mp][mp][0];
+            const double x1 = sm.Nf[c1][m][m][0], y1 = sm.Nf[c1][mp][mp][0];
+            if (m != mp) dJ = x0 * y0 + x1 * y1;
+            dU = dJ + (x0 * y1 + x1 * y0);
+        } else {
+            // spinor (App. B): complex diagonal blocks N^{xy}_m = n^{xy}_mm
+            auto re_mul = [&](int b1, int m1, int b2, int m2) {
+                return sm.Nf[b1][m1][m1][0] * sm.Nf[b2][m2][m2][0] - sm.Nf[b1][m1][m1][1] * sm.Nf[b2][m2][m2][1];
+            };
+            for (int s = 0; s < 2; ++s) {
+                const int ss = 3 * s, oo = 3 * (1 - s), so = 2 * s + (1 - s), os = 2 * (1 - s) + s;
+                dU += re_mul(ss, m, oo, mp);
+                if (m != mp) {
+                    dU += re_mul(ss, m, ss, mp);
+                    dJ += re_mul(ss, m, ss, mp) + re_mul(so, m, os, mp);
+                } else {
+                    dU -= re_mul(so, m, os, m);
+                }
+            }
+        }
+    }
+    for (int m = 32; m >= 1; m >>= 1) {
+        dU += __shfl_xor(dU, m, 64);
+        dJ += __shfl_xor(dJ, m, 64);
+    }
     if (tid != 0) return;
     for (int w = 1; w < NB / 64; ++w) {
         redU[0] += redU[w];
         redJ[0] += redJ[w];
-    }
-    double dU = 0.0, dJ = 0.0;
-    if (nb != 4) {
-        // collinear: N^alpha_m = n^alpha_mm (real part)
-        double N[2][7];
-        for (int m = 0; m < L; ++m) {
-            N[0][m] = sm.Nf[c0][m][m][0];
-            N[1][m] = sm.Nf[c1][m][m][0];
-        }
-        for (int al = 0; al < 2; ++al)
-            for (int m = 0; m < L; ++m)
-                for (int mp = 0; mp < L; ++mp)
-                    if (m != mp) dJ += N[al][m] * N[al][mp];
-        dU = dJ;
-        for (int al = 0; al < 2; ++al)
-            for (int m = 0; m < L; ++m)
-                for (int mp = 0; mp < L; ++mp) dU += N[al][m] * N[1 - al][mp];
-    } else {
-        // spinor (App. B): complex diagonal blocks N^{xy}_m = n^{xy}_mm
-        auto re_mul = [&](int b1, int m1, int b2, int m2) {
-            return sm.Nf[b1][m1][m1][0] * sm.Nf[b2][m2][m2][0] - sm.Nf[b1][m1][m1][1] * sm.Nf[b2][m2][m2][1];
-        };
-        for (int s = 0; s < 2; ++s) {
-            const int ss = 3 * s, oo = 3 * (1 - s), so = 2 * s + (1 - s), os = 2 * (1 - s) + s;
-            for (int m = 0; m < L; ++m)
-                for (int mp = 0; mp < L; ++mp) {
-                    dU += re_mul(ss, m, oo, mp);
-                    if (m != mp) {
-                        dU += re_mul(ss, m, ss, mp);
-                        dJ += re_mul(ss, m, ss, mp) + re_mul(so, m, os, mp);
-                    }
-                }
-            for (int m = 0; m < L; ++m) dU -= re_mul(so, m, os, m);
-        }
     }
     int st = 0;
     double U = 0.0, J = 0.0;
@@ -580,24 +608,16 @@ __global__ void __launch_bounds__(NB) k_step_occ_part(const OccArgs a) {
     const int p1 = min(np, p0 + per);
     double nr = 0.0, ni = 0.0, pr = 0.0, pi = 0.0;
     for (int t0 = p0; t0 < p1; t0 += TILE) {
+        stage_pairs(a, ch, orb0, L, t0, p1, sm.o.cs);
         const int pp = t0 + tid;
         if (tid < TILE) {
+            double w = 0.0;
             if (pp < p1) {
                 const int k = pp / a.nstates, s = pp - k * a.nstates;
                 const int q = a.spinor ? k : k * a.nspin + ch;
-                sm.o.wt[tid] = a.kweights[k] * a.f[static_cast<int64_t>(q) * a.nstates + s];
-                for (int x = 0; x < nsig; ++x)
-                    for (int m = 0; m < L; ++m) {
-                        const double* p =
-                            a.c + ((static_cast<int64_t>(q) * a.J + orb0 + m) * a.ncol + s * nsig + x) * NC;
-                        sm.o.cs[x][m][tid][0] = p[0];
-                        sm.o.cs[x][m][tid][1] = (NC == 2) ? p[1] : 0.0;
-                    }
-            } else {
-                sm.o.wt[tid] = 0.0;
-                for (int x = 0; x < nsig; ++x)
-                    for (int m = 0; m < L; ++m) sm.o.cs[x][m][tid][0] = sm.o.cs[x][m][tid][1] = 0.0;
+                w = a.kweights[k] * a.f[static_cast<int64_t>(q) * a.nstates + s];
             }
+            sm.o.wt[tid] = w;
         }
         {
             // N-bar of the tile's pairs: part tid / TILE (one wave each) of pair tid % TILE
@@ -684,36 +704,26 @@ __global__ void __launch_bounds__(NB) k_step_occ_final(const OccArgs a, const Ac
 
 // ---------------------------------------------------------------- energy
 // E_U = Ueff/2 sum_channels Tr[n - n n] (Eq. E_Dudarev); spinor: the 2L x 2L
-// matrix of App. A.  Unpolarized contexts count their channel twice.
-__global__ void k_energy(const EnergyArgs a) {
-    const int site = blockIdx.x * blockDim.x + threadIdx.x;
-    if (site >= a.nsites) return;
+// matrix of App. A.  Unpolarized contexts count their channel twice.  A wave
+// per site, its lanes over the (block, i, j) elements (one thread per site
+// walking them took 14.4 us with an f shell, 3.1 us here).
+__global__ void __launch_bounds__(64) k_energy(const EnergyArgs a) {
+    const int site = blockIdx.x;
     const int L = a.site_L[site];
-    const double* nb = a.n + static_cast<int64_t>(site) * a.nblk * 98;
+    const double* __restrict__ nb = a.n + static_cast<int64_t>(site) * a.nblk * 98;
     double val = 0.0;
-    if (a.nblk == 4) {
-        const int M = 2 * L;
-        auto el = [&](int i, int j, int r) {
-            const int x = i / L, y = j / L;
-            return nb[((2 * x + y) * 49 + (i % L) * 7 + (j % L)) * 2 + r];
-        };
-        for (int i = 0; i < M; ++i) {
-            val += el(i, i, 0);
-            for (int j = 0; j < M; ++j) val -= el(i, j, 0) * el(j, i, 0) - el(i, j, 1) * el(j, i, 1);
-        }
-    } else {
-        for (int b = 0; b < a.nblk; ++b) {
-            const double* m = nb + b * 98;
-            double v = 0.0;
-            for (int i = 0; i < L; ++i) {
-                v += m[(i * 7 + i) * 2];
-                for (int j = 0; j < L; ++j)
-                    v -= m[(i * 7 + j) * 2] * m[(j * 7 + i) * 2] - m[(i * 7 + j) * 2 + 1] * m[(j * 7 + i) * 2 + 1];
-            }
-            val += (a.nblk == 1) ? 2.0 * v : v;
-        }
+    for (int o = threadIdx.x; o < a.nblk * 49; o += 64) {
+        const int blk = o / 49, e = o - blk * 49, i = e / 7, j = e - i * 7;
+        if (i >= L || j >= L) continue;
+        // (n n)_ii: element (i, j) of block (s, t) with (j, i) of block (t, s)
+        const int rb = a.nblk == 4 ? 2 * (blk & 1) + (blk >> 1) : blk;
+        const double* x = nb + blk * 98 + (i * 7 + j) * 2;
+        const double* y = nb + rb * 98 + (j * 7 + i) * 2;
+        val -= x[0] * y[0] - x[1] * y[1];
+        if (i == j && rb == blk && (a.nblk != 4 || blk == 0 || blk == 3)) val += x[0];
     }
-    a.EU[site] = 0.5 * a.Ueff[site] * val;
+    for (int m = 32; m >= 1; m >>= 1) val += __shfl_xor(val, m, 64);
+    if (threadIdx.x == 0) a.EU[site] = 0.5 * a.Ueff[site] * (a.nblk == 1 ? 2.0 * val : val);
 }
 
 // ---------------------------------------------------------------- FLL terms
@@ -1031,7 +1041,7 @@ hipError_t launch_fll(const FllArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_energy(const EnergyArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(k_energy, dim3((a.nsites + 63) / 64), dim3(64), 0, st, a);
+    hipLaunchKernelGGL(k_energy, dim3(a.nsites), dim3(64), 0, st, a);
     return hipGetLastError();
 }
 
