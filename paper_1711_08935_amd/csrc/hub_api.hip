@@ -145,8 +145,6 @@ struct hub_ctx {
     double* d_nbar_ws = nullptr;
     size_t nbar_cap = 0;
     unsigned char* d_cover = nullptr;        // [G] 1: in the grouped list (covered by a sphere)
-    double* d_coul = nullptr;                // scratch of the Coulomb tensors (kept while small)
-    size_t coul_cap = 0;
     // Workspaces of the call in flight come from the buffers above (grown
     // with hipMalloc on demand) unless ws_fixed points at slices of the
     // static scratch array (hub_step_noalloc), which are used as they are.
@@ -239,9 +237,9 @@ void release(hub_ctx* c) {
     f(c->d_chunks); f(c->d_all); f(c->d_gidx); f(c->d_img); f(c->d_phi); f(c->d_gphi); f(c->d_phase);
     f(c->d_site_chunk_ptr); f(c->d_site_chunk_ids); f(c->d_orb_site); f(c->d_site_L); f(c->d_site_orb0);
     f(c->d_site_species); f(c->d_species_orb_ptr); f(c->d_species_orb_ids); f(c->d_kw); f(c->d_ueff_fixed);
-    f(c->d_tensor); f(c->d_cover); f(c->d_coul); f(c->d_part); f(c->d_grad); f(c->d_nbar_ws); f(c->d_sink); f(c->d_occ_ws);
+    f(c->d_tensor); f(c->d_cover); f(c->d_part); f(c->d_grad); f(c->d_nbar_ws); f(c->d_sink); f(c->d_occ_ws);
     f(c->d_pg); f(c->d_mphi); f(c->d_images); f(c->d_kred);
-    c->part_cap = c->coul_cap = c->grad_cap = c->nbar_cap = c->sink_cap = c->occ_cap = 0;
+    c->part_cap = c->grad_cap = c->nbar_cap = c->sink_cap = c->occ_cap = 0;
     f(c->d_phi2); f(c->d_gphi_dn); f(c->d_mphi_dn);
     f(c->d_st_chunks); f(c->d_st_all); f(c->d_st_gidx); f(c->d_st_site_ptr); f(c->d_st_site_ids); f(c->d_st_tab); f(c->d_st_tab_dn);
     f(c->d_gchunks); f(c->d_gall); f(c->d_gall_m); f(c->d_gmom); f(c->d_ggidx); f(c->d_gfun); f(c->d_gred_ptr);
@@ -1096,7 +1094,9 @@ int step_impl(hub_ctx* c, const hub_step_io* io, int mode, double* jcur) {
 // Coulomb tensors of some sites: the plan's tables go up in one copy beside
 // the scratch, whose slices start on 256-byte boundaries.
 constexpr size_t kCoulombBatch = size_t(512) << 20;    // bytes of densities and offsets per batch
-constexpr size_t kCoulombKeep = size_t(32) << 20;      // scratch kept for the next call
+// Scratch up to this size is the projection's workspace, which the next step
+// finds allocated; more is given back at once.
+constexpr size_t kCoulombKeep = size_t(64) << 20;
 
 int coulomb_batch(hub_ctx* c, const std::vector<int>& sites) {
     CoulombPlan P;
@@ -1150,14 +1150,16 @@ int coulomb_batch(hub_ctx* c, const std::vector<int>& sites) {
     const size_t o_sites = add(P.sites), o_items = add(items), o_lines = add(P.lines), o_planes = add(P.planes);
     const size_t n_rho = slice256(P.rho), n_part = slice256(P.part), n_yz = slice256(P.slots), n_tab = slice256(table);
     const size_t need = n_rho + n_part + n_yz + n_tab + host.size() / sizeof(double);
-    if (c->coul_cap < need) {
-        if (c->d_coul) (void)hipFree(c->d_coul);
-        c->d_coul = nullptr;
-        c->coul_cap = 0;
-        HUB_TRY(dev_malloc(c, &c->d_coul, need * sizeof(double)));
-        c->coul_cap = need;
+    double* own = nullptr;
+    if (need * sizeof(double) <= kCoulombKeep) {
+        // a projection on another stream may still read it
+        if (c->d_part) HUB_TRY(hipDeviceSynchronize());
+        const int st = ensure(&c->d_part, &c->part_cap, need, c);
+        if (st) return st;
+    } else {
+        HUB_TRY(dev_malloc(c, &own, need * sizeof(double)));
     }
-    double* w = c->d_coul;
+    double* w = own ? own : c->d_part;
     char* tabs = reinterpret_cast<char*>(w + n_rho + n_part + n_yz + n_tab);
     CoulombArgs a{};
     a.sites = reinterpret_cast<CoulombSite*>(tabs + o_sites);
@@ -1194,11 +1196,7 @@ int coulomb_batch(hub_ctx* c, const std::vector<int>& sites) {
     // the next one on any stream
     const hipError_t es = hipStreamSynchronize(c->stream);
     if (e == hipSuccess) e = es;
-    if (c->coul_cap * sizeof(double) > kCoulombKeep) {
-        (void)hipFree(c->d_coul);
-        c->d_coul = nullptr;
-        c->coul_cap = 0;
-    }
+    if (own) (void)hipFree(own);
     if (e != hipSuccess) return map_err(e);
     for (int s : sites) c->have_tensor[s] = 1;
     return HUB_OK;
