@@ -14,6 +14,7 @@
 #include <numeric>
 #include <vector>
 
+#include "kbloch.h"
 #include "ksmall.h"
 
 namespace {
@@ -114,6 +115,18 @@ struct hub_ctx {
     double* d_gtab = nullptr;
     double *d_gd0 = nullptr, *d_gfdel = nullptr;   // moment tables of the grouped list, uploaded
                                                    // at the first hub_step_current
+    // Bloch-summed work list (k_bloch.hip), where the grouped list needs passes
+    bool bloch = false;
+    bool no_bloch = false;                   // the call in flight does without (scratch limit)
+    std::vector<int32_t> bl_pass_ptr;
+    int64_t bl_part_rows = 0, bl_wlen = 0;
+    int bl_rows_per_orbital = 0;
+    HubChunk* d_bl_chunks = nullptr;
+    int32_t *d_bl_gidx = nullptr, *d_bl_orb = nullptr, *d_bl_red_ptr = nullptr, *d_bl_red_row = nullptr;
+    int32_t* d_bl_img0 = nullptr;            // zeros: every row of the reduction has the phase 1
+    double *d_bl_W = nullptr, *d_bl_one = nullptr;
+    double* d_bcoef = nullptr;               // coefficients B[q][j][col]
+    size_t bcoef_cap = 0;
     std::vector<char> have_tensor;
     size_t table_bytes = 0;
 
@@ -153,6 +166,7 @@ struct hub_ctx {
         double* occ;
         double* nbar;
         double* sink;
+        double* bcoef;
     };
     const FixedWs* ws_fixed = nullptr;
     int64_t nalloc = 0;                      // device allocations made so far (hub_query 15)
@@ -244,6 +258,10 @@ void release(hub_ctx* c) {
     f(c->d_st_chunks); f(c->d_st_all); f(c->d_st_gidx); f(c->d_st_site_ptr); f(c->d_st_site_ids); f(c->d_st_tab); f(c->d_st_tab_dn);
     f(c->d_gchunks); f(c->d_gall); f(c->d_gall_m); f(c->d_gmom); f(c->d_ggidx); f(c->d_gfun); f(c->d_gred_ptr);
     f(c->d_gred_row); f(c->d_gred_img); f(c->d_gtab); f(c->d_gspin_shift); f(c->d_gd0); f(c->d_gfdel);
+    f(c->d_bl_chunks); f(c->d_bl_gidx); f(c->d_bl_orb); f(c->d_bl_red_ptr); f(c->d_bl_red_row); f(c->d_bl_img0);
+    f(c->d_bl_W); f(c->d_bl_one); f(c->d_bcoef);
+    c->bcoef_cap = 0;
+    c->bloch = false;
     drop_graph(c);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     for (int k = 0; k < HUB_NCLASS; ++k) {
@@ -384,6 +402,19 @@ int proj_split(const hub_ctx* c, int nchunks, int64_t rows, int ncol, int cpl, i
     return split_of(c, proj_groups(c, nchunks, ncol, cpl, wide),
                     8.0 * c->nsets() * rows * ncol * c->ncplx());
 }
+// The same for the Bloch-summed list, whose work-groups are single waves, by
+// the whole list and every state set: two in the projection, whose partial
+// rows a reduction of few work-groups reads (two sets of 20 columns: 31 us of
+// projection and 9 of reduction unsplit, 20 and 14 with two, 25 and 34 with
+// eight), up to four in the apply (44, 32 and 28 us with one, two and four).
+constexpr int64_t kBlochGroups = 4096;
+int bloch_split(const hub_ctx* c, int ncol, int most) {
+    const int w = 16 * bloch_nj(ncol);
+    const int64_t groups = static_cast<int64_t>(c->bl_pass_ptr.back()) * c->nsets() * ((ncol + w - 1) / w);
+    int s = 1;
+    while (s < most && groups * s * 2 <= kBlochGroups) s *= 2;
+    return s;
+}
 int ilog2(int v) {
     int l = 0;
     while (v > 1) v >>= 1, ++l;
@@ -394,6 +425,13 @@ bool built(const hub_ctx* c) { return c && c->built_dev; }
 
 // Batched launches use the grouped work list when it exists.
 bool grouped(const hub_ctx* c) { return c->use_grouped && c->T.grouped.ok; }
+
+// The Bloch-summed list takes the place of the grouped list's passes (without
+// a field, which changes the phases at every step).
+bool use_bloch(const hub_ctx* c) { return c->bloch && !c->no_bloch && grouped(c) && !c->gauge; }
+size_t bcoef_need(const hub_ctx* c, int ncol) {
+    return use_bloch(c) ? static_cast<size_t>(c->nsets()) * c->T.J * ncol * 2 : 0;
+}
 
 // Columns per lane so that a lane's FP64 accumulators (functions x scalars)
 // stay within 96 values (nf: the largest function count launched).
@@ -536,6 +574,7 @@ size_t part_need(const hub_ctx* c, int ncol, int mult) {
     if (c->T.grouped.ok)
         rows = std::max<int64_t>(rows, rows_of(static_cast<int>(c->T.grouped.chunks.size()), c->T.grouped.part_rows));
     if (mult == 3) rows = std::max<int64_t>(rows, rows_of(c->stencil_nchunks, c->stencil_part_rows) * 3);
+    if (use_bloch(c)) rows = std::max(rows, c->bl_part_rows * bloch_split(c, ncol, 2));
     return static_cast<size_t>(c->nsets()) * rows * ncol * c->ncplx();
 }
 // the grouped projection with the three position-moment components as well
@@ -545,6 +584,24 @@ size_t part_need_moments(const hub_ctx* c, int ncol) {
 }
 // whether hub_step_current takes the moments in the step's own projection
 bool fused_moments(const hub_ctx* c) { return grouped(c) && c->is_complex; }
+
+BlochArgs bloch_args(const hub_ctx* c, int64_t ld, int ncol, int q0, int nq) {
+    BlochArgs b{};
+    b.ld = ld;
+    b.qstride = c->G() * ld * 2;
+    b.ncol = ncol;
+    b.nq = nq;
+    b.q0 = q0;
+    b.nspin = c->nspin();
+    b.spinor = c->spin_mode == HUB_SPINOR;
+    b.J = c->T.J;
+    b.chunks = c->d_bl_chunks;
+    b.gidx = c->d_bl_gidx;
+    b.f_orb = c->d_bl_orb;
+    b.W = c->d_bl_W;
+    b.wlen = c->bl_wlen;
+    return b;
+}
 
 // q0, nq: the state sets projected (psi and out hold those sets only);
 // nq < 0: every set of the context.
@@ -573,6 +630,40 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     ProjArgs a = proj_args(c, psi, ld, ncol, table);
     a.part = part;
     a.nq = nq;
+    if (!per_site && !grad && !mout && use_bloch(c)) {
+        BlochArgs b = bloch_args(c, ld, ncol, q0, nq);
+        b.psi = psi;
+        b.part = part;
+        b.split = bloch_split(c, ncol, 2);
+        b.prows = c->bl_part_rows * b.split;
+        b.chunk0 = 0;
+        b.nchunks = c->bl_pass_ptr.back();
+        {
+            StageTimer tm(c, HUB_STAGE_PROJECT);
+            HUB_TRY(launch_bloch_project(b, c->precision, c->stream));
+        }
+        ReduceGroupedArgs r{};
+        r.part = part;
+        r.prows = b.prows;
+        r.out = out;
+        r.J = c->T.J;
+        r.ncol = ncol;
+        r.ncplx = 2;
+        r.red_ptr = c->d_bl_red_ptr;
+        r.red_row = c->d_bl_red_row;
+        r.red_img = c->d_bl_img0;
+        r.rows_per_orbital = c->bl_rows_per_orbital;
+        r.split_log2 = ilog2(b.split);
+        r.phase = c->d_bl_one;
+        r.nimg = 1;
+        r.nspin = c->nspin();
+        r.spinor = c->spin_mode == HUB_SPINOR;
+        r.q0 = q0;
+        r.dV = (c->cell[0] / c->ngrid[0]) * (c->cell[1] / c->ngrid[1]) * (c->cell[2] / c->ngrid[2]);
+        StageTimer tm(c, HUB_STAGE_REDUCE);
+        HUB_TRY(launch_reduce_grouped(r, nq, c->stream));
+        return HUB_OK;
+    }
     if (!per_site && !grad && grouped(c)) {
         const GroupTables& GT = c->T.grouped;
         a.chunks = c->d_gchunks;
@@ -913,6 +1004,25 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
             b.split = split_of(c, static_cast<int64_t>(nch) * nq * lanes(cpl) / cpl, 0.0);
             return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, apply_waves(c), k, store, s);
         };
+        if (!overwrite && use_bloch(c)) {
+            double* B = c->ws_fixed ? c->ws_fixed->bcoef : nullptr;
+            if (!B) {
+                const int st = ensure(&c->d_bcoef, &c->bcoef_cap, bcoef_need(c, ncol), c);
+                if (st) return st;
+                B = c->d_bcoef;
+            }
+            a.phase = c->d_bl_one;
+            a.nimg = 1;
+            HUB_TRY(launch_bloch_coef(a, nq, c->d_orb_site, B, c->stream));
+            BlochArgs b = bloch_args(c, ld, ncol, q0, nq);
+            b.split = bloch_split(c, ncol, 4);
+            for (size_t p = 0; p + 1 < c->bl_pass_ptr.size(); ++p) {
+                b.chunk0 = c->bl_pass_ptr[p];
+                b.nchunks = c->bl_pass_ptr[p + 1] - b.chunk0;
+                HUB_TRY(launch_bloch_apply(b, c->precision, B, hpsi, c->stream));
+            }
+            return HUB_OK;
+        }
         if (overwrite) {
             const GroupTables& GT = c->T.grouped;
             const int merged = GT.nfmax <= 8 ? HUB_MERGED8 : HUB_MERGED16;
@@ -1037,7 +1147,10 @@ int step_impl(hub_ctx* c, const hub_step_io* io, int mode, double* jcur) {
     }
     st = ensure(&c->d_part, &c->part_cap, part, c);
     if (st) return st;
-
+    if (use_bloch(c)) {
+        st = ensure(&c->d_bcoef, &c->bcoef_cap, bcoef_need(c, ncol), c);
+        if (st) return st;
+    }
     if (!io->nbar) {
         st = ensure(&c->d_nbar_ws, &c->nbar_cap, static_cast<size_t>(c->nsets()) * c->T.nspecies * io->nstates, c);
         if (st) return st;
@@ -1357,6 +1470,67 @@ int hub_finalize_host(hub_ctx* c) {
 
 namespace {
 int gauge_tables(hub_ctx* c);
+
+// Bloch-summed work list and its tables for every k-point, from the plain
+// phases on the device; contexts whose tables would pass kBlochBytes keep the
+// grouped list's passes.
+constexpr size_t kBlochBytes = size_t(4) << 30;
+hipError_t build_bloch(hub_ctx* c, size_t& bytes) {
+    BlochTables B;
+    hub_build_bloch(c->T, c->G(), c->chunk_entries, B);
+    const size_t wbytes = static_cast<size_t>(B.wlen) * c->nk * sizeof(double);
+    if (wbytes > kBlochBytes || B.gidx.size() > INT32_MAX || B.part_rows > INT32_MAX) return hipSuccess;
+    hipError_t e = hipSuccess;
+    auto up = [&](auto** dst, const auto& src, size_t& n) {
+        if (e == hipSuccess) e = upload(c, dst, src, n);
+    };
+    up(&c->d_bl_chunks, B.chunks, bytes);
+    up(&c->d_bl_gidx, B.gidx, bytes);
+    up(&c->d_bl_orb, B.f_orb, bytes);
+    up(&c->d_bl_red_ptr, B.red_ptr, bytes);
+    up(&c->d_bl_red_row, B.red_row, bytes);
+    up(&c->d_bl_img0, std::vector<int32_t>(B.red_row.size(), 0), bytes);
+    std::vector<double> one(2 * c->nk, 0.0);
+    for (int k = 0; k < c->nk; ++k) one[2 * k] = 1.0;
+    up(&c->d_bl_one, one, bytes);
+    if (e == hipSuccess) e = dev_malloc(c, &c->d_bl_W, wbytes);
+    bytes += wbytes;
+    BlochTableArgs a{};
+    int32_t *cptr = nullptr, *cimg = nullptr, *cfun = nullptr;
+    int64_t* coff = nullptr;
+    double* cval = nullptr;
+    size_t tmp = 0;
+    up(&cptr, B.cptr, tmp);
+    up(&cimg, B.cimg, tmp);
+    up(&cfun, B.cfun, tmp);
+    up(&coff, B.coff, tmp);
+    up(&cval, B.cval, tmp);
+    if (e == hipSuccess) {
+        a.chunks = c->d_bl_chunks;
+        a.cptr = cptr;
+        a.cimg = cimg;
+        a.cfun = cfun;
+        a.coff = coff;
+        a.cval = cval;
+        a.phase = c->d_phase;
+        a.nimg = static_cast<int>(c->T.images.size() / 3);
+        a.wlen = B.wlen;
+        a.W = c->d_bl_W;
+        e = launch_bloch_table(a, static_cast<int>(B.chunks.size()), c->nk, c->stream);
+        const hipError_t es = hipStreamSynchronize(c->stream);
+        if (e == hipSuccess) e = es;
+    }
+    for (void* p : {static_cast<void*>(cptr), static_cast<void*>(cimg), static_cast<void*>(cfun),
+                    static_cast<void*>(coff), static_cast<void*>(cval)})
+        if (p) (void)hipFree(p);
+    if (e != hipSuccess) return e;
+    c->bl_pass_ptr = B.pass_ptr;
+    c->bl_part_rows = B.part_rows;
+    c->bl_wlen = B.wlen;
+    c->bl_rows_per_orbital = B.red_ptr.back() / std::max(1, c->T.J);
+    c->bloch = true;
+    return hipSuccess;
+}
 }  // namespace
 
 int hub_finalize(hub_ctx* c, void* stream) {
@@ -1478,6 +1652,14 @@ int hub_finalize(hub_ctx* c, void* stream) {
             for (int s = 0; s < T.nsites; ++s)
                 for (int m = 0; m < T.site_L[s]; ++m) shift[T.site_orb0[s] + m] = T.site_L[s];
             up(&c->d_gspin_shift, shift);
+        }
+    }
+    if (e == hipSuccess && T.grouped.ok && T.grouped.npass > 1 && c->is_complex && !T.spindep) {
+        try {
+            e = build_bloch(c, b);
+        } catch (...) {                              // host tables: out of memory
+            release(c);
+            return HUB_ENOMEM;
         }
     }
     if (e == hipSuccess) {
@@ -1872,15 +2054,27 @@ int hub_step_noalloc(hub_ctx* c, const hub_step_io* io) {
     // slices of the scratch array: projection partial sums, occupation
     // partial sums, N-bar (when the caller passes none), the apply's sink row
     const int ncol = c->ncol(io->nstates);
-    const size_t n_part = slice256(part_need(c, ncol, c->T.spindep ? 2 : 1));
+    size_t n_part = 0, n_b = 0;
     const size_t n_occ = slice256(occ_need(c, io->nstates));
     const size_t n_nbar = io->nbar ? 0 : slice256(static_cast<size_t>(c->nsets()) * c->T.nspecies * io->nstates);
     const size_t n_sink = slice256(static_cast<size_t>(io->ldh) * c->ncplx());
-    if ((n_part + n_occ + n_nbar + n_sink) * sizeof(double) > HUB_SCRATCH_BYTES) return HUB_ESCRATCH;
+    // where only the passes of the grouped list fit, they are taken
+    for (int t = 0; t < 2; ++t) {
+        c->no_bloch = t == 1;
+        n_part = slice256(part_need(c, ncol, c->T.spindep ? 2 : 1));
+        n_b = slice256(bcoef_need(c, ncol));
+        if ((n_part + n_occ + n_nbar + n_sink + n_b) * sizeof(double) <= HUB_SCRATCH_BYTES) break;
+        if (t == 1 || !use_bloch(c)) {
+            c->no_bloch = false;
+            return HUB_ESCRATCH;
+        }
+    }
     double* p = static_cast<double*>(base);
-    const hub_ctx::FixedWs ws{p, p + n_part, p + n_part + n_occ, p + n_part + n_occ + n_nbar};
+    const hub_ctx::FixedWs ws{p, p + n_part, p + n_part + n_occ, p + n_part + n_occ + n_nbar,
+                              p + n_part + n_occ + n_nbar + n_sink};
     c->ws_fixed = &ws;
     st = run_step(c, io, false);
+    c->no_bloch = false;
     c->ws_fixed = nullptr;
     return st;
 }

@@ -186,6 +186,30 @@ struct CoulombPlan {
 // from a table in device memory.
 #define HUB_COUL_LDS 65536
 
+// Work list of Bloch-summed orbitals (complex states whose points carry more
+// than HUB_GF_MAX (orbital, image) functions, where the grouped list needs
+// several passes): for one k-point the images of a site's orbital at a grid
+// point enter only through W_j(g) = sum_T exp(i k.T) phi_j(r_g + T), so a
+// point carries one complex function per orbital of its covering sites.
+// Chunks hold points of one set of covering sites, split over passes of at
+// most HUB_GF_MAX functions as in the grouped list.
+struct BlochTables {
+    std::vector<HubChunk> chunks;            // L functions, layer = pass, phi0: first double of the chunk
+                                             // in one k-point's table (rows of hub_bloch_row(L) doubles)
+    std::vector<int32_t> gidx;               // per entry
+    std::vector<int32_t> f_orb;              // per chunk HUB_GF_MAX: orbital j of function f, or -1
+    std::vector<int32_t> red_ptr, red_row;   // CSR orbital j -> workspace rows
+    std::vector<int32_t> pass_ptr;           // chunks of pass p: [pass_ptr[p], pass_ptr[p + 1])
+    int64_t part_rows = 0, wlen = 0;         // workspace rows; doubles of one k-point's table
+    // covers of each entry (CSR), from which the device builds the tables
+    std::vector<int32_t> cptr, cimg, cfun;   // cfun: first function | L << 8
+    std::vector<int64_t> coff;               // first value in cval
+    std::vector<double> cval;
+};
+// doubles per entry: the real, then the imaginary parts of 8 or 16 functions
+inline int hub_bloch_row(int nf) { return nf > 8 ? 32 : 16; }
+void hub_build_bloch(const HostTables& T, int64_t G, int chunk_entries, BlochTables& out);
+
 // Plan for the sites which[0..] of the context (sphere.cpp).
 void hub_coulomb_plan(const HostTables& T, const std::vector<int>& which, CoulombPlan& out);
 

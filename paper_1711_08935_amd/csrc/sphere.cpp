@@ -612,6 +612,124 @@ int hub_build_host(const double cell[3], const int ngrid[3], const std::vector<S
     return HUB_OK;
 }
 
+void hub_build_bloch(const HostTables& T, int64_t G, int chunk_entries, BlochTables& out) {
+    out = BlochTables();
+    // image id by triple
+    int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
+    const int nimg = static_cast<int>(T.images.size() / 3);
+    for (int i = 0; i < nimg; ++i)
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = std::min(lo[a], T.images[3 * i + a]);
+            hi[a] = std::max(hi[a], T.images[3 * i + a]);
+        }
+    const int n1 = hi[1] - lo[1] + 1, n2 = hi[2] - lo[2] + 1;
+    std::vector<int32_t> id(static_cast<size_t>(hi[0] - lo[0] + 1) * n1 * n2, -1);
+    auto at = [&](const int32_t* t) {
+        return (static_cast<size_t>(t[0] - lo[0]) * n1 + (t[1] - lo[1])) * n2 + (t[2] - lo[2]);
+    };
+    for (int i = 0; i < nimg; ++i) id[at(&T.images[3 * i])] = i;
+    // covers of every grid point, sites in order, a site's images in its order
+    std::vector<int32_t> ptr(static_cast<size_t>(G) + 1, 0);
+    for (const SiteSphere& sp : T.spheres)
+        for (int32_t g : sp.g) ++ptr[g + 1];
+    for (int64_t g = 0; g < G; ++g) ptr[g + 1] += ptr[g];
+    struct Cover {
+        int32_t site, p;
+    };
+    std::vector<Cover> cov(ptr[G]);
+    std::vector<int32_t> fill(ptr.begin(), ptr.end() - 1);
+    for (int s = 0; s < T.nsites; ++s)
+        for (size_t p = 0; p < T.spheres[s].g.size(); ++p)
+            cov[fill[T.spheres[s].g[p]]++] = {s, static_cast<int32_t>(p)};
+    // (pass, sites) -> points as ranges of their covers
+    struct Point {
+        int32_t g, c0, c1;
+    };
+    std::map<std::pair<int, std::vector<int>>, std::vector<Point>> groups;
+    std::vector<int> sites;
+    int npass = 1;
+    for (int64_t g = 0; g < G; ++g) {
+        int pass = 0, nf = 0;
+        int32_t c0 = ptr[g];
+        sites.clear();
+        for (int32_t c = c0; c < ptr[g + 1]; ++c) {
+            if (!sites.empty() && sites.back() == cov[c].site) continue;
+            const int L = T.site_L[cov[c].site];
+            if (nf + L > HUB_GF_MAX) {
+                groups[{pass, sites}].push_back({static_cast<int32_t>(g), c0, c});
+                ++pass;
+                nf = 0;
+                c0 = c;
+                sites.clear();
+            }
+            sites.push_back(cov[c].site);
+            nf += L;
+        }
+        if (!sites.empty()) groups[{pass, sites}].push_back({static_cast<int32_t>(g), c0, ptr[g + 1]});
+        npass = std::max(npass, pass + 1);
+    }
+    out.pass_ptr.assign(npass + 1, 0);
+    out.cptr.push_back(0);
+    std::vector<std::vector<int32_t>> red(T.J);
+    for (const auto& kv : groups) {                                // pass by pass: the map's order
+        const int pass = kv.first.first;
+        const std::vector<int>& sg = kv.first.second;
+        int nf = 0;
+        for (int s : sg) nf += T.site_L[s];
+        const int row = hub_bloch_row(nf);
+        const size_t chunk = static_cast<size_t>(std::max(64, row == 32 ? chunk_entries / 2 : chunk_entries));
+        const std::vector<Point>& pts = kv.second;
+        for (size_t b = 0; b < pts.size(); b += chunk) {
+            const size_t nb = std::min(pts.size() - b, chunk);
+            const size_t np = (nb + HUB_ENTRY_ALIGN - 1) / HUB_ENTRY_ALIGN * HUB_ENTRY_ALIGN;
+            HubChunk C{};
+            C.site = sg[0];
+            C.layer = pass;
+            C.e0 = static_cast<int32_t>(out.gidx.size());
+            C.ne = static_cast<int32_t>(np);
+            C.nreal = static_cast<int32_t>(nb);
+            C.L = nf;
+            C.orb0 = C.species = -1;
+            C.part0 = static_cast<int32_t>(out.part_rows);
+            C.phi0 = out.wlen;
+            for (size_t t = 0; t < np; ++t) {
+                const Point& P = pts[b + std::min(t, nb - 1)];
+                out.gidx.push_back(P.g);
+                int f0 = 0;
+                size_t slot = 0;
+                for (int32_t c = P.c0; t < nb && c < P.c1; ++c) {
+                    while (sg[slot] != cov[c].site) f0 += T.site_L[sg[slot++]];
+                    const SiteSphere& sp = T.spheres[cov[c].site];
+                    const int L = T.site_L[cov[c].site];
+                    out.cimg.push_back(id[at(&sp.img3[3 * static_cast<size_t>(cov[c].p)])]);
+                    out.cfun.push_back(f0 | L << 8);
+                    out.coff.push_back(static_cast<int64_t>(out.cval.size()));
+                    const double* v = &sp.phi[static_cast<size_t>(cov[c].p) * L];
+                    out.cval.insert(out.cval.end(), v, v + L);
+                }
+                out.cptr.push_back(static_cast<int32_t>(out.cimg.size()));
+            }
+            int f = 0;
+            for (int s : sg)
+                for (int m = 0; m < T.site_L[s]; ++m, ++f) {
+                    out.f_orb.push_back(T.site_orb0[s] + m);
+                    red[T.site_orb0[s] + m].push_back(C.part0 + f);
+                }
+            for (; f < HUB_GF_MAX; ++f) out.f_orb.push_back(-1);
+            out.part_rows += nf;
+            out.wlen += static_cast<int64_t>(np) * row;
+            out.chunks.push_back(C);
+            ++out.pass_ptr[pass + 1];
+        }
+    }
+    for (int p = 0; p < npass; ++p) out.pass_ptr[p + 1] += out.pass_ptr[p];
+    out.red_ptr.assign(1, 0);
+    for (const auto& r : red) {
+        out.red_row.insert(out.red_row.end(), r.begin(), r.end());
+        out.red_ptr.push_back(static_cast<int32_t>(out.red_row.size()));
+    }
+}
+
 void hub_coulomb_plan(const HostTables& T, const std::vector<int>& which, CoulombPlan& out) {
     out = CoulombPlan();
     for (int s : which) {
