@@ -105,6 +105,7 @@ struct hub_ctx {
     int32_t* d_gall_m = nullptr;             // chunk list of the merged launch, by pass
     int32_t* d_gmom = nullptr;               // work items of the moment projection (k_project_mom.h)
     int nmom = 0;
+    int32_t* d_gmgidx = nullptr;             // its grid points, runs marked (uploaded with d_gd0)
     std::vector<int> gpass_ptr;              // d_gall_m[gpass_ptr[p], gpass_ptr[p+1]): chunks of pass p
     int gcls_ptr[HUB_NCLASS + 1] = {};       // d_gall[gcls_ptr[k-1], gcls_ptr[k]): chunks of class k
     HubChunk* d_gchunks = nullptr;
@@ -256,8 +257,8 @@ void release(hub_ctx* c) {
     c->part_cap = c->grad_cap = c->nbar_cap = c->sink_cap = c->occ_cap = 0;
     f(c->d_phi2); f(c->d_gphi_dn); f(c->d_mphi_dn);
     f(c->d_st_chunks); f(c->d_st_all); f(c->d_st_gidx); f(c->d_st_site_ptr); f(c->d_st_site_ids); f(c->d_st_tab); f(c->d_st_tab_dn);
-    f(c->d_gchunks); f(c->d_gall); f(c->d_gall_m); f(c->d_gmom); f(c->d_ggidx); f(c->d_gfun); f(c->d_gred_ptr);
-    f(c->d_gred_row); f(c->d_gred_img); f(c->d_gtab); f(c->d_gspin_shift); f(c->d_gd0); f(c->d_gfdel);
+    f(c->d_gchunks); f(c->d_gall); f(c->d_gall_m); f(c->d_gmom); f(c->d_gmgidx); f(c->d_ggidx);
+    f(c->d_gfun); f(c->d_gred_ptr); f(c->d_gred_row); f(c->d_gred_img); f(c->d_gtab); f(c->d_gspin_shift); f(c->d_gd0); f(c->d_gfdel);
     f(c->d_bl_chunks); f(c->d_bl_gidx); f(c->d_bl_orb); f(c->d_bl_red_ptr); f(c->d_bl_red_row); f(c->d_bl_img0);
     f(c->d_bl_W); f(c->d_bl_one); f(c->d_bcoef);
     c->bcoef_cap = 0;
@@ -683,6 +684,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
             a.chunk_list = c->d_gmom;
             a.d0 = c->d_gd0;
             a.fdel = c->d_gfdel;
+            a.mgidx = c->d_gmgidx;
             a.pplane = pplane;
             StageTimer tm(c, HUB_STAGE_PROJECT);
             HUB_TRY(c->precision == HUB_F64 ? launch_project_mom_f64(a, c->nmom, nq, c->stream)
@@ -1141,6 +1143,15 @@ int step_impl(hub_ctx* c, const hub_step_io* io, int mode, double* jcur) {
         if (fused) {
             size_t bytes = 0;
             if (!c->d_gfdel) HUB_TRY(upload(c, &c->d_gfdel, c->T.grouped.fdel, bytes));
+            if (!c->d_gmgidx) {
+                std::vector<int32_t> g(c->T.grouped.gidx);
+                for (const HubChunk& C : c->T.grouped.chunks) {
+                    const double* d = &c->T.grouped.d0[3 * static_cast<size_t>(C.e0)];
+                    for (int e = 1; e < C.nreal; ++e)
+                        if (d[3 * e] != d[3 * e - 3] || d[3 * e + 1] != d[3 * e - 2]) g[C.e0 + e] |= INT32_MIN;
+                }
+                HUB_TRY(upload(c, &c->d_gmgidx, g, bytes));
+            }
             if (!c->d_gd0) HUB_TRY(upload(c, &c->d_gd0, c->T.grouped.d0, bytes));
             c->table_bytes += bytes;
         }
@@ -1611,16 +1622,20 @@ int hub_finalize(hub_ctx* c, void* stream) {
         for (int32_t i : gm) ++c->gpass_ptr[T.grouped.chunks[i].layer + 1];
         for (int p = 0; p < T.grouped.npass; ++p) c->gpass_ptr[p + 1] += c->gpass_ptr[p];
         up(&c->d_gall_m, gm);
-        // moment projection: one item per half of a chunk's functions, the
-        // costliest (entries times the FP64 instructions per entry) first
+        // moment projection: the costliest items (FP64 instructions of a wave:
+        // per entry, and at the ends of its runs) first
         std::vector<int32_t> items;
         std::vector<int64_t> cost;
         for (int32_t i : gm) {
             const HubChunk& C = T.grouped.chunks[i];
-            for (int h = 0; h * HUB_MOM_NFW < C.L; ++h) {
-                const int nfw = std::min(HUB_MOM_NFW, C.L - h * HUB_MOM_NFW);
-                items.push_back(2 * i + h);
-                cost.push_back(static_cast<int64_t>(C.ne) * (8 * nfw + 12));
+            const double* d = &T.grouped.d0[3 * static_cast<size_t>(C.e0)];
+            int64_t runs = 1;
+            for (int e = 1; e < C.nreal; ++e)
+                if (d[3 * e] != d[3 * e - 3] || d[3 * e + 1] != d[3 * e - 2]) ++runs;
+            const int64_t nfw = (C.L + hub_mom_parts(C.L) - 1) / hub_mom_parts(C.L);
+            for (int h = 0; h < hub_mom_waves(C.L); ++h) {
+                items.push_back(4 * i + h);
+                cost.push_back(C.ne * (4 * nfw + 8) + runs * 8 * nfw);
             }
         }
         std::vector<int32_t> order(items.size());

@@ -32,9 +32,12 @@ struct ProjArgs {
     // position-moment launch (k_project_mom) only: per grouped point the
     // displacement d0[3] from its chunk's first cover, per chunk and function
     // the offset fdel[HUB_GF_MAX][3] to its own cover; component i (0: the
-    // orbitals, 1-3: the moments) is written to part + i * pplane
+    // orbitals, 1-3: the moments) is written to part + i * pplane.  mgidx:
+    // gidx, with the sign bit set where d0's x or y component differs from
+    // the entry before (in the same chunk)
     const double* d0;
     const double* fdel;
+    const int32_t* mgidx;
     int64_t pplane;
 };
 
@@ -269,10 +272,18 @@ hipError_t launch_project_f32(const ProjArgs& a, int nchunks, int nq, int cplx, 
 hipError_t launch_project_f64(const ProjArgs& a, int nchunks, int nq, int cplx, int cpl, int waves, int cls,
                               hipStream_t st);
 // orbital and position-moment projections of complex states over grouped
-// chunks (k_project_mom.h).  Work items: chunk * 2 + h, h the half of the
-// chunk's functions (h = 1 only for chunks with more than HUB_MOM_NFW
-// functions); a.chunk_list holds nitems of them.
-#define HUB_MOM_NFW 8
+// chunks (k_project_mom.h), whose waves take at most HUB_MOM_NFW functions
+// each.  Work items: chunk * 4 + sub, sub < hub_mom_waves(functions);
+// a.chunk_list holds nitems of them.
+#define HUB_MOM_NFW 5
+// parts of a grouped chunk of L functions
+__host__ __device__ constexpr int hub_mom_parts(int L) { return (L + HUB_MOM_NFW - 1) / HUB_MOM_NFW; }
+// waves of a work-group that share a column tile of such a chunk (a power of two)
+__host__ __device__ constexpr int hub_mom_waves(int L) {
+    return hub_mom_parts(L) <= 2 ? hub_mom_parts(L) : 4;
+}
+// first function of part h
+__host__ __device__ constexpr int hub_mom_first(int L, int h) { return L * h / hub_mom_parts(L); }
 hipError_t launch_project_mom_f32(const ProjArgs& a, int nitems, int nq, hipStream_t st);
 hipError_t launch_project_mom_f64(const ProjArgs& a, int nitems, int nq, hipStream_t st);
 hipError_t launch_apply_f32(const ApplyArgs& a, int nchunks, int nq, int cplx, int cpl, int waves,
