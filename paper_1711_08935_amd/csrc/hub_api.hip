@@ -789,6 +789,13 @@ size_t occ_need(const hub_ctx* c, int nstates) {
     return static_cast<size_t>(c->T.nsites) * nchan * hub_occ_splits(c->nk, nstates) * HUB_OCC_PAIRS * 4;
 }
 
+// Orbitals up to which k_occ_one forms N-bar itself instead of reading
+// k_nbar's: a work-group per site and channel then reads every orbital of its
+// species, so the work grows with the sites' square.  hub_occupations with
+// N-bar and P-bar of 60 states: 13.7 us with 16 orbitals and 13.8 with 117,
+// against 16.2 and 16.4 with a launch of its own.
+constexpr int kFormNbar = 128;
+
 int do_occupations(hub_ctx* c, const double* cc, int nstates, const double* f, double* n, double* pbar, double* nbar,
                    bool per_site) {
     const int ncol = c->ncol(nstates);
@@ -798,7 +805,9 @@ int do_occupations(hub_ctx* c, const double* cc, int nstates, const double* f, d
         if (st) return st;
         ws = c->d_occ_ws;
     }
-    if (pbar && !nbar) {
+    const int nsplit = hub_occ_splits(c->nk, nstates);
+    const bool form = !per_site && nsplit == 1 && c->T.J <= kFormNbar && nstates > 0;
+    if (pbar && !nbar && !form) {
         if (c->ws_fixed) {
             nbar = c->ws_fixed->nbar;
         } else {
@@ -808,7 +817,7 @@ int do_occupations(hub_ctx* c, const double* cc, int nstates, const double* f, d
             nbar = c->d_nbar_ws;
         }
     }
-    if (nbar) {
+    if (nbar && !form) {
         NbarArgs b{};
         b.c = cc;
         b.nbar = nbar;
@@ -842,8 +851,14 @@ int do_occupations(hub_ctx* c, const double* cc, int nstates, const double* f, d
     o.nk = c->nk;
     o.nblk = c->nblk();
     o.nspecies = c->T.nspecies;
-    o.nsplit = hub_occ_splits(c->nk, nstates);
+    o.nsplit = nsplit;
     o.ws = ws;
+    if (form && (pbar || nbar)) {
+        o.nbar = nullptr;
+        o.nbar_out = nbar;
+        o.species_orb_ptr = c->d_species_orb_ptr;
+        o.species_orb_ids = c->d_species_orb_ids;
+    }
     StageTimer tm(c, HUB_STAGE_OCC);
     if (!per_site) {
         HUB_TRY(launch_occ(o, 0, c->T.nsites, c->stream));
@@ -854,7 +869,7 @@ int do_occupations(hub_ctx* c, const double* cc, int nstates, const double* f, d
 }
 
 // N-bar, n, P-bar and U-bar, J-bar, U_eff of the batched step in two
-// launches (k_step_occ_part, k_step_occ_final): the same sums in the same
+// launches (k_occ_part, k_step_occ_final) or one (k_occ_one): the same sums in the same
 // order as do_occupations followed by do_acbn0.
 int do_step_occ(hub_ctx* c, const hub_step_io* io) {
     double* ws = c->ws_fixed ? c->ws_fixed->occ : nullptr;

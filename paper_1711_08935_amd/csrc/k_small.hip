@@ -260,79 +260,6 @@ __device__ __forceinline__ void stage_pairs(const OccArgs& a, int ch, int orb0, 
         }
 }
 
-__global__ void __launch_bounds__(NB) k_occ_part(const OccArgs a) {
-    const int site = blockIdx.x;
-    const int ch = blockIdx.y;
-    const int split = blockIdx.z;
-    const int L = a.site_L[site];
-    const int orb0 = a.site_orb0[site];
-    const int T = a.site_species[site];
-    const int ncp = a.spinor ? 2 * L : L;            // rows of the combined matrix
-    const int npairs = ncp * ncp;
-    const int nslice = NB / npairs;
-    const int tid = threadIdx.x;
-    const int pair = tid % npairs;
-    const int slice = tid / npairs;
-    const bool worker = slice < nslice;
-    const int ra = pair / ncp, rb = pair % ncp;      // combined index: sigma * L + m
-
-    __shared__ double cs[2][7][TILE][2];
-    __shared__ double wt[TILE], wtn[TILE];
-    __shared__ double red[NB][4];
-
-    // this split's (k, state) pairs, flattened as k * nstates + s
-    const int np = a.nk * a.nstates;
-    const int per = (np + a.nsplit - 1) / a.nsplit;
-    const int p0 = split * per;
-    const int p1 = min(np, p0 + per);
-    double nr = 0.0, ni = 0.0, pr = 0.0, pi = 0.0;
-    for (int t0 = p0; t0 < p1; t0 += TILE) {
-        stage_pairs(a, ch, orb0, L, t0, p1, cs);
-        const int pp = t0 + tid;
-        if (tid < TILE) {
-            double w = 0.0, nb = 0.0;
-            if (pp < p1) {
-                const int k = pp / a.nstates, s = pp - k * a.nstates;
-                const int q = a.spinor ? k : k * a.nspin + ch;
-                w = a.kweights[k] * a.f[static_cast<int64_t>(q) * a.nstates + s];
-                if (a.nbar != nullptr) nb = a.nbar[(static_cast<int64_t>(q) * a.nspecies + T) * a.nstates + s];
-            }
-            wt[tid] = w;
-            wtn[tid] = w * nb;
-        }
-        __syncthreads();
-        if (worker) {
-            const int xa = ra / L, ma = ra % L, xb = rb / L, mb = rb % L;
-            const int nt = min(TILE, p1 - t0);
-            for (int t = slice; t < nt; t += nslice) {
-                // conj(c_a) c_b
-                const double ar = cs[xa][ma][t][0], ai = cs[xa][ma][t][1];
-                const double br = cs[xb][mb][t][0], bi = cs[xb][mb][t][1];
-                const double re = ar * br + ai * bi;
-                const double im = ar * bi - ai * br;
-                nr = fma(wt[t], re, nr);
-                ni = fma(wt[t], im, ni);
-                pr = fma(wtn[t], re, pr);
-                pi = fma(wtn[t], im, pi);
-            }
-        }
-        __syncthreads();
-    }
-    red[tid][0] = nr;
-    red[tid][1] = ni;
-    red[tid][2] = pr;
-    red[tid][3] = pi;
-    __syncthreads();
-    const int nchan = gridDim.y;
-    double* w = a.ws + ((static_cast<int64_t>(site) * nchan + ch) * a.nsplit + split) * (HUB_OCC_PAIRS * 4);
-    for (int o = tid; o < npairs; o += NB) {
-        double v[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int z = 0; z < nslice; ++z)
-            for (int r = 0; r < 4; ++r) v[r] += red[z * npairs + o][r];
-        for (int r = 0; r < 4; ++r) w[o * 4 + r] = v[r];
-    }
-}
-
 // Sums the splits of one site and NCH channels (ch0, ch0 + 1, ...) in
 // order: out = n and P-bar entries (blocks of the channel, zeros outside the
 // L x L corner), one thread per (entry, value) so that every split's load is
@@ -558,15 +485,15 @@ __global__ void __launch_bounds__(NB) k_acbn0(const Acbn0Args a) {
 
 // ---------------------------------------------------------------- fused step
 // N-bar, n, P-bar and U-bar/J-bar of the batched step in two launches.
-// k_step_occ_part: work-group (site, channel, split) stages the c of its
-// (k-point, state) pairs tile by tile, forms N-bar of each pair from the
-// species' projections (nbar_part: the order of k_nbar; the first site of a
-// species writes it out) and sums its split of n and P-bar as k_occ_part
-// does.  k_step_occ_final: one work-group per site sums every split of every
-// channel in order (as k_occ_final), writes n and P-bar and runs the site's
-// ACBN0 step from LDS (acbn0_site).  The kernel boundary orders the two; a
-// completion count inside one launch was measured slower, since every
-// work-group's device-scope release then writes back its L2.
+// k_occ_part: work-group (site, channel, split) stages the c of its (k-point,
+// state) pairs tile by tile, forms N-bar of each pair from the species'
+// projections (nbar_part: the order of k_nbar; the first site of a species
+// writes it out) and sums its split of n and P-bar.  k_step_occ_final: one
+// work-group per site sums every split of every channel in order (as
+// k_occ_final), writes n and P-bar and runs the site's ACBN0 step from LDS
+// (acbn0_site).  The kernel boundary orders the two; a completion count
+// inside one launch was measured slower, since every work-group's
+// device-scope release then writes back its L2.
 struct OccLds {
     double cs[2][7][TILE][2];
     double wt[TILE], wtn[TILE];
@@ -574,11 +501,10 @@ struct OccLds {
     double nbp[NBPART][TILE];
 };
 
-__global__ void __launch_bounds__(NB) k_step_occ_part(const OccArgs a) {
-    const int site = blockIdx.x;
-    const int ch = blockIdx.y;
-    const int split = blockIdx.z;
-    const int nchan = gridDim.y;
+// Sums of one site, channel and range p0..p1 of (k-point, state) pairs: every
+// thread's slice of its (a, b) pair into sm.red (n, then P-bar).  N-bar is
+// formed here (a.species_orb_ptr set) or read from a.nbar (0 if null).
+__device__ __forceinline__ void occ_channel(const OccArgs& a, int site, int ch, int p0, int p1, OccLds& sm) {
     const int L = a.site_L[site];
     const int orb0 = a.site_orb0[site];
     const int T = a.site_species[site];
@@ -592,34 +518,30 @@ __global__ void __launch_bounds__(NB) k_step_occ_part(const OccArgs a) {
     const int slice = tid / npairs;
     const bool worker = slice < nslice;
     const int ra = pair / ncp, rb = pair % ncp;
-
-    __shared__ struct {
-        OccLds o;
-    } sm;
+    const bool form = a.species_orb_ptr != nullptr;
 
     // the first site of each species writes that species' N-bar
-    bool writer = a.nbar_out != nullptr;
+    bool writer = form && a.nbar_out != nullptr;
     for (int s2 = 0; s2 < site && writer; ++s2) writer = a.site_species[s2] != T;
-    const int sp0 = a.species_orb_ptr[T], sp1 = a.species_orb_ptr[T + 1];
+    const int sp0 = form ? a.species_orb_ptr[T] : 0, sp1 = form ? a.species_orb_ptr[T + 1] : 0;
 
-    const int np = a.nk * a.nstates;
-    const int per = (np + a.nsplit - 1) / a.nsplit;
-    const int p0 = split * per;
-    const int p1 = min(np, p0 + per);
     double nr = 0.0, ni = 0.0, pr = 0.0, pi = 0.0;
     for (int t0 = p0; t0 < p1; t0 += TILE) {
-        stage_pairs(a, ch, orb0, L, t0, p1, sm.o.cs);
+        stage_pairs(a, ch, orb0, L, t0, p1, sm.cs);
         const int pp = t0 + tid;
+        double given = 0.0;
         if (tid < TILE) {
             double w = 0.0;
             if (pp < p1) {
                 const int k = pp / a.nstates, s = pp - k * a.nstates;
                 const int q = a.spinor ? k : k * a.nspin + ch;
                 w = a.kweights[k] * a.f[static_cast<int64_t>(q) * a.nstates + s];
+                if (!form && a.nbar != nullptr)
+                    given = a.nbar[(static_cast<int64_t>(q) * a.nspecies + T) * a.nstates + s];
             }
-            sm.o.wt[tid] = w;
+            sm.wt[tid] = w;
         }
-        {
+        if (form) {
             // N-bar of the tile's pairs: part tid / TILE (one wave each) of pair tid % TILE
             static_assert(TILE == 64 && NB == NBPART * TILE, "one N-bar part per wave");
             const int pl = tid % TILE, part = __builtin_amdgcn_readfirstlane(tid / TILE);
@@ -631,13 +553,13 @@ __global__ void __launch_bounds__(NB) k_step_occ_part(const OccArgs a) {
                 v = nbar_part(a.c, a.species_orb_ids, sp0, sp1, part, static_cast<int64_t>(q) * a.J * a.ncol * NC, s,
                               a.ncol, NC, nsig);
             }
-            sm.o.nbp[part][pl] = v;
+            sm.nbp[part][pl] = v;
+            __syncthreads();
         }
-        __syncthreads();
         if (tid < TILE) {
-            const double nb = (sm.o.nbp[0][tid] + sm.o.nbp[1][tid]) + (sm.o.nbp[2][tid] + sm.o.nbp[3][tid]);
-            sm.o.wtn[tid] = sm.o.wt[tid] * nb;
-            if (a.nbar_out != nullptr && pp < p1) {
+            const double nb = form ? (sm.nbp[0][tid] + sm.nbp[1][tid]) + (sm.nbp[2][tid] + sm.nbp[3][tid]) : given;
+            sm.wtn[tid] = sm.wt[tid] * nb;
+            if (form && a.nbar_out != nullptr && pp < p1) {
                 const int k = pp / a.nstates, s = pp - k * a.nstates;
                 const int q = a.spinor ? k : k * a.nspin + ch;
                 double* out = a.nbar_out + static_cast<int64_t>(q) * a.nspecies * a.nstates + s;
@@ -654,32 +576,92 @@ __global__ void __launch_bounds__(NB) k_step_occ_part(const OccArgs a) {
             const int xa = ra / L, ma = ra % L, xb = rb / L, mb = rb % L;
             const int nt = min(TILE, p1 - t0);
             for (int t = slice; t < nt; t += nslice) {
-                const double ar = sm.o.cs[xa][ma][t][0], ai = sm.o.cs[xa][ma][t][1];
-                const double br = sm.o.cs[xb][mb][t][0], bi = sm.o.cs[xb][mb][t][1];
+                // conj(c_a) c_b
+                const double ar = sm.cs[xa][ma][t][0], ai = sm.cs[xa][ma][t][1];
+                const double br = sm.cs[xb][mb][t][0], bi = sm.cs[xb][mb][t][1];
                 const double re = ar * br + ai * bi;
                 const double im = ar * bi - ai * br;
-                nr = fma(sm.o.wt[t], re, nr);
-                ni = fma(sm.o.wt[t], im, ni);
-                pr = fma(sm.o.wtn[t], re, pr);
-                pi = fma(sm.o.wtn[t], im, pi);
+                nr = fma(sm.wt[t], re, nr);
+                ni = fma(sm.wt[t], im, ni);
+                pr = fma(sm.wtn[t], re, pr);
+                pi = fma(sm.wtn[t], im, pi);
             }
         }
         __syncthreads();
     }
-    sm.o.red[tid][0] = nr;
-    sm.o.red[tid][1] = ni;
-    sm.o.red[tid][2] = pr;
-    sm.o.red[tid][3] = pi;
+    sm.red[tid][0] = nr;
+    sm.red[tid][1] = ni;
+    sm.red[tid][2] = pr;
+    sm.red[tid][3] = pi;
     __syncthreads();
-    {
-        double* w = a.ws + ((static_cast<int64_t>(site) * nchan + ch) * a.nsplit + split) * (HUB_OCC_PAIRS * 4);
-        for (int o = tid; o < npairs; o += NB) {
-            double v[4] = {0.0, 0.0, 0.0, 0.0};
-            for (int z = 0; z < nslice; ++z)
-                for (int r = 0; r < 4; ++r) v[r] += sm.o.red[z * npairs + o][r];
-            for (int r = 0; r < 4; ++r) w[o * 4 + r] = v[r];
+}
+
+// One split of a site and channel into the workspace.
+__global__ void __launch_bounds__(NB) k_occ_part(const OccArgs a) {
+    const int site = blockIdx.x, ch = blockIdx.y, split = blockIdx.z;
+    const int ncp = (a.spinor ? 2 : 1) * a.site_L[site], npairs = ncp * ncp, nslice = NB / npairs;
+    __shared__ OccLds sm;
+    const int np = a.nk * a.nstates;
+    const int per = (np + a.nsplit - 1) / a.nsplit;
+    const int p0 = split * per;
+    occ_channel(a, site, ch, p0, min(np, p0 + per), sm);
+    double* w = a.ws + ((static_cast<int64_t>(site) * gridDim.y + ch) * a.nsplit + split) * (HUB_OCC_PAIRS * 4);
+    for (int o = threadIdx.x; o < npairs; o += NB) {
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int z = 0; z < nslice; ++z)
+            for (int r = 0; r < 4; ++r) v[r] += sm.red[z * npairs + o][r];
+        for (int r = 0; r < 4; ++r) w[o * 4 + r] = v[r];
+    }
+}
+
+// One split only (at most a tile of pairs): n and P-bar of a site and channel
+// without the workspace, the slices summed as by k_occ_part, and with STEP
+// (one channel) the site's ACBN0 step, all in one launch.  Launch and latency
+// bound: the step of one d shell with 16 states 31.4 us against 32.5 with
+// k_occ_part and k_step_occ_final, of 64 shells with 60 states 198 against
+// 203; the separate calls of four shells 114.5 us against 121 with k_nbar,
+// k_occ_part and k_occ_final.  Two channels one after the other in the step's
+// work-group were slower than the two launches (58.6 us against 57.4).
+template <bool STEP>
+__global__ void __launch_bounds__(NB) k_occ_one(const OccArgs a, const Acbn0Args u) {
+    const int site = blockIdx.x;
+    const int L = a.site_L[site];
+    const int ncp = (a.spinor ? 2 : 1) * L, npairs = ncp * ncp, nslice = NB / npairs;
+    const int nblk_here = a.spinor ? 4 : 1;
+    __shared__ OccLds sm;
+    __shared__ typename std::conditional<STEP, AcbLds, int>::type acb;
+    bool tens = false;
+    if constexpr (STEP) {
+        // the site's tensor first: its loads overlap the sums below
+        tens = isnan(u.ueff_fixed[site]);
+        if (tens) {
+            const double* Tg = u.tensor + static_cast<int64_t>(site) * 2401;
+#pragma unroll 4
+            for (int o = threadIdx.x; o < L * L * L * L; o += NB) acb.Ts[o] = Tg[o];
         }
     }
+    const int ch = blockIdx.y;
+    occ_channel(a, site, ch, 0, a.nk * a.nstates, sm);
+    for (int o = threadIdx.x; o < nblk_here * 49 * 4; o += NB) {
+        const int r = o & 3, eb = o >> 2;
+        const int blk = eb / 49, e = eb % 49, i = e / 7, j = e % 7;
+        double v = 0.0;
+        if (i < L && j < L) {
+            const int x = a.spinor ? blk / 2 : 0, y = a.spinor ? blk % 2 : 0;
+            const int p = (x * L + i) * ncp + (y * L + j);
+            for (int z = 0; z < nslice; ++z) v += sm.red[z * npairs + p][r];
+        }
+        const int oblk = a.spinor ? blk : ch;
+        const int64_t base = ((static_cast<int64_t>(site) * a.nblk + oblk) * 49 + e) * 2;
+        if (r < 2) {
+            a.n[base + r] = v;
+            if constexpr (STEP) acb.Nf[oblk][i][j][r] = v;
+        } else {
+            if (a.pbar) a.pbar[base + r - 2] = v;
+            if constexpr (STEP) acb.P[oblk][i][j][r - 2] = v;
+        }
+    }
+    if constexpr (STEP) acbn0_site(u, site, acb, tens);
 }
 
 __global__ void __launch_bounds__(NB) k_step_occ_final(const OccArgs a, const Acbn0Args u) {
@@ -1005,6 +987,10 @@ hipError_t launch_occ(const OccArgs& a, int site0, int nsites, hipStream_t st) {
     b.n += static_cast<int64_t>(site0) * a.nblk * 98;
     if (b.pbar) b.pbar += static_cast<int64_t>(site0) * a.nblk * 98;
     const int nchan = a.spinor ? 1 : a.nspin;
+    if (a.nsplit == 1) {
+        hipLaunchKernelGGL((k_occ_one<false>), dim3(nsites, nchan), dim3(NB), 0, st, b, Acbn0Args{});
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_occ_part, dim3(nsites, nchan, a.nsplit), dim3(NB), 0, st, b);
     hipLaunchKernelGGL(k_occ_final, dim3(nsites, nchan), dim3(NB), 0, st, b);
     return hipGetLastError();
@@ -1014,7 +1000,11 @@ hipError_t launch_step_occ(const OccArgs& a, const Acbn0Args& u, hipStream_t st)
     const int nsites = static_cast<int>(a.nsites);
     if (nsites <= 0) return hipSuccess;
     const int nchan = a.spinor ? 1 : a.nspin;
-    hipLaunchKernelGGL(k_step_occ_part, dim3(nsites, nchan, a.nsplit), dim3(NB), 0, st, a);
+    if (a.nsplit == 1 && nchan == 1) {
+        hipLaunchKernelGGL((k_occ_one<true>), dim3(nsites), dim3(NB), 0, st, a, u);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_occ_part, dim3(nsites, nchan, a.nsplit), dim3(NB), 0, st, a);
     hipLaunchKernelGGL(k_step_occ_final, dim3(nsites), dim3(NB), 0, st, a, u);
     return hipGetLastError();
 }

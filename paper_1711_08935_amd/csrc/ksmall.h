@@ -58,10 +58,11 @@ struct OccArgs {
     int J; int ncol; int nstates; int ncplx; int spinor; int nspin; int nk; int nblk; int nspecies;
     int nsplit;               // (k-point, state) splits of the first pass
     double* ws;               // [site][channel][nsplit][HUB_OCC_PAIRS][4] partial sums
-    // batched step kernels (k_step_occ_part / k_step_occ_final) only:
-    int nsites;
-    const int32_t* species_orb_ptr; const int32_t* species_orb_ids;   // N-bar from c
-    double* nbar_out;         // [q][species][nstates] or null
+    int nsites;               // sites of a batched step
+    // set: N-bar is formed from c (and written to nbar_out, [q][species][nstates]
+    // or null); null: it is read from nbar
+    const int32_t* species_orb_ptr; const int32_t* species_orb_ids;
+    double* nbar_out;
 };
 
 // (k-point, state) splits of the occupation sums: about 64 pairs each
