@@ -740,12 +740,23 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     const int list = stencil_table(table) ? c->stencil_nchunks : static_cast<int>(c->T.chunks.size());
     const bool full = !per_site && proj_groups(c, list, ncol, cpl, a.wide) >= kFullLaunch;
     // gradients in a launch that does not fill the chip: two values per lane
-    // instead of four (4 d shells, 512 FP32 columns: 42 us against 45)
+    // instead of four (4 d shells, 512 FP32 columns: 42 us against 45).  On
+    // the dilated points only where the columns' last wave then fills better:
+    // 32 d shells, 100 FP32 columns 136 us against 169, but 200 and 256
+    // columns (twice the work-groups) 214 and 220 us against 196 and 206
     if (grad && !full && !c->tune_cpl[0] && cpl * c->ncplx() > 2) {
-        cpl = 2 / c->ncplx();
-        a.wide = pick_wide(c, ncol, cpl, 0);
+        const int half = 2 / c->ncplx(), wide = pick_wide(c, ncol, half, 0);
+        if (!stencil_table(table) ||
+            proj_groups(c, list, ncol, half, wide) < 2 * proj_groups(c, list, ncol, cpl, a.wide)) {
+            cpl = half;
+            a.wide = wide;
+        }
     }
-    const int waves = c->tune_waves[0] ? c->tune_waves[0] : (full ? (grad ? 2 : 1) : 4);
+    // one value per lane: the waves wait for the tables, so four even where
+    // the launch is full (32 d shells, 139 FP32 columns 243, 253 and 231 us
+    // with one, two and four; 64 uneven shells, 129 columns 354, 318 and 283)
+    const int gw = cpl * c->ncplx() == 1 ? 4 : 2;
+    const int waves = c->tune_waves[0] ? c->tune_waves[0] : (full ? (grad ? gw : 1) : 4);
     if (!per_site) {
         a.split = proj_split(c, list, stencil_table(table) ? c->stencil_part_rows : c->T.part_rows, ncol, cpl, a.wide);
         a.prows *= a.split;
