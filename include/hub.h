@@ -155,7 +155,7 @@ int hub_set_chunk(hub_ctx* ctx, int chunk_entries);
 
 /* Kernel shape for the projection (which = 0) and the application
  * (which = 1): columns handled per lane (1, 2 or 4; 0 = automatic), waves
- * per work-group (1, 2 or 4), and the lane layout (1: every wave inside one
+ * per work-group (1, 2 or 4; by default chosen from the launch's size), and the lane layout (1: every wave inside one
  * state set; 0: narrow state sets packed across the lanes of a wave;
  * -1: automatic).  Every shape computes the same result.  Any time after
  * creation. */
@@ -169,7 +169,11 @@ int hub_set_tuning(hub_ctx* ctx, int which, int cols_per_lane, int waves, int la
  * in successive atomic-free layers.  A grid point covered by more than 16
  * orbitals in total has its covers split over several passes of the
  * grouped list (at most 16 functions each; the apply launches the passes in
- * turn, hub_query 14).  Both give the same results up to summation order.
+ * turn, hub_query 14); for complex states without a field or spin-dependent
+ * orbitals, the projection and the apply then use a list with each point's
+ * covers summed over the images of a site instead, whose tables (at most
+ * 4 GiB, and half of the free device memory) hub_finalize makes.  All give the same results up to summation
+ * order.
  * Any time. */
 int hub_set_worklist(hub_ctx* ctx, int grouped_list);
 
@@ -421,7 +425,7 @@ int hub_step(hub_ctx* ctx, const hub_step_io* io, int mode);
  * U_eff, hpsi) agree with hub_step's to rounding, and J with hub_current's.
  * Elsewhere (HUB_STEP_PERSITE, the per-site work list, real states) it runs
  * hub_step's stages, bit for bit, and hub_current's own projection.  The first fused call uploads the moment
- * tables (three displacements per grouped point).  Errors: those of
+ * tables (three displacements and an index per grouped point).  Errors: those of
  * hub_step; HUB_EINVAL for a null J. */
 int hub_step_current(hub_ctx* ctx, const hub_step_io* io, double* J, int mode);
 
@@ -440,7 +444,9 @@ int hub_step_current(hub_ctx* ctx, const hub_step_io* io, double* J, int mode);
  * serialized by the caller.  Needs hub_finalize (which takes the array's
  * device address) and the Coulomb tensors unless every U_eff is fixed.
  * Errors: those of hub_step, and HUB_ESCRATCH when the step's workspace
- * exceeds HUB_SCRATCH_BYTES (nothing is launched). */
+ * exceeds HUB_SCRATCH_BYTES (nothing is launched; the image-summed list's
+ * coefficients do not count, without room for them the step runs the grouped
+ * list's passes). */
 #define HUB_SCRATCH_BYTES (128u << 20)
 int hub_step_noalloc(hub_ctx* ctx, const hub_step_io* io);
 

@@ -1509,14 +1509,16 @@ namespace {
 int gauge_tables(hub_ctx* c);
 
 // Bloch-summed work list and its tables for every k-point, from the plain
-// phases on the device; contexts whose tables would pass kBlochBytes keep the
-// grouped list's passes.
+// phases on the device; contexts whose tables would pass kBlochBytes, or half
+// of the device memory that is free, keep the grouped list's passes.
 constexpr size_t kBlochBytes = size_t(4) << 30;
 hipError_t build_bloch(hub_ctx* c, size_t& bytes) {
     BlochTables B;
     hub_build_bloch(c->T, c->G(), c->chunk_entries, B);
     const size_t wbytes = static_cast<size_t>(B.wlen) * c->nk * sizeof(double);
     if (wbytes > kBlochBytes || B.gidx.size() > INT32_MAX || B.part_rows > INT32_MAX) return hipSuccess;
+    size_t avail = 0, total = 0;
+    if (hipMemGetInfo(&avail, &total) != hipSuccess || wbytes > avail / 2) return hipSuccess;
     hipError_t e = hipSuccess;
     auto up = [&](auto** dst, const auto& src, size_t& n) {
         if (e == hipSuccess) e = upload(c, dst, src, n);
