@@ -118,6 +118,7 @@ struct hub_ctx {
                                                    // at the first hub_step_current
     // Bloch-summed work list (k_bloch.hip), where the grouped list needs passes
     bool bloch = false;
+    double pass_rows = 1.0;                  // rows the grouped list's passes read over the covered points
     bool no_bloch = false;                   // the call in flight does without (scratch limit)
     std::vector<int32_t> bl_pass_ptr;
     int64_t bl_part_rows = 0, bl_wlen = 0;
@@ -428,10 +429,29 @@ bool built(const hub_ctx* c) { return c && c->built_dev; }
 bool grouped(const hub_ctx* c) { return c->use_grouped && c->T.grouped.ok; }
 
 // The Bloch-summed list takes the place of the grouped list's passes (without
-// a field, which changes the phases at every step).
-bool use_bloch(const hub_ctx* c) { return c->bloch && !c->no_bloch && grouped(c) && !c->gauge; }
+// a field, which changes the phases at every step):
+// * for launches that do not fill the chip, which save the passes' launches
+//   (2 sets of 20 FP64 columns 68 us, 95 in passes), and for up to 32 columns,
+//   one wave's tile (16 sets of 17 FP64 columns 222 and 297 us);
+// * else where the passes read enough rows again.  Its tiles take 16 columns,
+//   rows that do not start on 128 bytes make it read lines twice, and the
+//   passes' waves idle past the last of 64 columns: these weigh in.  A 48^3
+//   rocksalt cell, 16 sets of 64 FP32 columns, rows in passes over rows 1.01,
+//   1.06, 1.15 and 1.40: this list 720, 734, 756 and 769 us, passes 666, 705,
+//   775 and 925; 33 FP64 columns at 1.06: 946 and 800; 45 FP32 columns at
+//   1.15: 801 and 676; 90 FP64 columns on 52^3 at 1.06: 2517 and 2692; 50
+//   FP64 columns on 44^3 at 1.06 and 1.28: 1032 and 889, 1051 and 1076.
+bool use_bloch(const hub_ctx* c, int ncol) {
+    if (!c->bloch || c->no_bloch || !grouped(c) || c->gauge) return false;
+    if (ncol <= 32 || proj_groups(c, static_cast<int>(c->T.grouped.chunks.size()), ncol, 1, 0) < kFullLaunch)
+        return true;
+    const double pad = (ncol + 15) / 16 * 16.0 / ncol;
+    const double idle = ncol < HUB_WAVE ? 1.0 : (ncol + 63) / 64 * 64.0 / ncol;
+    const bool lines = static_cast<size_t>(ncol) * c->elem() % 128 == 0;
+    return c->pass_rows * idle >= 1.1 * (1.0 + 0.35 * (pad - 1.0)) * (lines ? 1.0 : 1.05);
+}
 size_t bcoef_need(const hub_ctx* c, int ncol) {
-    return use_bloch(c) ? static_cast<size_t>(c->nsets()) * c->T.J * ncol * 2 : 0;
+    return use_bloch(c, ncol) ? static_cast<size_t>(c->nsets()) * c->T.J * ncol * 2 : 0;
 }
 
 // Columns per lane so that a lane's FP64 accumulators (functions x scalars)
@@ -575,7 +595,7 @@ size_t part_need(const hub_ctx* c, int ncol, int mult) {
     if (c->T.grouped.ok)
         rows = std::max<int64_t>(rows, rows_of(static_cast<int>(c->T.grouped.chunks.size()), c->T.grouped.part_rows));
     if (mult == 3) rows = std::max<int64_t>(rows, rows_of(c->stencil_nchunks, c->stencil_part_rows) * 3);
-    if (use_bloch(c)) rows = std::max(rows, c->bl_part_rows * bloch_split(c, ncol, 2));
+    if (use_bloch(c, ncol)) rows = std::max(rows, c->bl_part_rows * bloch_split(c, ncol, 2));
     return static_cast<size_t>(c->nsets()) * rows * ncol * c->ncplx();
 }
 // the grouped projection with the three position-moment components as well
@@ -631,7 +651,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     ProjArgs a = proj_args(c, psi, ld, ncol, table);
     a.part = part;
     a.nq = nq;
-    if (!per_site && !grad && !mout && use_bloch(c)) {
+    if (!per_site && !grad && !mout && use_bloch(c, ncol)) {
         BlochArgs b = bloch_args(c, ld, ncol, q0, nq);
         b.psi = psi;
         b.part = part;
@@ -1032,7 +1052,7 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
             b.split = split_of(c, static_cast<int64_t>(nch) * nq * lanes(cpl) / cpl, 0.0);
             return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, apply_waves(c), k, store, s);
         };
-        if (!overwrite && use_bloch(c)) {
+        if (!overwrite && use_bloch(c, ncol)) {
             double* B = c->ws_fixed ? c->ws_fixed->bcoef : nullptr;
             if (!B) {
                 const int st = ensure(&c->d_bcoef, &c->bcoef_cap, bcoef_need(c, ncol), c);
@@ -1184,7 +1204,7 @@ int step_impl(hub_ctx* c, const hub_step_io* io, int mode, double* jcur) {
     }
     st = ensure(&c->d_part, &c->part_cap, part, c);
     if (st) return st;
-    if (use_bloch(c)) {
+    if (use_bloch(c, ncol)) {
         st = ensure(&c->d_bcoef, &c->bcoef_cap, bcoef_need(c, ncol), c);
         if (st) return st;
     }
@@ -1677,6 +1697,10 @@ int hub_finalize(hub_ctx* c, void* stream) {
         std::vector<unsigned char> cover(static_cast<size_t>(c->G()), 0);
         for (int32_t g : T.grouped.gidx) cover[g] = 1;
         up(&c->d_cover, cover);
+        double rows = 0.0, points = 0.0;
+        for (const HubChunk& C : T.grouped.chunks) rows += C.nreal;
+        for (unsigned char v : cover) points += v;
+        c->pass_rows = rows / std::max(1.0, points);
         up(&c->d_gtab, T.grouped.tab);
         std::vector<HubFun> fun(T.grouped.f_orb.size(), HubFun{});
         for (size_t i = 0; i < fun.size(); ++i) {
@@ -2107,7 +2131,7 @@ int hub_step_noalloc(hub_ctx* c, const hub_step_io* io) {
         n_part = slice256(part_need(c, ncol, c->T.spindep ? 2 : 1));
         n_b = slice256(bcoef_need(c, ncol));
         if ((n_part + n_occ + n_nbar + n_sink + n_b) * sizeof(double) <= HUB_SCRATCH_BYTES) break;
-        if (t == 1 || !use_bloch(c)) {
+        if (t == 1 || !use_bloch(c, ncol)) {
             c->no_bloch = false;
             return HUB_ESCRATCH;
         }
