@@ -170,8 +170,8 @@ int hub_set_tuning(hub_ctx* ctx, int which, int cols_per_lane, int waves, int la
  * orbitals in total has its covers split over several passes of the
  * grouped list (at most 16 functions each; the apply launches the passes in
  * turn, hub_query 14); for complex states without a field or spin-dependent
- * orbitals, the projection and the apply then use a list with each point's
- * covers summed over the images of a site instead, whose tables (at most
+ * orbitals, the projection and the apply then use, where it is faster, a
+ * list with each point's covers summed over the images of a site, whose tables (at most
  * 4 GiB, and half of the free device memory) hub_finalize makes.  All give the same results up to summation
  * order.
  * Any time. */
