@@ -221,7 +221,10 @@ int hub_set_stream(hub_ctx* ctx, void* stream);
  * have their covers split over passes; 0 without a grouped work list),
  * 15 device allocations (hipMalloc) the context has made so far, 16 step
  * graphs captured so far (HUB_STEP_GRAPH keeps the last two argument sets'
- * graphs; a third set replaces the one used least recently). */
+ * graphs; a third set replaces the one used least recently), 17 whether
+ * hub_finalize built the image-summed list (1, else 0; hub_set_worklist),
+ * 18 projections and applies that took that list so far (one for each call;
+ * for a captured step, at its capture). */
 int hub_query(const hub_ctx* ctx, int what, int64_t* value);
 
 /* Per-site data after hub_finalize_host: L = 2l+1, offset of its first

@@ -120,6 +120,7 @@ struct hub_ctx {
     bool bloch = false;
     double pass_rows = 1.0;                  // rows the grouped list's passes read over the covered points
     bool no_bloch = false;                   // the call in flight does without (scratch limit)
+    int64_t nbloch = 0;                      // projections and applies that took the list (hub_query 18)
     std::vector<int32_t> bl_pass_ptr;
     int64_t bl_part_rows = 0, bl_wlen = 0;
     int bl_rows_per_orbital = 0;
@@ -663,6 +664,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
             StageTimer tm(c, HUB_STAGE_PROJECT);
             HUB_TRY(launch_bloch_project(b, c->precision, c->stream));
         }
+        ++c->nbloch;
         ReduceGroupedArgs r{};
         r.part = part;
         r.prows = b.prows;
@@ -1062,6 +1064,7 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
             a.phase = c->d_bl_one;
             a.nimg = 1;
             HUB_TRY(launch_bloch_coef(a, nq, c->d_orb_site, B, c->stream));
+            ++c->nbloch;
             BlochArgs b = bloch_args(c, ld, ncol, q0, nq);
             b.split = bloch_split(c, ncol, 4);
             for (size_t p = 0; p + 1 < c->bl_pass_ptr.size(); ++p) {
@@ -1777,6 +1780,8 @@ int hub_query(const hub_ctx* c, int what, int64_t* v) {
     case 14: *v = T.grouped.ok ? T.grouped.npass : 0; break;
     case 15: *v = c->nalloc; break;
     case 16: *v = c->ncapture; break;
+    case 17: *v = c->bloch ? 1 : 0; break;
+    case 18: *v = c->nbloch; break;
     default: return HUB_EINVAL;
     }
     return HUB_OK;

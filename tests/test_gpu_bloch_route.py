@@ -1,0 +1,79 @@
+"""Which work list the calls take (hub_query 17: image-summed list built, 18:
+projections and applies that took it), so that tests of that list's results
+cannot pass on the grouped list's passes."""
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_1711_08935_amd as H  # noqa: E402
+from tests.test_gpu_bloch import SYSTEMS  # noqa: E402
+
+KPTS = [[0.1, -0.2, 0.3], [0.0, 0.25, -0.4]]
+
+
+def _context(name="two passes", spin="collinear", prec="f64", rc=1.0, **kw):
+    cell, ngrid, shells = SYSTEMS[name]
+    sites = [dict(R=R, l=l, zeta=1.3, rc=r * rc, species=i) for i, (R, l, r) in enumerate(shells)]
+    kw.setdefault("is_complex", True)
+    if kw["is_complex"]:
+        kw.update(kpts=np.array(KPTS), kweights=[0.4, 0.6])
+    hub = H.Hubbard(cell, ngrid, sites, spin=spin, precision=prec, **kw)
+    for i in range(hub.nsites):
+        hub.set_fixed_ueff(i, 0.3 - 0.2 * i)
+    return hub
+
+
+def _inputs(hub, states, seed=0):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    psi = torch.randn((hub.nsets, hub.G, hub.ncol(states)), generator=gen, device="cuda", dtype=hub.state_dtype)
+    f = torch.rand((hub.nsets, states), generator=gen, device="cuda", dtype=torch.float64)
+    return psi, f
+
+
+@pytest.mark.parametrize("name", list(SYSTEMS))
+def test_calls_take_the_list(name):
+    hub = _context(name)
+    assert hub.query(14) > 1 and hub.query(17) == 1
+    psi, f = _inputs(hub, 48)
+    bufs = hub.step_buffers(48)
+
+    def used(call):
+        before = hub.query(18)
+        call()
+        return hub.query(18) - before
+
+    def step(mode):
+        return lambda: hub.step(psi, f, torch.zeros_like(psi), mode=mode, bufs=bufs)
+
+    c, h = hub.project(psi), torch.zeros_like(psi)
+    n, _, _ = hub.occupations(c, f)
+    ueff = torch.full((hub.nsites,), 0.2, dtype=torch.float64, device="cuda")
+    calls = [lambda: hub.project(psi), lambda: hub.project(psi[1:2], sets=(1, 1)), lambda: hub.apply(ueff, n, c, h)]
+    assert [used(x) for x in calls] == [1, 1, 1]
+    assert used(step("batched")) == 2 and used(step("persite")) == 0
+    hp = torch.zeros_like(psi)
+    graph = lambda: hub.step(psi, f, hp, mode="graph", bufs=bufs)  # noqa: E731
+    assert [used(graph), used(graph)] == [2, 0]                    # captured, replayed
+    hub.set_vector_potential([0.1, 0.0, 0.0])
+    assert [used(x) for x in calls] == [0, 0, 0]
+    hub.set_vector_potential(None)
+    hub.set_worklist(False)
+    assert [used(x) for x in calls] == [0, 0, 0]
+    hub.set_worklist(True)
+    assert [used(x) for x in calls] == [1, 1, 1]
+    hub.close()
+
+
+def test_contexts_without_the_list():
+    for kw in (dict(rc=0.4), dict(spin="unpolarized", is_complex=False)):      # one pass; real states
+        hub = _context(**kw)
+        assert hub.query(17) == 0
+        hub.project(_inputs(hub, 48)[0])
+        assert hub.query(18) == 0
+        hub.close()
