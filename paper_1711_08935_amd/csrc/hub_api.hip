@@ -125,11 +125,10 @@ struct hub_ctx {
     int64_t bl_part_rows = 0, bl_wlen = 0;
     int bl_rows_per_orbital = 0;
     HubChunk* d_bl_chunks = nullptr;
-    int32_t *d_bl_gidx = nullptr, *d_bl_orb = nullptr, *d_bl_red_ptr = nullptr, *d_bl_red_row = nullptr;
+    int32_t *d_bl_gidx = nullptr, *d_bl_red_ptr = nullptr, *d_bl_red_row = nullptr;
+    HubFun* d_bl_fun = nullptr;              // [chunk][HUB_GF_MAX] functions
     int32_t* d_bl_img0 = nullptr;            // zeros: every row of the reduction has the phase 1
     double *d_bl_W = nullptr, *d_bl_one = nullptr;
-    double* d_bcoef = nullptr;               // coefficients B[q][j][col]
-    size_t bcoef_cap = 0;
     std::vector<char> have_tensor;
     size_t table_bytes = 0;
 
@@ -169,7 +168,6 @@ struct hub_ctx {
         double* occ;
         double* nbar;
         double* sink;
-        double* bcoef;
     };
     const FixedWs* ws_fixed = nullptr;
     int64_t nalloc = 0;                      // device allocations made so far (hub_query 15)
@@ -261,9 +259,8 @@ void release(hub_ctx* c) {
     f(c->d_st_chunks); f(c->d_st_all); f(c->d_st_gidx); f(c->d_st_site_ptr); f(c->d_st_site_ids); f(c->d_st_tab); f(c->d_st_tab_dn);
     f(c->d_gchunks); f(c->d_gall); f(c->d_gall_m); f(c->d_gmom); f(c->d_gmgidx); f(c->d_ggidx);
     f(c->d_gfun); f(c->d_gred_ptr); f(c->d_gred_row); f(c->d_gred_img); f(c->d_gtab); f(c->d_gspin_shift); f(c->d_gd0); f(c->d_gfdel);
-    f(c->d_bl_chunks); f(c->d_bl_gidx); f(c->d_bl_orb); f(c->d_bl_red_ptr); f(c->d_bl_red_row); f(c->d_bl_img0);
-    f(c->d_bl_W); f(c->d_bl_one); f(c->d_bcoef);
-    c->bcoef_cap = 0;
+    f(c->d_bl_chunks); f(c->d_bl_gidx); f(c->d_bl_fun); f(c->d_bl_red_ptr); f(c->d_bl_red_row); f(c->d_bl_img0);
+    f(c->d_bl_W); f(c->d_bl_one);
     c->bloch = false;
     drop_graph(c);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
@@ -451,9 +448,6 @@ bool use_bloch(const hub_ctx* c, int ncol) {
     const bool lines = static_cast<size_t>(ncol) * c->elem() % 128 == 0;
     return c->pass_rows * idle >= 1.1 * (1.0 + 0.35 * (pad - 1.0)) * (lines ? 1.0 : 1.05);
 }
-size_t bcoef_need(const hub_ctx* c, int ncol) {
-    return use_bloch(c, ncol) ? static_cast<size_t>(c->nsets()) * c->T.J * ncol * 2 : 0;
-}
 
 // Columns per lane so that a lane's FP64 accumulators (functions x scalars)
 // stay within 96 values (nf: the largest function count launched).
@@ -619,7 +613,7 @@ BlochArgs bloch_args(const hub_ctx* c, int64_t ld, int ncol, int q0, int nq) {
     b.J = c->T.J;
     b.chunks = c->d_bl_chunks;
     b.gidx = c->d_bl_gidx;
-    b.f_orb = c->d_bl_orb;
+    b.fun = c->d_bl_fun;
     b.W = c->d_bl_W;
     b.wlen = c->bl_wlen;
     return b;
@@ -1055,22 +1049,13 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
             return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, apply_waves(c), k, store, s);
         };
         if (!overwrite && use_bloch(c, ncol)) {
-            double* B = c->ws_fixed ? c->ws_fixed->bcoef : nullptr;
-            if (!B) {
-                const int st = ensure(&c->d_bcoef, &c->bcoef_cap, bcoef_need(c, ncol), c);
-                if (st) return st;
-                B = c->d_bcoef;
-            }
-            a.phase = c->d_bl_one;
-            a.nimg = 1;
-            HUB_TRY(launch_bloch_coef(a, nq, c->d_orb_site, B, c->stream));
             ++c->nbloch;
             BlochArgs b = bloch_args(c, ld, ncol, q0, nq);
             b.split = bloch_split(c, ncol, 4);
             for (size_t p = 0; p + 1 < c->bl_pass_ptr.size(); ++p) {
                 b.chunk0 = c->bl_pass_ptr[p];
                 b.nchunks = c->bl_pass_ptr[p + 1] - b.chunk0;
-                HUB_TRY(launch_bloch_apply(b, c->precision, B, hpsi, c->stream));
+                HUB_TRY(launch_bloch_apply(b, a, c->precision, c->stream));
             }
             return HUB_OK;
         }
@@ -1207,10 +1192,6 @@ int step_impl(hub_ctx* c, const hub_step_io* io, int mode, double* jcur) {
     }
     st = ensure(&c->d_part, &c->part_cap, part, c);
     if (st) return st;
-    if (use_bloch(c, ncol)) {
-        st = ensure(&c->d_bcoef, &c->bcoef_cap, bcoef_need(c, ncol), c);
-        if (st) return st;
-    }
     if (!io->nbar) {
         st = ensure(&c->d_nbar_ws, &c->nbar_cap, static_cast<size_t>(c->nsets()) * c->T.nspecies * io->nstates, c);
         if (st) return st;
@@ -1548,7 +1529,13 @@ hipError_t build_bloch(hub_ctx* c, size_t& bytes) {
     };
     up(&c->d_bl_chunks, B.chunks, bytes);
     up(&c->d_bl_gidx, B.gidx, bytes);
-    up(&c->d_bl_orb, B.f_orb, bytes);
+    std::vector<HubFun> fun(B.f_orb.size(), HubFun{});
+    for (size_t i = 0; i < fun.size(); ++i)
+        if (B.f_orb[i] >= 0) {
+            const int site = c->T.orb_site[B.f_orb[i]], o0 = c->T.site_orb0[site];
+            fun[i] = HubFun{site, o0, c->T.site_L[site], B.f_orb[i] - o0, 0, -1, {0, 0}};
+        }
+    up(&c->d_bl_fun, fun, bytes);
     up(&c->d_bl_red_ptr, B.red_ptr, bytes);
     up(&c->d_bl_red_row, B.red_row, bytes);
     up(&c->d_bl_img0, std::vector<int32_t>(B.red_row.size(), 0), bytes);
@@ -2126,7 +2113,7 @@ int hub_step_noalloc(hub_ctx* c, const hub_step_io* io) {
     // slices of the scratch array: projection partial sums, occupation
     // partial sums, N-bar (when the caller passes none), the apply's sink row
     const int ncol = c->ncol(io->nstates);
-    size_t n_part = 0, n_b = 0;
+    size_t n_part = 0;
     const size_t n_occ = slice256(occ_need(c, io->nstates));
     const size_t n_nbar = io->nbar ? 0 : slice256(static_cast<size_t>(c->nsets()) * c->T.nspecies * io->nstates);
     const size_t n_sink = slice256(static_cast<size_t>(io->ldh) * c->ncplx());
@@ -2134,16 +2121,14 @@ int hub_step_noalloc(hub_ctx* c, const hub_step_io* io) {
     for (int t = 0; t < 2; ++t) {
         c->no_bloch = t == 1;
         n_part = slice256(part_need(c, ncol, c->T.spindep ? 2 : 1));
-        n_b = slice256(bcoef_need(c, ncol));
-        if ((n_part + n_occ + n_nbar + n_sink + n_b) * sizeof(double) <= HUB_SCRATCH_BYTES) break;
+        if ((n_part + n_occ + n_nbar + n_sink) * sizeof(double) <= HUB_SCRATCH_BYTES) break;
         if (t == 1 || !use_bloch(c, ncol)) {
             c->no_bloch = false;
             return HUB_ESCRATCH;
         }
     }
     double* p = static_cast<double*>(base);
-    const hub_ctx::FixedWs ws{p, p + n_part, p + n_part + n_occ, p + n_part + n_occ + n_nbar,
-                              p + n_part + n_occ + n_nbar + n_sink};
+    const hub_ctx::FixedWs ws{p, p + n_part, p + n_part + n_occ, p + n_part + n_occ + n_nbar};
     c->ws_fixed = &ws;
     st = run_step(c, io, false);
     c->no_bloch = false;

@@ -20,7 +20,6 @@
 // (0.099), apply 0.43 (1.39).  It wins from two passes on: 31 functions in
 // FP64, 16 sets of 45 columns 0.37 and 0.52 ms (0.56 and 0.95).
 
-#include "k_apply.h"
 #include "kbloch.h"
 
 namespace {
@@ -48,22 +47,6 @@ __global__ void __launch_bounds__(256) k_bloch_table(const BlochTableArgs a) {
         W[static_cast<int64_t>(e) * 2 * half + f] = wr;
         W[static_cast<int64_t>(e) * 2 * half + half + f] = wi;
     }
-}
-
-// B[q][j][col] = alpha scale sum_b V_ab c_b of every orbital j, a lane per
-// column (a.phase: ones).
-template <bool SPINOR>
-__global__ void __launch_bounds__(64) k_bloch_coef(const ApplyArgs a, const int32_t* __restrict__ orb_site,
-                                                   double* __restrict__ B) {
-    const int col = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y, q = blockIdx.z;
-    if (col >= a.ncol) return;
-    const int site = orb_site[j], o0 = a.site_orb0[site];
-    const HubFun F{site, o0, a.site_L[site], j - o0, 0, -1, {0, 0}};
-    double b[2];
-    coefficient<true, SPINOR, 1>(a, F, q, col, b);
-    double* o = B + ((static_cast<int64_t>(q) * a.J + j) * a.ncol + col) * 2;
-    o[0] = b[0];
-    o[1] = b[1];
 }
 
 // 16-entry blocks [first, last) of part idx of the parts that share a chunk's
@@ -193,15 +176,99 @@ k_bloch_project(const BlochArgs a, const int32_t* __restrict__ gidx, const doubl
     else project_tile<T, 1, NJ>(a, C, q, c0, part_of, gidx, Wk, part);
 }
 
+// Coefficients of one work-group (one wave): z[f][i] = alpha scale sum_b V_ab c_b
+// of the chunk's function f (orbital a of its site) and column c0 + i, as
+// coefficient() of the grouped apply forms them.  The projections of the
+// chunk's orbitals and the rows of V of its functions are staged in LDS, every
+// load of the two in flight together, so that the wave waits twice (for the
+// functions' records and for these) however many functions it has.
+template <bool SPINOR, int NF, int NC>
+struct CoefLds {
+    static constexpr int NV = SPINOR ? 4 : 1;        // blocks of n that a site's columns use
+    hub_d2 c[NF][NC];                                // the projections, then the coefficients z
+    hub_d2 V[NV][NF][HUB_LMAX];
+};
+
+template <bool SPINOR, int NF, int NC>
+__device__ __forceinline__ void bloch_coefficients(const ApplyArgs& a, const HubFun* __restrict__ fun, int nf, int q,
+                                                   int c0, CoefLds<SPINOR, NF, NC>& lds) {
+    using Lds = CoefLds<SPINOR, NF, NC>;
+    constexpr int STEP = 64 / NC, NT = NF / STEP;                    // functions at once; per lane
+    constexpr int VT = (Lds::NV * NF * 8 + 63) / 64;                 // rows of V, eight slots a function
+    const int lane = threadIdx.x, i = lane % NC, h = lane / NC;
+    const int col = c0 + i, colc = col < a.ncol ? col : 0;
+    const double* __restrict__ cq = a.c + static_cast<int64_t>(q) * a.J * a.ncol * 2;
+    hub_d2 x[NT], v[VT];
+    double U[VT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int f = h + STEP * t;
+        const HubFun F = fun[f < nf ? f : 0];
+        x[t] = *reinterpret_cast<const hub_d2*>(cq + (static_cast<int64_t>(F.o0 + F.m) * a.ncol + colc) * 2);
+    }
+#pragma unroll
+    for (int t = 0; t < VT; ++t) {
+        const int o = lane + 64 * t, b = o & 7, f = (o >> 3) % NF, blk = (o >> 3) / NF;
+        const HubFun F = fun[f < nf ? f : 0];
+        const int ch = SPINOR ? blk : (a.q0 + q) % a.nspin;
+        v[t] = *reinterpret_cast<const hub_d2*>(
+            a.n + ((static_cast<int64_t>(F.site) * a.nblk + ch) * 49 + (b < F.L ? b : 0) * 7 + F.m) * 2);
+        U[t] = a.ueff[F.site];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) lds.c[h + STEP * t][i] = x[t];
+#pragma unroll
+    for (int t = 0; t < VT; ++t) {
+        // V_ab = U (delta_ab / 2 - n_ba); spinors: block 2 sigma' + sigma of n
+        // gives V^{sigma sigma'}
+        const int o = lane + 64 * t, b = o & 7, f = (o >> 3) % NF, blk = (o >> 3) / NF;
+        const HubFun F = fun[f < nf ? f : 0];
+        const bool diag = F.m == b && (!SPINOR || blk == 0 || blk == 3);
+        hub_d2 w;
+        w[0] = SPINOR ? U[t] * (diag ? 0.5 : 0.0) - U[t] * v[t][0] : U[t] * ((diag ? 0.5 : 0.0) - v[t][0]);
+        w[1] = -U[t] * v[t][1];
+        if (b < HUB_LMAX) lds.V[blk][f][b] = w;
+    }
+    __syncthreads();
+    double sc = a.alpha;
+    if (a.colscale != nullptr && col < a.ncol)
+        sc *= a.colscale[static_cast<int64_t>(q) * a.nstates + (SPINOR ? col >> 1 : col)];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int f = h + STEP * t;
+        const HubFun F = fun[f < nf ? f : 0];
+        const int f0 = f - F.m;                                      // the site's first function
+        double br = 0.0, bi = 0.0;
+#pragma unroll
+        for (int s = 0; s < (SPINOR ? 2 : 1); ++s) {
+            // spinor columns 2 s + sigma; tiles start at even columns
+            const int blk = SPINOR ? 2 * s + (i & 1) : 0, is = SPINOR ? (i & ~1) + s : i;
+#pragma unroll
+            for (int b = 0; b < HUB_LMAX; ++b) {
+                if (b >= F.L || f >= nf) break;
+                const hub_d2 w = lds.V[blk][f][b], y = lds.c[f0 + b][is];
+                br = fma(w[0], y[0], fma(-w[1], y[1], br));
+                bi = fma(w[0], y[1], fma(w[1], y[0], bi));
+            }
+        }
+        x[t] = hub_d2{br * sc, bi * sc};
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NT; ++t) lds.c[h + STEP * t][i] = x[t];
+    __syncthreads();
+}
+
 // The same tile in the apply: A[l % 16][.] = W of point l % 16 of a 16-point
 // block, the functions' parts split over the lane groups in the order of the
 // table row (lane group l / 16 takes RL / 4 consecutive values), B = the
 // coefficients in that order, the sum starts at hpsi.
-template <typename T, int MT, int NJ>
-__device__ __forceinline__ void apply_tile(const BlochArgs& a, const HubChunk& C, const int32_t* __restrict__ orb,
-                                           int q, int c0, int part_of, const int32_t* __restrict__ gidx,
-                                           const double* __restrict__ W, const double* __restrict__ Bc,
-                                           T* __restrict__ hpsi) {
+template <typename T, bool SPINOR, int MT, int NJ>
+__device__ __forceinline__ void apply_tile(const BlochArgs& a, const ApplyArgs& u, const HubChunk& C,
+                                           const HubFun* __restrict__ fun, int q, int c0, int first, int nb,
+                                           const int32_t* __restrict__ gidx, const double* __restrict__ W,
+                                           T* __restrict__ hpsi, CoefLds<SPINOR, 8 * MT, 16 * NJ>& lds) {
     constexpr int RL = 16 * MT, KB = RL / 4;
     const int lane = threadIdx.x, i16 = lane & 15, g4 = lane >> 4;
     T* __restrict__ h_q = hpsi + static_cast<int64_t>(q) * a.qstride;
@@ -214,18 +281,17 @@ __device__ __forceinline__ void apply_tile(const BlochArgs& a, const HubChunk& C
         ok[j] = col < a.ncol;
         cofs[j] = 2 * static_cast<int64_t>(ok[j] ? col : 0);
     }
+    bloch_coefficients<SPINOR, 8 * MT, 16 * NJ>(u, fun, C.L, q, c0, lds);
     // conj(W) B = (Wr Br + Wi Bi) + i (Wr Bi - Wi Br)
     double bf[KB][NJ][2];
     const bool imag = g4 >> 1;
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
         const int f = KB * (g4 & 1) + kb;
-        const int o = f < C.L ? orb[f] : -1;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const hub_d2 z = *reinterpret_cast<const hub_d2*>(
-                Bc + (static_cast<int64_t>(q) * a.J + (o < 0 ? 0 : o)) * a.ncol * 2 + cofs[j]);
-            const bool use = o >= 0 && ok[j];
+            const hub_d2 z = lds.c[f][16 * j + i16];
+            const bool use = f < C.L && ok[j];
             bf[kb][j][0] = use ? (imag ? z[1] : z[0]) : 0.0;
             bf[kb][j][1] = use ? (imag ? -z[0] : z[1]) : 0.0;
         }
@@ -280,9 +346,6 @@ __device__ __forceinline__ void apply_tile(const BlochArgs& a, const HubChunk& C
             }
         }
     };
-    int first, nb;
-    block_range(C.ne, a.split, part_of, first, nb);
-    if (first >= nb) return;
     Blk A, B;
     int ga[4], gb[4], gn[4];
     index(first, ga);
@@ -306,35 +369,36 @@ __device__ __forceinline__ void apply_tile(const BlochArgs& a, const HubChunk& C
     }
 }
 
-template <typename T, int NJ>
+template <typename T, bool SPINOR, int NJ>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
-k_bloch_apply(const BlochArgs a, const int32_t* __restrict__ gidx, const double* __restrict__ W,
-              const double* __restrict__ Bc, T* __restrict__ hpsi) {
+k_bloch_apply(const BlochArgs a, const ApplyArgs u, const int32_t* __restrict__ gidx, const double* __restrict__ W,
+              T* __restrict__ hpsi) {
+    __shared__ union Lds {
+        CoefLds<SPINOR, 16, 16 * NJ> wide;
+        CoefLds<SPINOR, 8, 16 * NJ> narrow;
+        __device__ Lds() {}
+    } lds;
     const HubSlot slot = hub_slot(a.tiles);
     if (slot.chunk >= a.nchunks) return;
     const int ci = a.chunk0 + slot.chunk;
     const HubChunk C = a.chunks[ci];
     const int tps = (a.ncol + 16 * NJ - 1) / (16 * NJ);
     const int tile = slot.tile / a.split, part_of = slot.tile - tile * a.split;
+    int first, nb;
+    block_range(C.ne, a.split, part_of, first, nb);
+    if (first >= nb) return;
     const int q = tile / tps, c0 = (tile - q * tps) * (16 * NJ);
     const int k = a.spinor ? a.q0 + q : (a.q0 + q) / a.nspin;
     const double* __restrict__ Wk = W + k * a.wlen;
-    const int32_t* __restrict__ orb = a.f_orb + ci * HUB_GF_MAX;
-    if (C.L > 8) apply_tile<T, 2, NJ>(a, C, orb, q, c0, part_of, gidx, Wk, Bc, hpsi);
-    else apply_tile<T, 1, NJ>(a, C, orb, q, c0, part_of, gidx, Wk, Bc, hpsi);
+    const HubFun* __restrict__ fun = a.fun + ci * HUB_GF_MAX;
+    if (C.L > 8) apply_tile<T, SPINOR, 2, NJ>(a, u, C, fun, q, c0, first, nb, gidx, Wk, hpsi, lds.wide);
+    else apply_tile<T, SPINOR, 1, NJ>(a, u, C, fun, q, c0, first, nb, gidx, Wk, hpsi, lds.narrow);
 }
 
 }  // namespace
 
 hipError_t launch_bloch_table(const BlochTableArgs& a, int nchunks, int nk, hipStream_t st) {
     hipLaunchKernelGGL(k_bloch_table, dim3(nchunks, nk), dim3(256), 0, st, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_bloch_coef(const ApplyArgs& a, int nq, const int32_t* orb_site, double* B, hipStream_t st) {
-    const dim3 grid((a.ncol + 63) / 64, a.J, nq);
-    if (a.spinor) hipLaunchKernelGGL(k_bloch_coef<true>, grid, dim3(64), 0, st, a, orb_site, B);
-    else hipLaunchKernelGGL(k_bloch_coef<false>, grid, dim3(64), 0, st, a, orb_site, B);
     return hipGetLastError();
 }
 
@@ -353,13 +417,18 @@ hipError_t project_t(const BlochArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <typename T, int NJ>
-hipError_t apply_t(const BlochArgs& a, const double* B, void* hpsi, hipStream_t st) {
+template <typename T, bool SPINOR, int NJ>
+hipError_t apply_t(const BlochArgs& a, const ApplyArgs& u, hipStream_t st) {
     BlochArgs b = a;
     b.tiles = a.nq * ((a.ncol + 16 * NJ - 1) / (16 * NJ)) * a.split;
-    hipLaunchKernelGGL((k_bloch_apply<T, NJ>), dim3(static_cast<unsigned>(hub_slot_grid(a.nchunks, b.tiles))), dim3(64), 0,
-                       st, b, b.gidx, b.W, B, static_cast<T*>(hpsi));
+    hipLaunchKernelGGL((k_bloch_apply<T, SPINOR, NJ>), dim3(static_cast<unsigned>(hub_slot_grid(a.nchunks, b.tiles))),
+                       dim3(64), 0, st, b, u, b.gidx, b.W, static_cast<T*>(u.hpsi));
     return hipGetLastError();
+}
+
+template <typename T, int NJ>
+hipError_t apply_s(const BlochArgs& a, const ApplyArgs& u, hipStream_t st) {
+    return a.spinor ? apply_t<T, true, NJ>(a, u, st) : apply_t<T, false, NJ>(a, u, st);
 }
 
 }  // namespace
@@ -369,7 +438,7 @@ hipError_t launch_bloch_project(const BlochArgs& a, int prec, hipStream_t st) {
     return prec == HUB_F64 ? project_t<double, 1>(a, st) : project_t<float, 1>(a, st);
 }
 
-hipError_t launch_bloch_apply(const BlochArgs& a, int prec, const double* B, void* hpsi, hipStream_t st) {
-    if (bloch_nj(a.ncol) == 2) return prec == HUB_F64 ? apply_t<double, 2>(a, B, hpsi, st) : apply_t<float, 2>(a, B, hpsi, st);
-    return prec == HUB_F64 ? apply_t<double, 1>(a, B, hpsi, st) : apply_t<float, 1>(a, B, hpsi, st);
+hipError_t launch_bloch_apply(const BlochArgs& a, const ApplyArgs& u, int prec, hipStream_t st) {
+    if (bloch_nj(a.ncol) == 2) return prec == HUB_F64 ? apply_s<double, 2>(a, u, st) : apply_s<float, 2>(a, u, st);
+    return prec == HUB_F64 ? apply_s<double, 1>(a, u, st) : apply_s<float, 1>(a, u, st);
 }

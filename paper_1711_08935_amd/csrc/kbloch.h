@@ -23,7 +23,7 @@ struct BlochArgs {
     int tiles;                               // (set, columns) tiles times split (set by the launcher)
     int split;                               // work-groups that share a chunk's entries in one tile
     const int32_t* gidx;
-    const int32_t* f_orb;                    // [chunk][HUB_GF_MAX]
+    const HubFun* fun;                       // [chunk][HUB_GF_MAX] functions (image unused)
     const double* W;
     int64_t wlen;
     double* part;                            // projection: [nq][prows][ncol] complex, row r split + s
@@ -33,7 +33,7 @@ struct BlochArgs {
 // 16-column blocks per wave (1 or 2) for ncol columns.
 int bloch_nj(int ncol);
 hipError_t launch_bloch_table(const BlochTableArgs& a, int nchunks, int nk, hipStream_t st);
-// B[q][j][col] of nq sets; a.phase, a.nimg: ones for every k-point.
-hipError_t launch_bloch_coef(const ApplyArgs& a, int nq, const int32_t* orb_site, double* B, hipStream_t st);
 hipError_t launch_bloch_project(const BlochArgs& a, int prec, hipStream_t st);
-hipError_t launch_bloch_apply(const BlochArgs& a, int prec, const double* B, void* hpsi, hipStream_t st);
+// u: the states, projections, occupations and scales of the apply (the chunk
+// fields, phases and sink are not used).
+hipError_t launch_bloch_apply(const BlochArgs& a, const ApplyArgs& u, int prec, hipStream_t st);

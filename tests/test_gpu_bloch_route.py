@@ -1,6 +1,7 @@
 """Which work list the calls take (hub_query 17: image-summed list built, 18:
 projections and applies that took it), so that tests of that list's results
-cannot pass on the grouped list's passes."""
+cannot pass on the grouped list's passes; and that an apply over it uses
+nothing that a second apply on another stream would overwrite."""
 
 import numpy as np
 import pytest
@@ -77,3 +78,36 @@ def test_contexts_without_the_list():
         hub.project(_inputs(hub, 48)[0])
         assert hub.query(18) == 0
         hub.close()
+
+
+@pytest.mark.parametrize("spin,states", [("collinear", 64), ("collinear", 13), ("spinor", 24)])
+def test_apply_keeps_no_workspace(spin, states):
+    hub = _context(spin=spin)
+    psi, f = _inputs(hub, states)
+    c = hub.project(psi)
+    n, _, _ = hub.occupations(c, f)
+    ueff = [torch.full((hub.nsites,), u, dtype=torch.float64, device="cuda") for u in (0.3, -0.4)]
+    # a field's apply allocates the row that padding entries write, all that an apply needs
+    hub.set_vector_potential([0.0, 0.0, 0.0])
+    hub.apply(ueff[0], n, c, torch.zeros_like(psi))
+    hub.set_vector_potential(None)
+    allocations, taken = hub.query(15), hub.query(18)
+    ref = [torch.zeros_like(psi) for _ in ueff]
+    for u, h in zip(ueff, ref):
+        hub.apply(u, n, c, h)
+    assert hub.query(15) == allocations and hub.query(18) == taken + 2
+    # two potentials on all sets, and two halves of the sets, on two streams at once
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    half = [c[:1].contiguous(), c[1:].contiguous()]
+    for _ in range(10):
+        h = [torch.zeros_like(psi) for _ in ueff]
+        g = torch.zeros_like(psi)
+        torch.cuda.synchronize()
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                hub.apply(ueff[i], n, c, h[i])
+                hub.apply(ueff[0], n, half[i], g[:1] if i == 0 else g[1:], sets=(i, 1 if i == 0 else hub.nsets - 1))
+        torch.cuda.synchronize()
+        assert torch.equal(h[0], ref[0]) and torch.equal(h[1], ref[1]) and torch.equal(g, ref[0])
+    hub.close()
