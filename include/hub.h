@@ -28,7 +28,8 @@
  *    environment when hub_create runs, that context's N-th device
  *    allocation attempt fails once, as if the GPU were out of memory; the
  *    call returns HUB_ENOMEM, frees what it had allocated, and may be
- *    repeated.
+ *    repeated (in the tables of the image-summed list, which a context can do
+ *    without, hub_finalize succeeds and the context has no such list).
  *
  * State layouts (T = double for HUB_F64, float for HUB_F32; complex states
  * store (re, im) pairs of T):
@@ -171,9 +172,11 @@ int hub_set_tuning(hub_ctx* ctx, int which, int cols_per_lane, int waves, int la
  * grouped list (at most 16 functions each; the apply launches the passes in
  * turn, hub_query 14); for complex states without a field or spin-dependent
  * orbitals, the projection and the apply then use, where it is faster, a
- * list with each point's covers summed over the images of a site, whose tables (at most
- * 4 GiB, and half of the free device memory) hub_finalize makes.  All give the same results up to summation
- * order.
+ * list with each point's covers summed over the images of a site.
+ * hub_finalize makes its tables where they take at most 4 GiB and, while they
+ * are made, half of the free device memory; where they do not fit, or an
+ * allocation for them fails, the passes serve every call (hub_query 17 and 18
+ * tell).  All give the same results up to summation order.
  * Any time. */
 int hub_set_worklist(hub_ctx* ctx, int grouped_list);
 

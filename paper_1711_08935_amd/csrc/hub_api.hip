@@ -241,6 +241,7 @@ hipError_t upload(hub_ctx* c, T** dst, const std::vector<T>& src, size_t& bytes)
 }
 
 void drop_graph(hub_ctx* c);
+void drop_bloch(hub_ctx* c);
 
 // Frees every device table and workspace and leaves the pointers null (so a
 // failed hub_finalize can be retried and hub_destroy frees nothing twice).
@@ -259,9 +260,7 @@ void release(hub_ctx* c) {
     f(c->d_st_chunks); f(c->d_st_all); f(c->d_st_gidx); f(c->d_st_site_ptr); f(c->d_st_site_ids); f(c->d_st_tab); f(c->d_st_tab_dn);
     f(c->d_gchunks); f(c->d_gall); f(c->d_gall_m); f(c->d_gmom); f(c->d_gmgidx); f(c->d_ggidx);
     f(c->d_gfun); f(c->d_gred_ptr); f(c->d_gred_row); f(c->d_gred_img); f(c->d_gtab); f(c->d_gspin_shift); f(c->d_gd0); f(c->d_gfdel);
-    f(c->d_bl_chunks); f(c->d_bl_gidx); f(c->d_bl_fun); f(c->d_bl_red_ptr); f(c->d_bl_red_row); f(c->d_bl_img0);
-    f(c->d_bl_W); f(c->d_bl_one);
-    c->bloch = false;
+    drop_bloch(c);
     drop_graph(c);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     for (int k = 0; k < HUB_NCLASS; ++k) {
@@ -1512,43 +1511,63 @@ int hub_finalize_host(hub_ctx* c) {
 namespace {
 int gauge_tables(hub_ctx* c);
 
+void drop_bloch(hub_ctx* c) {
+    auto f = [](auto*& p) {
+        if (p) (void)hipFree(p);
+        p = nullptr;
+    };
+    f(c->d_bl_chunks); f(c->d_bl_gidx); f(c->d_bl_fun); f(c->d_bl_red_ptr); f(c->d_bl_red_row); f(c->d_bl_img0);
+    f(c->d_bl_W); f(c->d_bl_one);
+    c->bloch = false;
+}
+
 // Bloch-summed work list and its tables for every k-point, from the plain
-// phases on the device; contexts whose tables would pass kBlochBytes, or half
-// of the device memory that is free, keep the grouped list's passes.
-constexpr size_t kBlochBytes = size_t(4) << 30;
-hipError_t build_bloch(hub_ctx* c, size_t& bytes) {
+// phases on the device.  The list is an option: contexts whose tables would
+// pass kBlochBytes or, with the covers that they are made from, half of the
+// device memory that is free, and contexts for which memory runs out here, keep
+// the grouped list's passes.
+constexpr int64_t kBlochBytes = int64_t(4) << 30;
+hipError_t build_bloch(hub_ctx* c, size_t& table_bytes) {
     BlochTables B;
-    hub_build_bloch(c->T, c->G(), c->chunk_entries, B);
+    std::vector<HubFun> fun;
+    std::vector<int32_t> img0;
+    std::vector<double> one;
+    try {
+        if (!hub_build_bloch(c->T, c->G(), c->chunk_entries, B, c->nk, kBlochBytes)) return hipSuccess;
+        fun.resize(B.f_orb.size(), HubFun{});
+        for (size_t i = 0; i < fun.size(); ++i)
+            if (B.f_orb[i] >= 0) {
+                const int site = c->T.orb_site[B.f_orb[i]], o0 = c->T.site_orb0[site];
+                fun[i] = HubFun{site, o0, c->T.site_L[site], B.f_orb[i] - o0, 0, -1, {0, 0}};
+            }
+        img0.assign(B.red_row.size(), 0);
+        one.assign(2 * c->nk, 0.0);
+        for (int k = 0; k < c->nk; ++k) one[2 * k] = 1.0;
+    } catch (...) {                                  // host memory
+        return hipSuccess;
+    }
     const size_t wbytes = static_cast<size_t>(B.wlen) * c->nk * sizeof(double);
-    if (wbytes > kBlochBytes || B.gidx.size() > INT32_MAX || B.part_rows > INT32_MAX) return hipSuccess;
+    const size_t covers = (B.cptr.size() + B.cimg.size() + B.cfun.size()) * sizeof(int32_t) +
+                          B.coff.size() * sizeof(int64_t) + B.cval.size() * sizeof(double);
     size_t avail = 0, total = 0;
-    if (hipMemGetInfo(&avail, &total) != hipSuccess || wbytes > avail / 2) return hipSuccess;
+    if (hipMemGetInfo(&avail, &total) != hipSuccess || wbytes + covers > avail / 2) return hipSuccess;
     hipError_t e = hipSuccess;
+    size_t bytes = wbytes, tmp = 0;
     auto up = [&](auto** dst, const auto& src, size_t& n) {
         if (e == hipSuccess) e = upload(c, dst, src, n);
     };
     up(&c->d_bl_chunks, B.chunks, bytes);
     up(&c->d_bl_gidx, B.gidx, bytes);
-    std::vector<HubFun> fun(B.f_orb.size(), HubFun{});
-    for (size_t i = 0; i < fun.size(); ++i)
-        if (B.f_orb[i] >= 0) {
-            const int site = c->T.orb_site[B.f_orb[i]], o0 = c->T.site_orb0[site];
-            fun[i] = HubFun{site, o0, c->T.site_L[site], B.f_orb[i] - o0, 0, -1, {0, 0}};
-        }
     up(&c->d_bl_fun, fun, bytes);
     up(&c->d_bl_red_ptr, B.red_ptr, bytes);
     up(&c->d_bl_red_row, B.red_row, bytes);
-    up(&c->d_bl_img0, std::vector<int32_t>(B.red_row.size(), 0), bytes);
-    std::vector<double> one(2 * c->nk, 0.0);
-    for (int k = 0; k < c->nk; ++k) one[2 * k] = 1.0;
+    up(&c->d_bl_img0, img0, bytes);
     up(&c->d_bl_one, one, bytes);
     if (e == hipSuccess) e = dev_malloc(c, &c->d_bl_W, wbytes);
-    bytes += wbytes;
     BlochTableArgs a{};
     int32_t *cptr = nullptr, *cimg = nullptr, *cfun = nullptr;
     int64_t* coff = nullptr;
     double* cval = nullptr;
-    size_t tmp = 0;
     up(&cptr, B.cptr, tmp);
     up(&cimg, B.cimg, tmp);
     up(&cfun, B.cfun, tmp);
@@ -1572,8 +1591,14 @@ hipError_t build_bloch(hub_ctx* c, size_t& bytes) {
     for (void* p : {static_cast<void*>(cptr), static_cast<void*>(cimg), static_cast<void*>(cfun),
                     static_cast<void*>(coff), static_cast<void*>(cval)})
         if (p) (void)hipFree(p);
-    if (e != hipSuccess) return e;
-    c->bl_pass_ptr = B.pass_ptr;
+    if (e != hipSuccess) {
+        drop_bloch(c);
+        if (e != hipErrorOutOfMemory) return e;
+        (void)hipGetLastError();                     // it would show at the next launch
+        return hipSuccess;
+    }
+    table_bytes += bytes;
+    c->bl_pass_ptr.swap(B.pass_ptr);
     c->bl_part_rows = B.part_rows;
     c->bl_wlen = B.wlen;
     c->bl_rows_per_orbital = B.red_ptr.back() / std::max(1, c->T.J);
@@ -1711,14 +1736,7 @@ int hub_finalize(hub_ctx* c, void* stream) {
             up(&c->d_gspin_shift, shift);
         }
     }
-    if (e == hipSuccess && T.grouped.ok && T.grouped.npass > 1 && c->is_complex && !T.spindep) {
-        try {
-            e = build_bloch(c, b);
-        } catch (...) {                              // host tables: out of memory
-            release(c);
-            return HUB_ENOMEM;
-        }
-    }
+    if (e == hipSuccess && T.grouped.ok && T.grouped.npass > 1 && c->is_complex && !T.spindep) e = build_bloch(c, b);
     if (e == hipSuccess) {
         e = dev_malloc(c, &c->d_tensor, c->sites.size() * 2401 * sizeof(double));
         b += c->sites.size() * 2401 * sizeof(double);

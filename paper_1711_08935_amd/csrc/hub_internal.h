@@ -208,7 +208,11 @@ struct BlochTables {
 };
 // doubles per entry: the real, then the imaginary parts of 8 or 16 functions
 inline int hub_bloch_row(int nf) { return nf > 8 ? 32 : 16; }
-void hub_build_bloch(const HostTables& T, int64_t G, int chunk_entries, BlochTables& out);
+// False, and out empty, where the tables of nk k-points would take more than
+// wlimit bytes or an index would pass 32 bits; counted before the tables of the
+// entries are filled.
+bool hub_build_bloch(const HostTables& T, int64_t G, int chunk_entries, BlochTables& out, int nk = 1,
+                     int64_t wlimit = INT64_MAX);
 
 // Plan for the sites which[0..] of the context (sphere.cpp).
 void hub_coulomb_plan(const HostTables& T, const std::vector<int>& which, CoulombPlan& out);

@@ -612,8 +612,12 @@ int hub_build_host(const double cell[3], const int ngrid[3], const std::vector<S
     return HUB_OK;
 }
 
-void hub_build_bloch(const HostTables& T, int64_t G, int chunk_entries, BlochTables& out) {
+bool hub_build_bloch(const HostTables& T, int64_t G, int chunk_entries, BlochTables& out, int nk, int64_t wlimit) {
     out = BlochTables();
+    int64_t covers = 0;
+    for (const SiteSphere& sp : T.spheres) covers += static_cast<int64_t>(sp.g.size());
+    if (covers > INT32_MAX) return false;
+    const int64_t per_double = static_cast<int64_t>(nk) * static_cast<int64_t>(sizeof(double));
     // image id by triple
     int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
     const int nimg = static_cast<int>(T.images.size() / 3);
@@ -632,7 +636,12 @@ void hub_build_bloch(const HostTables& T, int64_t G, int chunk_entries, BlochTab
     std::vector<int32_t> ptr(static_cast<size_t>(G) + 1, 0);
     for (const SiteSphere& sp : T.spheres)
         for (int32_t g : sp.g) ++ptr[g + 1];
-    for (int64_t g = 0; g < G; ++g) ptr[g + 1] += ptr[g];
+    int64_t covered = 0;
+    for (int64_t g = 0; g < G; ++g) {
+        covered += ptr[g + 1] > 0;
+        ptr[g + 1] += ptr[g];
+    }
+    if (covered * hub_bloch_row(1) > wlimit / per_double) return false;      // the least they take
     struct Cover {
         int32_t site, p;
     };
@@ -668,20 +677,37 @@ void hub_build_bloch(const HostTables& T, int64_t G, int chunk_entries, BlochTab
         if (!sites.empty()) groups[{pass, sites}].push_back({static_cast<int32_t>(g), c0, ptr[g + 1]});
         npass = std::max(npass, pass + 1);
     }
+    auto functions = [&](const std::vector<int>& sg) {
+        int nf = 0;
+        for (int s : sg) nf += T.site_L[s];
+        return nf;
+    };
+    auto chunk_of = [&](int nf) {
+        return static_cast<size_t>(std::max(64, hub_bloch_row(nf) == 32 ? chunk_entries / 2 : chunk_entries));
+    };
+    auto padded = [](size_t n) { return (n + HUB_ENTRY_ALIGN - 1) / HUB_ENTRY_ALIGN * HUB_ENTRY_ALIGN; };
+    int64_t entries = 0, rows = 0, wlen = 0;
+    for (const auto& kv : groups) {
+        const int nf = functions(kv.first.second);
+        const size_t n = kv.second.size(), chunk = chunk_of(nf);
+        const int64_t ne = static_cast<int64_t>(n / chunk * padded(chunk) + padded(n % chunk));
+        entries += ne;
+        rows += static_cast<int64_t>((n + chunk - 1) / chunk) * nf;
+        wlen += ne * hub_bloch_row(nf);
+    }
+    if (entries > INT32_MAX || rows > INT32_MAX || wlen > wlimit / per_double) return false;
     out.pass_ptr.assign(npass + 1, 0);
     out.cptr.push_back(0);
     std::vector<std::vector<int32_t>> red(T.J);
     for (const auto& kv : groups) {                                // pass by pass: the map's order
         const int pass = kv.first.first;
         const std::vector<int>& sg = kv.first.second;
-        int nf = 0;
-        for (int s : sg) nf += T.site_L[s];
-        const int row = hub_bloch_row(nf);
-        const size_t chunk = static_cast<size_t>(std::max(64, row == 32 ? chunk_entries / 2 : chunk_entries));
+        const int nf = functions(sg), row = hub_bloch_row(nf);
+        const size_t chunk = chunk_of(nf);
         const std::vector<Point>& pts = kv.second;
         for (size_t b = 0; b < pts.size(); b += chunk) {
             const size_t nb = std::min(pts.size() - b, chunk);
-            const size_t np = (nb + HUB_ENTRY_ALIGN - 1) / HUB_ENTRY_ALIGN * HUB_ENTRY_ALIGN;
+            const size_t np = padded(nb);
             HubChunk C{};
             C.site = sg[0];
             C.layer = pass;
@@ -728,6 +754,7 @@ void hub_build_bloch(const HostTables& T, int64_t G, int chunk_entries, BlochTab
         out.red_row.insert(out.red_row.end(), r.begin(), r.end());
         out.red_ptr.push_back(static_cast<int32_t>(out.red_row.size()));
     }
+    return true;
 }
 
 void hub_coulomb_plan(const HostTables& T, const std::vector<int>& which, CoulombPlan& out) {

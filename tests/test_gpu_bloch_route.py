@@ -111,3 +111,41 @@ def test_apply_keeps_no_workspace(spin, states):
         torch.cuda.synchronize()
         assert torch.equal(h[0], ref[0]) and torch.equal(h[1], ref[1]) and torch.equal(g, ref[0])
     hub.close()
+
+
+def test_finalize_does_without_the_list_when_memory_runs_out(monkeypatch):
+    """Every allocation of hub_finalize fails once: either the call reports
+    it and succeeds when repeated, or it was one of the list's and the context
+    runs the passes."""
+    ref = _context()
+    psi, f = _inputs(ref, 40)
+    taken = ref.step(psi, f, torch.zeros_like(psi), mode="batched")["c"]
+    ref.set_vector_potential([0.0, 0.0, 0.0])
+    passes = ref.step(psi, f, torch.zeros_like(psi), mode="batched")["c"]
+    hub = _context()
+    total, bytes_with = hub.query(15), hub.query(9)
+    hub.close()
+    without = []
+    for i in range(1, total + 1):
+        print(f"[fail-alloc] attempt {i} of {total}", flush=True)
+        monkeypatch.setenv("HUB_FAIL_ALLOC", str(i))
+        hub = _context(finalize=False)
+        monkeypatch.delenv("HUB_FAIL_ALLOC")
+        try:
+            hub.finalize()
+            # not met: only the list's own failures are passed over
+            assert hub.query(17) == 0
+            without.append(hub.query(9))
+        except H.HubError as e:
+            assert e.code == H.HUB_ENOMEM
+            hub.finalize()
+            assert hub.query(17) == 1 and hub.query(9) == bytes_with
+        used = hub.query(18)
+        c = hub.step(psi, f, torch.zeros_like(psi), mode="batched")["c"]
+        assert hub.query(18) - used == (2 if hub.query(17) else 0)
+        # the sums of a vanishing field's passes, whose phases are formed on the GPU
+        assert (torch.equal(c, taken) if hub.query(17) else (c - passes).abs().max() < 1e-12 * passes.abs().max())
+        hub.close()
+    # its lists, tables and the covers that these are made from; all released
+    assert len(without) == 13 and len(set(without)) == 1 and without[0] < bytes_with
+    ref.close()
