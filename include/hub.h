@@ -171,7 +171,7 @@ int hub_set_tuning(hub_ctx* ctx, int which, int cols_per_lane, int waves, int la
  * orbitals in total has its covers split over several passes of the
  * grouped list (at most 16 functions each; the apply launches the passes in
  * turn, hub_query 14); for complex states without a field or spin-dependent
- * orbitals, the projection and the apply then use, where it is faster, a
+ * orbitals, the projection and the apply then use, where by its size it is faster, a
  * list with each point's covers summed over the images of a site.
  * hub_finalize makes its tables where they take at most 4 GiB and, while they
  * are made, half of the free device memory; where they do not fit, or an

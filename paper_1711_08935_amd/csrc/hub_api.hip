@@ -118,7 +118,7 @@ struct hub_ctx {
                                                    // at the first hub_step_current
     // Bloch-summed work list (k_bloch.hip), where the grouped list needs passes
     bool bloch = false;
-    double pass_rows = 1.0;                  // rows the grouped list's passes read over the covered points
+    double g_rows = 0.0, bl_entries = 0.0;   // rows of one state set that the grouped list's passes and it read
     bool no_bloch = false;                   // the call in flight does without (scratch limit)
     int64_t nbloch = 0;                      // projections and applies that took the list (hub_query 18)
     std::vector<int32_t> bl_pass_ptr;
@@ -425,27 +425,58 @@ bool built(const hub_ctx* c) { return c && c->built_dev; }
 // Batched launches use the grouped work list when it exists.
 bool grouped(const hub_ctx* c) { return c->use_grouped && c->T.grouped.ok; }
 
-// The Bloch-summed list takes the place of the grouped list's passes (without
-// a field, which changes the phases at every step):
-// * for launches that do not fill the chip, which save the passes' launches
-//   (2 sets of 20 FP64 columns 68 us, 95 in passes), and for up to 32 columns,
-//   one wave's tile (16 sets of 17 FP64 columns 222 and 297 us);
-// * else where the passes read enough rows again.  Its tiles take 16 columns,
-//   rows that do not start on 128 bytes make it read lines twice, and the
-//   passes' waves idle past the last of 64 columns: these weigh in.  A 48^3
-//   rocksalt cell, 16 sets of 64 FP32 columns, rows in passes over rows 1.01,
-//   1.06, 1.15 and 1.40: this list 720, 734, 756 and 769 us, passes 666, 705,
-//   775 and 925; 33 FP64 columns at 1.06: 946 and 800; 45 FP32 columns at
-//   1.15: 801 and 676; 90 FP64 columns on 52^3 at 1.06: 2517 and 2692; 50
-//   FP64 columns on 44^3 at 1.06 and 1.28: 1032 and 889, 1051 and 1076.
-bool use_bloch(const hub_ctx* c, int ncol) {
-    if (!c->bloch || c->no_bloch || !grouped(c) || c->gauge) return false;
-    if (ncol <= 32 || proj_groups(c, static_cast<int>(c->T.grouped.chunks.size()), ncol, 1, 0) < kFullLaunch)
-        return true;
-    const double pad = (ncol + 15) / 16 * 16.0 / ncol;
-    const double idle = ncol < HUB_WAVE ? 1.0 : (ncol + 63) / 64 * 64.0 / ncol;
-    const bool lines = static_cast<size_t>(ncol) * c->elem() % 128 == 0;
-    return c->pass_rows * idle >= 1.1 * (1.0 + 0.35 * (pad - 1.0)) * (lines ? 1.0 : 1.05);
+// Whether the Bloch-summed list may take the place of the grouped list's
+// passes (a field changes its phases at every step).
+bool have_bloch(const hub_ctx* c) { return c->bloch && !c->no_bloch && grouped(c) && !c->gauge; }
+
+// 128-byte lines of a row that tiles of w columns touch, on average over rows
+// ld columns apart.
+double row_lines(const hub_ctx* c, int64_t ld, int ncol, int w) {
+    const double el = static_cast<double>(c->elem());
+    const double align = static_cast<double>(std::gcd<int64_t, int64_t>(ld * static_cast<int64_t>(c->elem()), 128));
+    double n = 0.0;
+    for (int t = 0; t < ncol; t += w) {
+        const double bytes = std::min(w, ncol - t) * el;
+        n += align == 128.0 ? std::ceil(bytes / 128.0) : (bytes + 128.0 - align) / 128.0;
+    }
+    return n;
+}
+
+// Which of the two a projection (which = 0) or an apply (1) takes: the one
+// whose estimated time is less, for the whole context (a range of sets takes
+// its route).  In microseconds, with what each moves and does:
+// * the passes read every row once per pass (and the apply writes it): row
+//   lines at 5 TB/s, beside a cost per wave, per row and wave in the apply
+//   (one state set per wave, so narrow sets leave lanes idle) and, in the
+//   projection, of the reduction;
+// * the Bloch-summed list reads every row once (the apply writes it, in tiles
+//   of 16 or 32 columns) and, in the projection, the k-point's table for every
+//   tile, at 30 TB/s from the caches; its products take whole 16-column tiles at
+//   71 TF/s.
+// The factors are fitted to 400 timings of each call: rocksalt cells of 24^3 to
+// 48^3 points, 1 to 125 k-points, rows in passes over rows 1.01 to 3.5, 1 to
+// 128 columns in both precisions.  The chosen route is 0.8 % (projection) and
+// 0.2 % (apply) above the faster one on average, 24 % and 20 % at most.  Passes
+// and this list for projections of 8 FP32 columns: 48^3 points and 16 sets at
+// 1.06 52 and 80 us, at 3.5 181 and 87; 24^3 points and 128 sets at 1.17 143 and
+// 93.  The applies there: 208 and 107, 743 and 115, 334 and 122.  33 columns on
+// 44^3 points at 1.06: 126 and 193, 242 and 281.
+bool use_bloch(const hub_ctx* c, int which, int64_t ld, int ncol) {
+    if (!have_bloch(c)) return false;
+    const double us = 128.0 / 5e6;                           // a line
+    const double sets = c->nsets(), nch = static_cast<double>(c->T.grouped.chunks.size());
+    const double tiles = (ncol + HUB_WAVE - 1) / HUB_WAVE;
+    const int w = 16 * bloch_nj(ncol);
+    const double rows = us * c->g_rows * sets, entries = us * c->bl_entries * sets;
+    const double wide = row_lines(c, ld, ncol, HUB_WAVE), table = sets * static_cast<double>(c->bl_wlen);
+    const double products = (ncol + 15) / 16 * 16 * table * 4.0 / 71e6;
+    if (which == 0) {
+        const double passes = 16.0 + 0.87 * rows * wide + 0.0044 * nch * std::ceil(sets * ncol / HUB_WAVE) +
+                              0.013 * c->T.J * sets * tiles;
+        return 14.5 + 0.58 * entries * wide + 0.83 * products + 1.1 * ((ncol + w - 1) / w) * table * 8.0 / 30e6 < passes;
+    }
+    const double passes = 17.0 + 1.25 * rows * wide + 0.0175 * nch * sets * tiles + 6e-6 * c->g_rows * sets * tiles;
+    return 7.1 + entries * (0.07 * wide + 0.99 * row_lines(c, ld, ncol, w)) + 1.38 * products < passes;
 }
 
 // Columns per lane so that a lane's FP64 accumulators (functions x scalars)
@@ -589,7 +620,7 @@ size_t part_need(const hub_ctx* c, int ncol, int mult) {
     if (c->T.grouped.ok)
         rows = std::max<int64_t>(rows, rows_of(static_cast<int>(c->T.grouped.chunks.size()), c->T.grouped.part_rows));
     if (mult == 3) rows = std::max<int64_t>(rows, rows_of(c->stencil_nchunks, c->stencil_part_rows) * 3);
-    if (use_bloch(c, ncol)) rows = std::max(rows, c->bl_part_rows * bloch_split(c, ncol, 2));
+    if (have_bloch(c)) rows = std::max(rows, c->bl_part_rows * bloch_split(c, ncol, 2));
     return static_cast<size_t>(c->nsets()) * rows * ncol * c->ncplx();
 }
 // the grouped projection with the three position-moment components as well
@@ -645,7 +676,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     ProjArgs a = proj_args(c, psi, ld, ncol, table);
     a.part = part;
     a.nq = nq;
-    if (!per_site && !grad && !mout && use_bloch(c, ncol)) {
+    if (!per_site && !grad && !mout && use_bloch(c, 0, ld, ncol)) {
         BlochArgs b = bloch_args(c, ld, ncol, q0, nq);
         b.psi = psi;
         b.part = part;
@@ -1047,7 +1078,7 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
             b.split = split_of(c, static_cast<int64_t>(nch) * nq * lanes(cpl) / cpl, 0.0);
             return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, apply_waves(c), k, store, s);
         };
-        if (!overwrite && use_bloch(c, ncol)) {
+        if (!overwrite && use_bloch(c, 1, ld, ncol)) {
             ++c->nbloch;
             BlochArgs b = bloch_args(c, ld, ncol, q0, nq);
             b.split = bloch_split(c, ncol, 4);
@@ -1601,6 +1632,7 @@ hipError_t build_bloch(hub_ctx* c, size_t& table_bytes) {
     c->bl_pass_ptr.swap(B.pass_ptr);
     c->bl_part_rows = B.part_rows;
     c->bl_wlen = B.wlen;
+    c->bl_entries = static_cast<double>(B.gidx.size());
     c->bl_rows_per_orbital = B.red_ptr.back() / std::max(1, c->T.J);
     c->bloch = true;
     return hipSuccess;
@@ -1712,10 +1744,8 @@ int hub_finalize(hub_ctx* c, void* stream) {
         std::vector<unsigned char> cover(static_cast<size_t>(c->G()), 0);
         for (int32_t g : T.grouped.gidx) cover[g] = 1;
         up(&c->d_cover, cover);
-        double rows = 0.0, points = 0.0;
-        for (const HubChunk& C : T.grouped.chunks) rows += C.nreal;
-        for (unsigned char v : cover) points += v;
-        c->pass_rows = rows / std::max(1.0, points);
+        c->g_rows = 0.0;
+        for (const HubChunk& C : T.grouped.chunks) c->g_rows += C.nreal;
         up(&c->d_gtab, T.grouped.tab);
         std::vector<HubFun> fun(T.grouped.f_orb.size(), HubFun{});
         for (size_t i = 0; i < fun.size(); ++i) {
@@ -2140,7 +2170,7 @@ int hub_step_noalloc(hub_ctx* c, const hub_step_io* io) {
         c->no_bloch = t == 1;
         n_part = slice256(part_need(c, ncol, c->T.spindep ? 2 : 1));
         if ((n_part + n_occ + n_nbar + n_sink) * sizeof(double) <= HUB_SCRATCH_BYTES) break;
-        if (t == 1 || !use_bloch(c, ncol)) {
+        if (t == 1 || !have_bloch(c)) {
             c->no_bloch = false;
             return HUB_ESCRATCH;
         }

@@ -149,3 +149,49 @@ def test_finalize_does_without_the_list_when_memory_runs_out(monkeypatch):
     # its lists, tables and the covers that these are made from; all released
     assert len(without) == 13 and len(set(without)) == 1 and without[0] < bytes_with
     ref.close()
+
+
+@pytest.fixture(scope="module")
+def crystal():
+    """Rocksalt cell of 44^3 points whose second pass covers 6 % of them, 8 k-points."""
+    a = 8.35
+    sites = [dict(R=[x * a for x in p], l=l, zeta=z, rc=rc, species=t)
+             for p, l, z, rc, t in [((0, 0, 0), 2, 2.2, 4.83, 0), ((.5, .5, .5), 2, 2.2, 4.83, 0),
+                                    ((.5, .5, 0), 1, 1.6, 4.025, 1), ((0, 0, .5), 1, 1.6, 4.025, 1)]]
+    kpts = [[x, y, z] for x in (-.25, .25) for y in (-.25, .25) for z in (-.25, .25)]
+    hub = H.Hubbard((a, a, a), (44, 44, 44), sites, kpts=kpts, kweights=[0.125] * 8, spin="collinear",
+                    is_complex=True, precision="f32")
+    assert hub.query(14) == 2 and hub.query(17) == 1
+    yield hub
+    hub.close()
+
+
+@pytest.mark.parametrize("states,ld,project,apply", [
+    (8, 8, 0, 1),          # narrow rows: the projection would read more table than rows, the apply's lanes idle
+    (33, 33, 0, 0),        # rows that start anywhere: the tiles' lines are read and written twice
+    (33, 48, 0, 1),        # the same columns on whole lines
+])
+def test_route_follows_what_the_rows_cost(crystal, states, ld, project, apply):
+    hub = crystal
+    gen = torch.Generator(device="cuda").manual_seed(ld)
+    base = torch.randn((hub.nsets, hub.G, ld), generator=gen, device="cuda", dtype=hub.state_dtype)
+    psi = base[:, :, :states]
+    f = torch.rand((hub.nsets, states), generator=gen, device="cuda", dtype=torch.float64)
+    before = hub.query(18)
+    c = hub.project(psi)
+    assert hub.query(18) - before == project
+    n, _, _ = hub.occupations(c, f)
+    ueff = torch.full((hub.nsites,), 0.2, dtype=torch.float64, device="cuda")
+    h = base.clone()
+    before = hub.query(18)
+    hub.apply(ueff, n, c, h[:, :, :states])
+    assert hub.query(18) - before == apply
+    assert torch.equal(h[:, :, states:], base[:, :, states:])
+    # either route gives the passes' sums: up to three FP32 roundings of a component apart
+    hub.set_vector_potential([0.0, 0.0, 0.0])
+    ref = base.clone()
+    hub.apply(ueff, n, c, ref[:, :, :states])
+    c2 = hub.project(psi)
+    hub.set_vector_potential(None)
+    assert (c - c2).abs().max() < 1e-13 * c2.abs().max() * 10
+    assert (h - ref).abs().max() < 2.6e-7 * ref.abs().max()
