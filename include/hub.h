@@ -450,9 +450,10 @@ int hub_step_current(hub_ctx* ctx, const hub_step_io* io, double* J, int mode);
  * serialized by the caller.  Needs hub_finalize (which takes the array's
  * device address) and the Coulomb tensors unless every U_eff is fixed.
  * Errors: those of hub_step, and HUB_ESCRATCH when the step's workspace
- * exceeds HUB_SCRATCH_BYTES (nothing is launched; where only the
- * image-summed list's projection does not fit, the step runs the grouped
- * list's passes). */
+ * exceeds HUB_SCRATCH_BYTES (nothing is launched).  Where the partial sums of
+ * hub_step's projection exceed it only because a small launch shares its
+ * chunks among several work-groups, the step sums whole chunks and agrees with
+ * hub_step to rounding instead of bit for bit. */
 #define HUB_SCRATCH_BYTES (128u << 20)
 int hub_step_noalloc(hub_ctx* ctx, const hub_step_io* io);
 

@@ -119,7 +119,6 @@ struct hub_ctx {
     // Bloch-summed work list (k_bloch.hip), where the grouped list needs passes
     bool bloch = false;
     double g_rows = 0.0, bl_entries = 0.0;   // rows of one state set that the grouped list's passes and it read
-    bool no_bloch = false;                   // the call in flight does without (scratch limit)
     int64_t nbloch = 0;                      // projections and applies that took the list (hub_query 18)
     std::vector<int32_t> bl_pass_ptr;
     int64_t bl_part_rows = 0, bl_wlen = 0;
@@ -170,6 +169,7 @@ struct hub_ctx {
         double* sink;
     };
     const FixedWs* ws_fixed = nullptr;
+    bool no_split = false;                   // projections of the call in flight leave chunks whole (scratch limit)
     int64_t nalloc = 0;                      // device allocations made so far (hub_query 15)
     int64_t alloc_attempts = 0;
     int64_t fail_alloc = 0;                  // HUB_FAIL_ALLOC: the attempt that fails (0: none)
@@ -398,6 +398,7 @@ int split_of(const hub_ctx* c, int64_t groups, double row_bytes) {
     return s;
 }
 int proj_split(const hub_ctx* c, int nchunks, int64_t rows, int ncol, int cpl, int wide) {
+    if (c->no_split) return 1;
     return split_of(c, proj_groups(c, nchunks, ncol, cpl, wide),
                     8.0 * c->nsets() * rows * ncol * c->ncplx());
 }
@@ -427,7 +428,7 @@ bool grouped(const hub_ctx* c) { return c->use_grouped && c->T.grouped.ok; }
 
 // Whether the Bloch-summed list may take the place of the grouped list's
 // passes (a field changes its phases at every step).
-bool have_bloch(const hub_ctx* c) { return c->bloch && !c->no_bloch && grouped(c) && !c->gauge; }
+bool have_bloch(const hub_ctx* c) { return c->bloch && grouped(c) && !c->gauge; }
 
 // 128-byte lines of a row that tiles of w columns touch, on average over rows
 // ld columns apart.
@@ -620,7 +621,7 @@ size_t part_need(const hub_ctx* c, int ncol, int mult) {
     if (c->T.grouped.ok)
         rows = std::max<int64_t>(rows, rows_of(static_cast<int>(c->T.grouped.chunks.size()), c->T.grouped.part_rows));
     if (mult == 3) rows = std::max<int64_t>(rows, rows_of(c->stencil_nchunks, c->stencil_part_rows) * 3);
-    if (have_bloch(c)) rows = std::max(rows, c->bl_part_rows * bloch_split(c, ncol, 2));
+    if (have_bloch(c)) rows = std::max(rows, c->bl_part_rows * bloch_split(c, ncol, c->no_split ? 1 : 2));
     return static_cast<size_t>(c->nsets()) * rows * ncol * c->ncplx();
 }
 // the grouped projection with the three position-moment components as well
@@ -680,7 +681,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
         BlochArgs b = bloch_args(c, ld, ncol, q0, nq);
         b.psi = psi;
         b.part = part;
-        b.split = bloch_split(c, ncol, 2);
+        b.split = bloch_split(c, ncol, c->no_split ? 1 : 2);
         b.prows = c->bl_part_rows * b.split;
         b.chunk0 = 0;
         b.nchunks = c->bl_pass_ptr.back();
@@ -1556,7 +1557,9 @@ void drop_bloch(hub_ctx* c) {
 // phases on the device.  The list is an option: contexts whose tables would
 // pass kBlochBytes or, with the covers that they are made from, half of the
 // device memory that is free, and contexts for which memory runs out here, keep
-// the grouped list's passes.
+// the grouped list's passes.  So would one with more partial rows than the
+// passes have, whose projections always fit the passes' workspace otherwise
+// (a list chunk holds the points of several grouped ones and no more functions).
 constexpr int64_t kBlochBytes = int64_t(4) << 30;
 hipError_t build_bloch(hub_ctx* c, size_t& table_bytes) {
     BlochTables B;
@@ -1565,6 +1568,7 @@ hipError_t build_bloch(hub_ctx* c, size_t& table_bytes) {
     std::vector<double> one;
     try {
         if (!hub_build_bloch(c->T, c->G(), c->chunk_entries, B, c->nk, kBlochBytes)) return hipSuccess;
+        if (B.part_rows > c->T.grouped.part_rows) return hipSuccess;
         fun.resize(B.f_orb.size(), HubFun{});
         for (size_t i = 0; i < fun.size(); ++i)
             if (B.f_orb[i] >= 0) {
@@ -2165,21 +2169,21 @@ int hub_step_noalloc(hub_ctx* c, const hub_step_io* io) {
     const size_t n_occ = slice256(occ_need(c, io->nstates));
     const size_t n_nbar = io->nbar ? 0 : slice256(static_cast<size_t>(c->nsets()) * c->T.nspecies * io->nstates);
     const size_t n_sink = slice256(static_cast<size_t>(io->ldh) * c->ncplx());
-    // where only the passes of the grouped list fit, they are taken
-    for (int t = 0; t < 2; ++t) {
-        c->no_bloch = t == 1;
+    // where only the partial rows of whole chunks fit, chunks are not split
+    auto fits = [&] {
         n_part = slice256(part_need(c, ncol, c->T.spindep ? 2 : 1));
-        if ((n_part + n_occ + n_nbar + n_sink) * sizeof(double) <= HUB_SCRATCH_BYTES) break;
-        if (t == 1 || !have_bloch(c)) {
-            c->no_bloch = false;
-            return HUB_ESCRATCH;
-        }
+        return (n_part + n_occ + n_nbar + n_sink) * sizeof(double) <= HUB_SCRATCH_BYTES;
+    };
+    c->no_split = !fits();
+    if (c->no_split && !fits()) {
+        c->no_split = false;
+        return HUB_ESCRATCH;
     }
     double* p = static_cast<double*>(base);
     const hub_ctx::FixedWs ws{p, p + n_part, p + n_part + n_occ, p + n_part + n_occ + n_nbar};
     c->ws_fixed = &ws;
     st = run_step(c, io, false);
-    c->no_bloch = false;
+    c->no_split = false;
     c->ws_fixed = nullptr;
     return st;
 }
