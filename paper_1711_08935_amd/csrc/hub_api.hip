@@ -105,6 +105,7 @@ struct hub_ctx {
     int32_t* d_gall_m = nullptr;             // chunk list of the merged launch, by pass
     int32_t* d_gmom = nullptr;               // work items of the moment projection (k_project_mom.h)
     int nmom = 0;
+    int site_longest = 0, grouped_longest = 0;   // entries of the longest chunk of either list
     int32_t* d_gmgidx = nullptr;             // its grid points, runs marked (uploaded with d_gd0)
     std::vector<int> gpass_ptr;              // d_gall_m[gpass_ptr[p], gpass_ptr[p+1]): chunks of pass p
     int gcls_ptr[HUB_NCLASS + 1] = {};       // d_gall[gcls_ptr[k-1], gcls_ptr[k]): chunks of class k
@@ -150,7 +151,7 @@ struct hub_ctx {
     size_t grad_cap = 0;
     // state-gradient force form: dilated-sphere tables, built at first use
     bool stencil_built = false;
-    int stencil_nchunks = 0;
+    int stencil_nchunks = 0, stencil_longest = 0;
     int64_t stencil_part_rows = 0, stencil_entries = 0;
     HubChunk* d_st_chunks = nullptr;
     int32_t *d_st_all = nullptr, *d_st_gidx = nullptr, *d_st_site_ptr = nullptr, *d_st_site_ids = nullptr;
@@ -383,24 +384,35 @@ constexpr int64_t kFullLaunch = 1536;
 
 // Work-groups that share a chunk's entries in one column tile: a launch of
 // few work-groups waits for one batch of rows after another, so its chunks
-// are split (by powers of two, waves of at least 8 entries) up to
-// kSplitGroups work-groups of four waves.  A projection then writes one
+// are split (by powers of two, waves of at least 8 entries of the list's
+// longest chunk) up to kSplitGroups work-groups of four waves.  A projection then writes one
 // partial row per split, at most 16 MB of them (per function of an orbital),
 // which the reduction reads.  Up to 512, 1024 and none: one d shell's step
 // 37 / 40 / 52 us, a small spinor step 82 / 82 / 104 us, four d shells with
 // 512 columns 109 / 116 / 111 us.
 constexpr int64_t kSplitGroups = 512;
-int split_of(const hub_ctx* c, int64_t groups, double row_bytes) {
+int split_of(int longest, int64_t groups, double row_bytes) {
     int s = 1;
-    while (s < 16 && groups * s * 2 <= kSplitGroups && s * 2 * 32 <= c->chunk_entries &&
+    while (s < 16 && groups * s * 2 <= kSplitGroups && s * 2 * 32 <= longest &&
            row_bytes * s * 2 <= 16.0 * (1 << 20))
         s *= 2;
     return s;
 }
-int proj_split(const hub_ctx* c, int nchunks, int64_t rows, int ncol, int cpl, int wide) {
+// A list of chunks as the projection's launch rules see it.
+struct ListShape {
+    int nchunks, longest;                    // chunks; entries of the longest
+    int64_t rows;                            // workspace rows (per function of an orbital)
+};
+ListShape site_list(const hub_ctx* c) {
+    return {static_cast<int>(c->T.chunks.size()), c->site_longest, c->T.part_rows};
+}
+ListShape grouped_list(const hub_ctx* c) {
+    return {static_cast<int>(c->T.grouped.chunks.size()), c->grouped_longest, c->T.grouped.part_rows};
+}
+ListShape stencil_list(const hub_ctx* c) { return {c->stencil_nchunks, c->stencil_longest, c->stencil_part_rows}; }
+int proj_split(const hub_ctx* c, const ListShape& l, int ncol, int cpl, int wide) {
     if (c->no_split) return 1;
-    return split_of(c, proj_groups(c, nchunks, ncol, cpl, wide),
-                    8.0 * c->nsets() * rows * ncol * c->ncplx());
+    return split_of(l.longest, proj_groups(c, l.nchunks, ncol, cpl, wide), 8.0 * c->nsets() * l.rows * ncol * c->ncplx());
 }
 // The same for the Bloch-summed list, whose work-groups are single waves, by
 // the whole list and every state set: two in the projection, whose partial
@@ -414,6 +426,11 @@ int bloch_split(const hub_ctx* c, int ncol, int most) {
     int s = 1;
     while (s < most && groups * s * 2 <= kBlochGroups) s *= 2;
     return s;
+}
+int longest_chunk(const std::vector<HubChunk>& chunks) {
+    int n = 0;
+    for (const HubChunk& C : chunks) n = std::max(n, C.ne);
+    return n;
 }
 int ilog2(int v) {
     int l = 0;
@@ -616,11 +633,10 @@ ReduceArgs reduce_args(hub_ctx* c, const double* part, double* out, int ncol, in
 // project + reduce into c (per_site: one projection launch per site)
 size_t part_need(const hub_ctx* c, int ncol, int mult) {
     // the split of the widest lanes, the largest
-    auto rows_of = [&](int nchunks, int64_t r) { return r * proj_split(c, nchunks, r, ncol, 4, 0); };
-    int64_t rows = rows_of(static_cast<int>(c->T.chunks.size()), c->T.part_rows) * mult;
-    if (c->T.grouped.ok)
-        rows = std::max<int64_t>(rows, rows_of(static_cast<int>(c->T.grouped.chunks.size()), c->T.grouped.part_rows));
-    if (mult == 3) rows = std::max<int64_t>(rows, rows_of(c->stencil_nchunks, c->stencil_part_rows) * 3);
+    auto rows_of = [&](const ListShape& l) { return l.rows * proj_split(c, l, ncol, 4, 0); };
+    int64_t rows = rows_of(site_list(c)) * mult;
+    if (c->T.grouped.ok) rows = std::max<int64_t>(rows, rows_of(grouped_list(c)));
+    if (mult == 3) rows = std::max<int64_t>(rows, rows_of(stencil_list(c)) * 3);
     if (have_bloch(c)) rows = std::max(rows, c->bl_part_rows * bloch_split(c, ncol, c->no_split ? 1 : 2));
     return static_cast<size_t>(c->nsets()) * rows * ncol * c->ncplx();
 }
@@ -723,7 +739,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
         const int nall = static_cast<int>(GT.chunks.size());
         if (!mout) {
             const int cpl = clamp_cpl(c, pick_cpl(c, psi, ld, 0, ncol), HUB_GF_MAX);
-            a.split = proj_split(c, nall, GT.part_rows, ncol, cpl, pick_wide(c, ncol, cpl, 0));
+            a.split = proj_split(c, grouped_list(c), ncol, cpl, pick_wide(c, ncol, cpl, 0));
             a.prows = GT.part_rows * a.split;
         }
         if (mout) {
@@ -784,7 +800,8 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     // gradient tiles hold 3L functions, spin-dependent tiles 2L
     if ((grad || spindep) && cpl * c->ncplx() > 4) cpl = 4 / c->ncplx();
     a.wide = pick_wide(c, ncol, cpl, 0);
-    const int list = stencil_table(table) ? c->stencil_nchunks : static_cast<int>(c->T.chunks.size());
+    const ListShape shape = stencil_table(table) ? stencil_list(c) : site_list(c);
+    const int list = shape.nchunks;
     const bool full = !per_site && proj_groups(c, list, ncol, cpl, a.wide) >= kFullLaunch;
     // gradients in a launch that does not fill the chip: two values per lane
     // instead of four (4 d shells, 512 FP32 columns: 42 us against 45).  On
@@ -805,7 +822,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     const int gw = cpl * c->ncplx() == 1 ? 4 : 2;
     const int waves = c->tune_waves[0] ? c->tune_waves[0] : (full ? (grad ? gw : 1) : 4);
     if (!per_site) {
-        a.split = proj_split(c, list, stencil_table(table) ? c->stencil_part_rows : c->T.part_rows, ncol, cpl, a.wide);
+        a.split = proj_split(c, shape, ncol, cpl, a.wide);
         a.prows *= a.split;
     }
     {
@@ -1076,7 +1093,7 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
             if (c->tune_cpl[1] || store || !full)
                 cpl = clamp_cpl(c, pick_cpl(c, hpsi, ld, 1, ncol), hub_cls_nfmax(k));
             while (!c->tune_cpl[1] && cpl > 1 && lanes(cpl / 2) < lanes(cpl)) cpl /= 2;
-            b.split = split_of(c, static_cast<int64_t>(nch) * nq * lanes(cpl) / cpl, 0.0);
+            b.split = split_of(c->grouped_longest, static_cast<int64_t>(nch) * nq * lanes(cpl) / cpl, 0.0);
             return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, apply_waves(c), k, store, s);
         };
         if (!overwrite && use_bloch(c, 1, ld, ncol)) {
@@ -1671,6 +1688,8 @@ int hub_finalize(hub_ctx* c, void* stream) {
     auto up = [&](auto** dst, const auto& src) {
         if (e == hipSuccess) e = upload(c, dst, src, b);
     };
+    c->site_longest = longest_chunk(T.chunks);
+    c->grouped_longest = longest_chunk(T.grouped.chunks);
     up(&c->d_chunks, T.chunks);
     up(&c->d_all, all);
     up(&c->d_gidx, T.gidx);
@@ -2094,6 +2113,7 @@ int build_stencil(hub_ctx* c) {
     if (c->T.spindep) HUB_TRY(upload(c, &c->d_st_tab_dn, S.tab_dn, bytes));
     c->table_bytes += bytes;
     c->stencil_nchunks = static_cast<int>(S.chunks.size());
+    c->stencil_longest = longest_chunk(S.chunks);
     c->stencil_part_rows = S.part_rows;
     c->stencil_entries = S.nentries;
     c->stencil_built = true;

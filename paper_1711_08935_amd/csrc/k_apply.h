@@ -165,6 +165,12 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C
         col0 = active ? (t - q * cg) * CPL : 0;
     }
 
+    // this wave's entries: e0 + [lo, lo + nj) of the chunk; a short chunk may
+    // have none for the whole work-group
+    int lo, nj;
+    hub_entry_range(C.ne, nw * a.split, part_of * nw, lo, nj);
+    if (nj == 0) return;
+    hub_entry_range(C.ne, nw * a.split, part_of * nw + wave, lo, nj);
     // coefficients: the waves split the functions (lanes past the last
     // column compute zeros for column 0 of their set and are then idle)
     for (int f = wave; f < L; f += nw) {
@@ -193,9 +199,6 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C
         for (int v = 0; v < NV; ++v) B[f][v] = Bs[(f * NV + v) * HUB_WAVE + lane];
 
     T* __restrict__ h_q = hpsi + static_cast<int64_t>(q) * a.qstride;
-    // this wave's entries: e0 + [lo, lo + nj) of the chunk
-    int lo, nj;
-    hub_entry_range(C.ne, nw * a.split, part_of * nw + wave, lo, nj);
     const int32_t* __restrict__ gi = gidx + C.e0 + lo;
     const double* __restrict__ tb = tab + (C.phi0 * (SPINDEP ? 2 : 1) + static_cast<int64_t>(lo) * L);
     const int lofs = col0 * NC;
