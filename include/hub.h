@@ -156,9 +156,10 @@ int hub_set_chunk(hub_ctx* ctx, int chunk_entries);
 
 /* Kernel shape for the projection (which = 0) and the application
  * (which = 1): columns handled per lane (1, 2 or 4; 0 = automatic), waves
- * per work-group (1, 2 or 4; by default chosen from the launch's size), and the lane layout (1: every wave inside one
- * state set; 0: narrow state sets packed across the lanes of a wave;
- * -1: automatic).  Every shape computes the same result.  Any time after
+ * per work-group (1, 2 or 4; 0 = automatic, from the launch's size), and the
+ * lane layout (1: every wave inside one state set; 0: narrow state sets packed
+ * across the lanes of a wave; -1: automatic).  Every shape computes the same
+ * result; (0, 0, -1), the default, chooses all three.  Any time after
  * creation. */
 int hub_set_tuning(hub_ctx* ctx, int which, int cols_per_lane, int waves, int layout);
 

@@ -268,7 +268,8 @@ class Hubbard:
 
     def set_tuning(self, which, cols_per_lane, waves, layout=-1):
         """Kernel shape of the projection (which=0) or apply (1); layout 1 =
-        one state set per wave, 0 = sets packed across lanes, -1 = automatic."""
+        one state set per wave, 0 = sets packed across lanes; (0, 0, -1) =
+        automatic (the default)."""
         _check(lib().hub_set_tuning(self._ctx, int(which), int(cols_per_lane), int(waves), int(layout)),
                "hub_set_tuning")
 

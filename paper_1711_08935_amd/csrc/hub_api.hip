@@ -1530,7 +1530,7 @@ int hub_set_class_launch(hub_ctx* c, int policy) {
 int hub_set_tuning(hub_ctx* c, int which, int cpl, int waves, int layout) {
     if (!c || (which != 0 && which != 1)) return HUB_EINVAL;
     if (cpl != 0 && cpl != 1 && cpl != 2 && cpl != 4) return HUB_EINVAL;
-    if (waves != 1 && waves != 2 && waves != 4) return HUB_EINVAL;
+    if (waves != 0 && waves != 1 && waves != 2 && waves != 4) return HUB_EINVAL;
     if (layout < -1 || layout > 1) return HUB_EINVAL;
     c->tune_cpl[which] = cpl;
     c->tune_waves[which] = waves;
