@@ -859,9 +859,13 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     return HUB_OK;
 }
 
-size_t occ_need(const hub_ctx* c, int nstates) {
-    const int nchan = c->spin_mode == HUB_SPINOR ? 1 : c->nspin();
-    return static_cast<size_t>(c->T.nsites) * nchan * hub_occ_splits(c->nk, nstates) * HUB_OCC_PAIRS * 4;
+// Partial sums of the occupations; none where k_occ_one forms them in one launch
+// (step: with the site's ACBN0 step, one channel only).
+size_t occ_need(const hub_ctx* c, int nstates, bool step) {
+    const int nchan = c->spin_mode == HUB_COLLINEAR ? 2 : 1;
+    const int nsplit = hub_occ_splits(c->nk, nstates);
+    if (nsplit == 1 && (!step || nchan == 1)) return 0;
+    return static_cast<size_t>(c->T.nsites) * nchan * nsplit * HUB_OCC_PAIRS * 4;
 }
 
 // Orbitals up to which k_occ_one forms N-bar itself instead of reading
@@ -875,8 +879,8 @@ int do_occupations(hub_ctx* c, const double* cc, int nstates, const double* f, d
                    bool per_site) {
     const int ncol = c->ncol(nstates);
     double* ws = c->ws_fixed ? c->ws_fixed->occ : nullptr;
-    if (!ws) {
-        const int st = ensure(&c->d_occ_ws, &c->occ_cap, occ_need(c, nstates), c);
+    if (const size_t need = occ_need(c, nstates, false); !ws && need) {
+        const int st = ensure(&c->d_occ_ws, &c->occ_cap, need, c);
         if (st) return st;
         ws = c->d_occ_ws;
     }
@@ -948,8 +952,8 @@ int do_occupations(hub_ctx* c, const double* cc, int nstates, const double* f, d
 // order as do_occupations followed by do_acbn0.
 int do_step_occ(hub_ctx* c, const hub_step_io* io) {
     double* ws = c->ws_fixed ? c->ws_fixed->occ : nullptr;
-    if (!ws) {
-        const int st = ensure(&c->d_occ_ws, &c->occ_cap, occ_need(c, io->nstates), c);
+    if (const size_t need = occ_need(c, io->nstates, true); !ws && need) {
+        const int st = ensure(&c->d_occ_ws, &c->occ_cap, need, c);
         if (st) return st;
         ws = c->d_occ_ws;
     }
@@ -1246,8 +1250,10 @@ int step_impl(hub_ctx* c, const hub_step_io* io, int mode, double* jcur) {
     }
     st = ensure(&c->d_sink, &c->sink_cap, static_cast<size_t>(io->ldh) * c->ncplx(), c);
     if (st) return st;
-    st = ensure(&c->d_occ_ws, &c->occ_cap, occ_need(c, io->nstates), c);
-    if (st) return st;
+    if (const size_t need = occ_need(c, io->nstates, mode != HUB_STEP_PERSITE)) {
+        st = ensure(&c->d_occ_ws, &c->occ_cap, need, c);
+        if (st) return st;
+    }
     if (mode != HUB_STEP_GRAPH) return run_step(c, io, mode == HUB_STEP_PERSITE, jcur);
 
     hub_ctx::GraphSlot* slot = nullptr;
@@ -2186,7 +2192,7 @@ int hub_step_noalloc(hub_ctx* c, const hub_step_io* io) {
     // partial sums, N-bar (when the caller passes none), the apply's sink row
     const int ncol = c->ncol(io->nstates);
     size_t n_part = 0;
-    const size_t n_occ = slice256(occ_need(c, io->nstates));
+    const size_t n_occ = slice256(occ_need(c, io->nstates, true));
     const size_t n_nbar = io->nbar ? 0 : slice256(static_cast<size_t>(c->nsets()) * c->T.nspecies * io->nstates);
     const size_t n_sink = slice256(static_cast<size_t>(io->ldh) * c->ncplx());
     // where only the partial rows of whole chunks fit, chunks are not split
