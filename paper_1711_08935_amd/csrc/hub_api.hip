@@ -1924,9 +1924,12 @@ int hub_coulomb(hub_ctx* c, int site, double* tensor) {
     }
     if (!st && tensor) {
         const int L = c->T.site_L[site];
-        st = map_err(hipMemcpyAsync(tensor, c->d_tensor + static_cast<size_t>(site) * 2401,
-                                    static_cast<size_t>(L) * L * L * L * sizeof(double), hipMemcpyDeviceToDevice,
-                                    c->stream));
+        hipError_t e = hipMemcpyAsync(tensor, c->d_tensor + static_cast<size_t>(site) * 2401,
+                                      static_cast<size_t>(L) * L * L * L * sizeof(double), hipMemcpyDeviceToDevice,
+                                      c->stream);
+        // like the context's tensors, the copy is there when the call returns
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        st = map_err(e);
     }
     return st;
 }
