@@ -1229,15 +1229,7 @@ int step_impl(hub_ctx* c, const hub_step_io* io, int mode, double* jcur) {
         if (fused) {
             size_t bytes = 0;
             if (!c->d_gfdel) HUB_TRY(upload(c, &c->d_gfdel, c->T.grouped.fdel, bytes));
-            if (!c->d_gmgidx) {
-                std::vector<int32_t> g(c->T.grouped.gidx);
-                for (const HubChunk& C : c->T.grouped.chunks) {
-                    const double* d = &c->T.grouped.d0[3 * static_cast<size_t>(C.e0)];
-                    for (int e = 1; e < C.nreal; ++e)
-                        if (d[3 * e] != d[3 * e - 3] || d[3 * e + 1] != d[3 * e - 2]) g[C.e0 + e] |= INT32_MIN;
-                }
-                HUB_TRY(upload(c, &c->d_gmgidx, g, bytes));
-            }
+            if (!c->d_gmgidx) HUB_TRY(upload(c, &c->d_gmgidx, c->T.grouped.run_gidx, bytes));
             if (!c->d_gd0) HUB_TRY(upload(c, &c->d_gd0, c->T.grouped.d0, bytes));
             c->table_bytes += bytes;
         }
@@ -1666,11 +1658,8 @@ hipError_t build_bloch(hub_ctx* c, size_t& table_bytes) {
 }
 }  // namespace
 
-int hub_finalize(hub_ctx* c, void* stream) {
-    if (!c) return HUB_EINVAL;
-    int st = hub_finalize_host(c);
-    if (st) return st;
-    if (c->built_dev) return HUB_OK;
+namespace {
+int finalize_device(hub_ctx* c, void* stream) {
     HUB_TRY(hipGetDevice(&c->device));
     HUB_TRY(scratch_address(c->device));
     c->stream = reinterpret_cast<hipStream_t>(stream);
@@ -1752,10 +1741,8 @@ int hub_finalize(hub_ctx* c, void* stream) {
         std::vector<int64_t> cost;
         for (int32_t i : gm) {
             const HubChunk& C = T.grouped.chunks[i];
-            const double* d = &T.grouped.d0[3 * static_cast<size_t>(C.e0)];
             int64_t runs = 1;
-            for (int e = 1; e < C.nreal; ++e)
-                if (d[3 * e] != d[3 * e - 3] || d[3 * e + 1] != d[3 * e - 2]) ++runs;
+            for (int e = 1; e < C.nreal; ++e) runs += T.grouped.run_gidx[C.e0 + e] < 0;
             const int64_t nfw = (C.L + hub_mom_parts(C.L) - 1) / hub_mom_parts(C.L);
             for (int h = 0; h < hub_mom_waves(C.L); ++h) {
                 items.push_back(4 * i + h);
@@ -1814,6 +1801,20 @@ int hub_finalize(hub_ctx* c, void* stream) {
     c->built_dev = true;
     if (c->gauge) return gauge_tables(c);
     return HUB_OK;
+}
+}  // namespace
+
+int hub_finalize(hub_ctx* c, void* stream) {
+    if (!c) return HUB_EINVAL;
+    const int st = hub_finalize_host(c);
+    if (st) return st;
+    if (c->built_dev) return HUB_OK;
+    try {
+        return finalize_device(c, stream);
+    } catch (...) {                                  // host memory for the launch lists
+        release(c);
+        return HUB_ENOMEM;
+    }
 }
 
 int hub_set_stream(hub_ctx* c, void* stream) {
@@ -2141,7 +2142,12 @@ int hub_forces_state_gradient(hub_ctx* c, const void* psi, int64_t ld, int nstat
     if (!c) return HUB_EINVAL;
     if (!built(c)) return HUB_ESTATE;
     if (!c->stencil_built) {
-        const int st = build_stencil(c);
+        int st;
+        try {
+            st = build_stencil(c);
+        } catch (...) {                              // host memory for the tables
+            st = HUB_ENOMEM;
+        }
         if (st) return st;
     }
     return contract_moments(c, psi, ld, nstates, cc, f, Ueff, n, F, TAB_STENCIL);

@@ -91,6 +91,9 @@ struct GroupTables {
     // site, fdel[chunk][HUB_GF_MAX][3] (constant over a chunk's points)
     std::vector<double> d0;
     std::vector<double> fdel;
+    // gidx, with the sign bit set on points that start a new run: d0's x or y
+    // component differs from the point before in the chunk
+    std::vector<int32_t> run_gidx;
     std::vector<int32_t> f_orb;              // per chunk HUB_GF_MAX: global orbital j of function f
     std::vector<int32_t> f_img;              // per chunk HUB_GF_MAX: lattice image of function f
     std::vector<int32_t> red_ptr;            // CSR orbital j -> workspace rows

@@ -531,6 +531,9 @@ int hub_build_host(const double cell[3], const int ngrid[3], const std::vector<S
                         const size_t i0 = firsts[b + t];
                         GT.gidx.push_back(cov[i0].g);
                         for (int i = 0; i < 3; ++i) GT.d0.push_back(disp(cov[i0], i));
+                        const double* d = &GT.d0[GT.d0.size() - 3];
+                        const bool run = t > 0 && (d[0] != d[-3] || d[1] != d[-2]);
+                        GT.run_gidx.push_back(run ? cov[i0].g | INT32_MIN : cov[i0].g);
                         for (size_t sl = 0; sl < sig.size(); ++sl) {
                             const Cover& cv = cov[i0 + sl];
                             const int L = T.site_L[cv.site];
@@ -544,6 +547,7 @@ int hub_build_host(const double cell[3], const int ngrid[3], const std::vector<S
                     }
                     for (size_t t = nb; t < np; ++t) {
                         GT.gidx.push_back(GT.gidx.back());
+                        GT.run_gidx.push_back(GT.gidx.back());
                         GT.tab.insert(GT.tab.end(), nf, 0.0);
                         GT.d0.insert(GT.d0.end(), 3, 0.0);
                     }
