@@ -1659,6 +1659,8 @@ hipError_t build_bloch(hub_ctx* c, size_t& table_bytes) {
 }  // namespace
 
 namespace {
+constexpr size_t kSinkRow = 8192;
+
 int finalize_device(hub_ctx* c, void* stream) {
     HUB_TRY(hipGetDevice(&c->device));
     HUB_TRY(scratch_address(c->device));
@@ -1787,6 +1789,10 @@ int finalize_device(hub_ctx* c, void* stream) {
         e = dev_malloc(c, &c->d_tensor, c->sites.size() * 2401 * sizeof(double));
         b += c->sites.size() * 2401 * sizeof(double);
     }
+    // the apply's row for padding entries, for rows of up to kSinkRow values;
+    // longer ones replace it at their first apply
+    if (e == hipSuccess) e = dev_malloc(c, &c->d_sink, kSinkRow * sizeof(double));
+    if (e == hipSuccess) c->sink_cap = kSinkRow;
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
     for (int k = 0; k < HUB_NCLASS && e == hipSuccess; ++k) {
         e = hipStreamCreateWithFlags(&c->side[k], hipStreamNonBlocking);

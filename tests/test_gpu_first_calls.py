@@ -32,3 +32,23 @@ def test_occupations_allocate_only_what_they_use(spin, nk, states, calls, step):
     assert hub.query(15) - before == step - calls
     assert torch.equal(b["n"], n) and torch.equal(b["pbar"], pbar) and torch.equal(b["nbar"], nbar)
     hub.close()
+
+
+@pytest.mark.parametrize("ld,calls", [(40, 0), (4096, 0), (4128, 1)])
+def test_apply_allocates_for_long_rows_only(ld, calls):
+    # complex rows: the row that padding entries write holds up to 8192 values from hub_finalize on
+    hub = _hub("unpolarized", 1, MIX[:2])
+    gen = torch.Generator(device="cuda").manual_seed(ld)
+    c = torch.randn((1, hub.J, 40), generator=gen, device="cuda", dtype=torch.complex128)
+    n, _, _ = hub.occupations(c, torch.ones((1, 40), device="cuda", dtype=torch.float64))
+    ueff = torch.full((hub.nsites,), 0.2, dtype=torch.float64, device="cuda")
+    out = []
+    for width, new in ((ld, calls), (40, 0)):
+        h = torch.zeros((1, hub.G, width), device="cuda", dtype=hub.state_dtype)
+        before = hub.query(15)
+        hub.apply(ueff, n, c, h[:, :, :40])
+        assert hub.query(15) - before == new
+        out.append(h[:, :, :40].clone())
+        assert torch.count_nonzero(h[:, :, 40:]) == 0
+    assert torch.equal(*out) and torch.count_nonzero(out[0]) > 0
+    hub.close()
