@@ -36,10 +36,10 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E, 8 TB/s
 # the step (hub_current)
 GAUGE_RUNS = (("gauge_steps_per_s", None), ("gauge_current_steps_per_s", "step"),
               ("gauge_current_separate_steps_per_s", "separate"))
-# sources of the projection and apply kernels (the counter files record
-# their hash: traffic measured on other sources is not reported)
-KERNEL_SOURCES = ["kcommon.h", "k_project.h", "k_project_f32.hip", "k_project_f64.hip", "k_apply.h",
-                  "k_apply_f32.hip", "k_apply_f64.hip", "k_apply_grouped_f32.hip", "k_apply_grouped_f64.hip"]
+# sources of the kernels (the counter files record their hash: traffic
+# measured on other sources is not reported)
+KERNEL_SOURCES = sorted(f for f in os.listdir(os.path.join(ROOT, "paper_1711_08935_amd", "csrc"))
+                        if f.endswith((".h", ".hip")) and f != "hub_api.hip")
 
 
 def log(msg):

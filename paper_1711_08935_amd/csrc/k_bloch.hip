@@ -17,8 +17,9 @@
 // functions, 16 sets of 64 FP32 columns: 0.18 ms of products, 0.22 ms of rows
 // and tables for the projection).  Measured there against the grouped list's
 // five passes (76 functions): projection 0.31 ms (0.76), reduction 0.020
-// (0.099), apply 0.43 (1.39).  It wins from two passes on: 31 functions in
-// FP64, 16 sets of 45 columns 0.37 and 0.52 ms (0.56 and 0.95).
+// (0.099), apply 0.43 (1.39).  31 functions in FP64, 16 sets of 45 columns:
+// 0.37 and 0.52 ms (0.56 and 0.95).  Where few points need a second pass or rows
+// are short the passes win (use_bloch, hub_api.hip).
 
 #include "kbloch.h"
 
@@ -181,7 +182,10 @@ k_bloch_project(const BlochArgs a, const int32_t* __restrict__ gidx, const doubl
 // coefficient() of the grouped apply forms them.  The projections of the
 // chunk's orbitals and the rows of V of its functions are staged in LDS, every
 // load of the two in flight together, so that the wave waits twice (for the
-// functions' records and for these) however many functions it has.
+// functions' records and for these) however many functions it has.  From a
+// buffer that a launch of its own filled, the apply took as long on full
+// launches (110 592 points, 16 sets of 64 columns: 454 us, 456 here) and longer
+// on small ones (13 824 points, 16 sets of 13 columns: 24.3 us, 20.4 here).
 template <bool SPINOR, int NF, int NC>
 struct CoefLds {
     static constexpr int NV = SPINOR ? 4 : 1;        // blocks of n that a site's columns use
