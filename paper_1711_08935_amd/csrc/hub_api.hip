@@ -391,10 +391,11 @@ constexpr int64_t kFullLaunch = 1536;
 // 37 / 40 / 52 us, a small spinor step 82 / 82 / 104 us, four d shells with
 // 512 columns 109 / 116 / 111 us.
 constexpr int64_t kSplitGroups = 512;
+constexpr int64_t kSplitBytes = 16 << 20;
 int split_of(int longest, int64_t groups, double row_bytes) {
     int s = 1;
     while (s < 16 && groups * s * 2 <= kSplitGroups && s * 2 * 32 <= longest &&
-           row_bytes * s * 2 <= 16.0 * (1 << 20))
+           row_bytes * s * 2 <= static_cast<double>(kSplitBytes))
         s *= 2;
     return s;
 }
@@ -631,14 +632,31 @@ ReduceArgs reduce_args(hub_ctx* c, const double* part, double* out, int ncol, in
 }
 
 // project + reduce into c (per_site: one projection launch per site)
-size_t part_need(const hub_ctx* c, int ncol, int mult) {
-    // the split of the widest lanes, the largest
-    auto rows_of = [&](const ListShape& l) { return l.rows * proj_split(c, l, ncol, 4, 0); };
-    int64_t rows = rows_of(site_list(c)) * mult;
-    if (c->T.grouped.ok) rows = std::max<int64_t>(rows, rows_of(grouped_list(c)));
-    if (mult == 3) rows = std::max<int64_t>(rows, rows_of(stencil_list(c)) * 3);
-    if (have_bloch(c)) rows = std::max(rows, c->bl_part_rows * bloch_split(c, ncol, c->no_split ? 1 : 2));
-    return static_cast<size_t>(c->nsets()) * rows * ncol * c->ncplx();
+// Doubles of the partial rows.  Fewer columns may be split more and so take
+// more rows: a workspace that the context keeps (smaller: also for every
+// smaller number of columns, and for the Bloch-summed list also under a field)
+// is not replaced when they come, under a caller's graph say.
+size_t part_need(const hub_ctx* c, int ncol, int mult, bool smaller = true) {
+    const int64_t nq = c->nsets(), nc = c->ncplx();
+    // rows times columns, at the split of the widest lanes, the largest
+    auto most = [&](const ListShape& l) {
+        int64_t n = l.rows * ncol * proj_split(c, l, ncol, 4, 0);
+        for (int s = 2; smaller && l.rows > 0 && s <= 16 && s * 32 <= l.longest; s *= 2) {
+            const int64_t tiles = kSplitGroups / s / l.nchunks;
+            const int64_t cols = std::min(4 * (tiles * HUB_WAVE / nq), kSplitBytes / (8 * nq * l.rows * nc * s));
+            n = std::max(n, l.rows * s * std::min<int64_t>(ncol, cols));
+        }
+        return n;
+    };
+    int64_t n = most(site_list(c)) * mult;
+    if (c->T.grouped.ok) n = std::max(n, most(grouped_list(c)));
+    if (mult == 3) n = std::max(n, most(stencil_list(c)) * 3);
+    if (smaller ? c->bloch : have_bloch(c)) {
+        n = std::max(n, c->bl_part_rows * ncol * bloch_split(c, ncol, c->no_split ? 1 : 2));
+        const int64_t tiles = kBlochGroups / 2 / (c->bl_pass_ptr.back() * nq);
+        if (smaller) n = std::max(n, c->bl_part_rows * 2 * std::min<int64_t>(ncol, 32 * tiles));
+    }
+    return static_cast<size_t>(nq * nc * n);
 }
 // the grouped projection with the three position-moment components as well
 size_t part_need_moments(const hub_ctx* c, int ncol) {
@@ -2212,7 +2230,7 @@ int hub_step_noalloc(hub_ctx* c, const hub_step_io* io) {
     const size_t n_sink = slice256(static_cast<size_t>(io->ldh) * c->ncplx());
     // where only the partial rows of whole chunks fit, chunks are not split
     auto fits = [&] {
-        n_part = slice256(part_need(c, ncol, c->T.spindep ? 2 : 1));
+        n_part = slice256(part_need(c, ncol, c->T.spindep ? 2 : 1, false));
         return (n_part + n_occ + n_nbar + n_sink) * sizeof(double) <= HUB_SCRATCH_BYTES;
     };
     c->no_split = !fits();
