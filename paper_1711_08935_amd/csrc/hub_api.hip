@@ -1312,8 +1312,9 @@ int step_impl(hub_ctx* c, const hub_step_io* io, int mode, double* jcur) {
 // Coulomb tensors of some sites: the plan's tables go up in one copy beside
 // the scratch, whose slices start on 256-byte boundaries.
 constexpr size_t kCoulombBatch = size_t(512) << 20;    // bytes of densities and offsets per batch
-// Scratch up to this size is the projection's workspace, which the next step
-// finds allocated; more is given back at once.
+// Scratch up to this size becomes the projection's workspace, which the next
+// step finds allocated; more is given back at once, and so is what a workspace
+// that is there cannot hold: captured steps run on that one.
 constexpr size_t kCoulombKeep = size_t(64) << 20;
 
 int coulomb_batch(hub_ctx* c, const std::vector<int>& sites) {
@@ -1369,7 +1370,7 @@ int coulomb_batch(hub_ctx* c, const std::vector<int>& sites) {
     const size_t n_rho = slice256(P.rho), n_part = slice256(P.part), n_yz = slice256(P.slots), n_tab = slice256(table);
     const size_t need = n_rho + n_part + n_yz + n_tab + host.size() / sizeof(double);
     double* own = nullptr;
-    if (need * sizeof(double) <= kCoulombKeep) {
+    if (c->d_part ? c->part_cap >= need : need * sizeof(double) <= kCoulombKeep) {
         // a projection on another stream may still read it
         if (c->d_part) HUB_TRY(hipDeviceSynchronize());
         const int st = ensure(&c->d_part, &c->part_cap, need, c);
