@@ -171,13 +171,13 @@ int hub_set_tuning(hub_ctx* ctx, int which, int cols_per_lane, int waves, int la
  * in successive atomic-free layers.  A grid point covered by more than 16
  * orbitals in total has its covers split over several passes of the
  * grouped list (at most 16 functions each; the apply launches the passes in
- * turn, hub_query 14); for complex states without a field or spin-dependent
- * orbitals, the projection and the apply then use, where by its size it is faster, a
- * list with each point's covers summed over the images of a site.
- * hub_finalize makes its tables where they take at most 4 GiB and, while they
- * are made, half of the free device memory; where they do not fit, or an
- * allocation for them fails, the passes serve every call (hub_query 17 and 18
- * tell).  All give the same results up to summation order.
+ * turn, hub_query 14).  For complex states without a field or spin-dependent
+ * orbitals, the projection and the apply then each use, where its estimated
+ * time is less, a list with each point's covers summed over the images of a
+ * site.  hub_finalize makes its tables where they take at most 4 GiB and,
+ * while they are made, half of the free device memory; where they do not fit,
+ * or an allocation for them fails, the passes serve every call (hub_query 17
+ * and 18 tell).  All give the same results up to summation order.
  * Any time. */
 int hub_set_worklist(hub_ctx* ctx, int grouped_list);
 
@@ -431,9 +431,9 @@ int hub_step(hub_ctx* ctx, const hub_step_io* io, int mode);
  * in one sequence, so c and everything that follows from it (n, U, J,
  * U_eff, hpsi) agree with hub_step's to rounding, and J with hub_current's.
  * Elsewhere (HUB_STEP_PERSITE, the per-site work list, real states) it runs
- * hub_step's stages, bit for bit, and hub_current's own projection.  The first fused call uploads the moment
- * tables (three displacements and an index per grouped point).  Errors: those of
- * hub_step; HUB_EINVAL for a null J. */
+ * hub_step's stages, bit for bit, and hub_current's own projection.  The first
+ * fused call uploads the moment tables (three displacements and an index per
+ * grouped point).  Errors: those of hub_step; HUB_EINVAL for a null J. */
 int hub_step_current(hub_ctx* ctx, const hub_step_io* io, double* J, int mode);
 
 /* For callers that cannot allocate device memory (code under HIP graph
