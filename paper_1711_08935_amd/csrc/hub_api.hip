@@ -1089,6 +1089,7 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
     a.site_orb0 = c->d_site_orb0;
     a.site_L = c->d_site_L;
     a.split = 1;
+    a.stream = (reinterpret_cast<uintptr_t>(hpsi) | static_cast<uintptr_t>(ld) * c->elem()) % 128 == 0;
     a.spindep = c->T.spindep ? 1 : 0;
     if (!per_site && grouped(c)) {
         a.wide = 1;

@@ -135,8 +135,10 @@ __device__ __forceinline__ void coefficient(const ApplyArgs& a, const HubFun& F,
 // coefficient is nonzero only in that component's columns.
 // STORE: the rows are overwritten with the update instead of being read and
 // added to (the energy gradient, whose buffer starts at zero), with
-// non-temporal stores (16 sets of 64 complex FP32 columns: 193 us, 244 with
-// ordinary ones; 512 real columns the same).
+// non-temporal stores where rows start on 128 bytes (16 sets of 64 complex FP32
+// columns: 198 us, 269 with ordinary ones).  Elsewhere rows share lines, which
+// the cache has to put together (249 real FP32 columns of 32 d shells, apply
+// alone 179 us non-temporal, 150 when it added to cleared rows).
 template <typename T, bool CPX, bool SPINOR, int CPL, int L, bool WIDE, bool GROUPED, bool GAUGE,
           bool SPINDEP = false, bool STORE = false>
 __device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C, int ci, int slot_tile,
@@ -257,7 +259,7 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C
 #pragma unroll
             for (int v = 0; v < NV; ++v)
                 out[v] = static_cast<T>(STORE ? add[v] : static_cast<double>(r[u][v]) + add[v]);
-            if constexpr (STORE) store_row_stream<T, NV>(p[u], out);
+            if (STORE && a.stream) store_row_stream<T, NV>(p[u], out);
             else store_row<T, NV>(p[u], out);
         }
     };

@@ -912,10 +912,10 @@ __global__ void __launch_bounds__(256) k_zero_cols(T* __restrict__ p, int64_t ro
 
 // Zeroes the used columns of every row whose grid point no sphere covers: a
 // wave takes 64 rows, learns which are covered with one byte per lane and
-// writes the others V bytes per lane, consecutive lanes on consecutive bytes.
+// writes the others 16 bytes per lane (vpr pieces a row), consecutive lanes on
+// consecutive bytes.
 // Bound: HBM writes (the 433 000 uncovered rows of 2 KB of 32 d shells on a
 // 96^3 grid: 162 us, 5.5 TB/s; clearing all 885 000 took 325 us).
-template <typename V>
 __global__ void __launch_bounds__(256) k_zero_uncovered(char* __restrict__ p, const unsigned char* __restrict__ cover,
                                                         int64_t rows, int64_t G, int64_t rowbytes, int vpr) {
     const int lane = threadIdx.x & 63;
@@ -927,7 +927,37 @@ __global__ void __launch_bounds__(256) k_zero_uncovered(char* __restrict__ p, co
         char* __restrict__ b = p + r0 * rowbytes;
         for (int o = lane; o < 64 * vpr; o += 64) {
             const int k = o / vpr;
-            if ((todo >> k) & 1) *reinterpret_cast<V*>(b + k * rowbytes + static_cast<int64_t>(o - k * vpr) * sizeof(V)) = V{};
+            if ((todo >> k) & 1)
+                *reinterpret_cast<float4*>(b + k * rowbytes + static_cast<int64_t>(o - k * vpr) * 16) = float4{};
+        }
+    }
+}
+
+// The same for rows that do not start on 16 bytes: lpr lanes (16 or 64) take a
+// row, write its 16-byte pieces whole and the ends in 4-byte ones.  (A value
+// per lane, whose row each lane has to find by a division, took as long for the
+// uncovered half of 32 d shells' rows of 249 FP32 columns, 163 us, as clearing
+// every row did.)
+__global__ void __launch_bounds__(256) k_zero_uncovered_rows(char* __restrict__ p,
+                                                             const unsigned char* __restrict__ cover, int64_t rows,
+                                                             int64_t G, int64_t rowbytes, int usedbytes, int lpr) {
+    const int lane = threadIdx.x & 63, l = lane & (lpr - 1);
+    const int64_t nw = static_cast<int64_t>(gridDim.x) * 4;
+    for (int64_t r0 = (blockIdx.x * static_cast<int64_t>(4) + (threadIdx.x >> 6)) * 64; r0 < rows; r0 += nw * 64) {
+        const int64_t r = r0 + lane;
+        const uint64_t todo = __ballot(r < rows && cover[r % G] == 0);
+        if (todo == 0) continue;
+        for (int k = lane / lpr; k < 64; k += 64 / lpr) {
+            if (!((todo >> k) & 1)) continue;
+            char* __restrict__ b = p + (r0 + k) * rowbytes;
+            const int to16 = static_cast<int>(-reinterpret_cast<uintptr_t>(b) & 15);
+            const int head = to16 < usedbytes ? to16 : usedbytes;
+            const int pieces = (usedbytes - head) / 16, tail = usedbytes - head - 16 * pieces;
+            for (int o = l; o < pieces; o += lpr) *reinterpret_cast<float4*>(b + head + 16 * o) = float4{};
+            // the ends, of up to three values each
+            if (l < 3 && 4 * l < head) *reinterpret_cast<float*>(b + 4 * l) = 0.0f;
+            if (l >= 4 && l < 7 && 4 * (l - 4) < tail)
+                *reinterpret_cast<float*>(b + head + 16 * pieces + 4 * (l - 4)) = 0.0f;
         }
     }
 }
@@ -1057,16 +1087,13 @@ hipError_t launch_zero_uncovered(void* p, const unsigned char* cover, int64_t ro
     if (rows <= 0 || usedbytes <= 0) return hipSuccess;
     const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((rows + 255) / 256, 8192));
     char* b = static_cast<char*>(p);
-    // the widest vector that the rows' start, stride and length are multiples of
+    // whether the rows' start, stride and length are multiples of 16 bytes
     const int64_t a = reinterpret_cast<uintptr_t>(p) | static_cast<uint64_t>(rowbytes) | static_cast<uint64_t>(usedbytes);
     if (a % 16 == 0)
-        hipLaunchKernelGGL(k_zero_uncovered<float4>, dim3(blocks), dim3(256), 0, st, b, cover, rows, G, rowbytes,
+        hipLaunchKernelGGL(k_zero_uncovered, dim3(blocks), dim3(256), 0, st, b, cover, rows, G, rowbytes,
                            usedbytes / 16);
-    else if (a % 8 == 0)
-        hipLaunchKernelGGL(k_zero_uncovered<float2>, dim3(blocks), dim3(256), 0, st, b, cover, rows, G, rowbytes,
-                           usedbytes / 8);
     else
-        hipLaunchKernelGGL(k_zero_uncovered<float>, dim3(blocks), dim3(256), 0, st, b, cover, rows, G, rowbytes,
-                           usedbytes / 4);
+        hipLaunchKernelGGL(k_zero_uncovered_rows, dim3(blocks), dim3(256), 0, st, b, cover, rows, G, rowbytes,
+                           usedbytes, usedbytes > 512 ? 64 : 16);
     return hipGetLastError();
 }
