@@ -599,7 +599,7 @@ ProjArgs proj_args(hub_ctx* c, const void* psi, int64_t ld, int ncol, int table)
         a.prows = c->stencil_part_rows * 3;
     }
     a.pg = c->gauge ? c->d_pg : nullptr;
-    a.split = 1;
+    a.split_log2 = 0;
     return a;
 }
 
@@ -757,8 +757,8 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
         const int nall = static_cast<int>(GT.chunks.size());
         if (!mout) {
             const int cpl = clamp_cpl(c, pick_cpl(c, psi, ld, 0, ncol), HUB_GF_MAX);
-            a.split = proj_split(c, grouped_list(c), ncol, cpl, pick_wide(c, ncol, cpl, 0));
-            a.prows = GT.part_rows * a.split;
+            a.split_log2 = ilog2(proj_split(c, grouped_list(c), ncol, cpl, pick_wide(c, ncol, cpl, 0)));
+            a.prows = GT.part_rows << a.split_log2;
         }
         if (mout) {
             // orbitals and position moments in one launch over every chunk
@@ -787,7 +787,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
         ReduceGroupedArgs r{};
         r.part = part;
         r.prows = a.prows;
-        r.split_log2 = ilog2(a.split);
+        r.split_log2 = a.split_log2;
         r.out = out;
         r.J = c->T.J;
         r.ncol = ncol;
@@ -840,8 +840,8 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     const int gw = cpl * c->ncplx() == 1 ? 4 : 2;
     const int waves = c->tune_waves[0] ? c->tune_waves[0] : (full ? (grad ? gw : 1) : 4);
     if (!per_site) {
-        a.split = proj_split(c, shape, ncol, cpl, a.wide);
-        a.prows *= a.split;
+        a.split_log2 = ilog2(proj_split(c, shape, ncol, cpl, a.wide));
+        a.prows <<= a.split_log2;
     }
     {
     StageTimer tm(c, grad ? HUB_STAGE_GRADPROJ : HUB_STAGE_PROJECT);
@@ -871,7 +871,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
         r.chunks_per_site = c->stencil_nchunks / c->T.nsites;
     }
     r.prows = a.prows;
-    r.split_log2 = ilog2(a.split);
+    r.split_log2 = a.split_log2;
     StageTimer tm(c, HUB_STAGE_REDUCE);
     HUB_TRY(launch_reduce(r, nq, c->stream));
     return HUB_OK;
@@ -1088,7 +1088,7 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
     a.alpha = alpha;
     a.site_orb0 = c->d_site_orb0;
     a.site_L = c->d_site_L;
-    a.split = 1;
+    a.split_log2 = 0;
     a.stream = (reinterpret_cast<uintptr_t>(hpsi) | static_cast<uintptr_t>(ld) * c->elem()) % 128 == 0;
     a.spindep = c->T.spindep ? 1 : 0;
     if (!per_site && grouped(c)) {
@@ -1116,7 +1116,7 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
             if (c->tune_cpl[1] || store || !full)
                 cpl = clamp_cpl(c, pick_cpl(c, hpsi, ld, 1, ncol), hub_cls_nfmax(k));
             while (!c->tune_cpl[1] && cpl > 1 && lanes(cpl / 2) < lanes(cpl)) cpl /= 2;
-            b.split = split_of(c->grouped_longest, static_cast<int64_t>(nch) * nq * lanes(cpl) / cpl, 0.0);
+            b.split_log2 = ilog2(split_of(c->grouped_longest, static_cast<int64_t>(nch) * nq * lanes(cpl) / cpl, 0.0));
             return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, apply_waves(c), k, store, s);
         };
         if (!overwrite && use_bloch(c, 1, ld, ncol)) {

@@ -128,8 +128,8 @@ __device__ __forceinline__ void coefficient(const ApplyArgs& a, const HubFun& F,
 }
 
 // Bs: LDS of the work-group, at least L * NV * HUB_WAVE doubles.
-// ci: the chunk's index; slot_tile: column tile times split plus the part of
-// the chunk's entries that the work-group takes.
+// ci: the chunk's index; slot_tile: column tile and the part of the chunk's
+// entries that the work-group takes.
 // L: functions per entry; SPINDEP: per-site chunks of spin-dependent orbitals,
 // function sigma * (L/2) + m is orbital m of spin component sigma, whose
 // coefficient is nonzero only in that component's columns.
@@ -152,7 +152,7 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / HUB_WAVE);
     const int nw = blockDim.x / HUB_WAVE;
     const int cg = (a.ncol + CPL - 1) / CPL;
-    const int tile = slot_tile / a.split, part_of = slot_tile - tile * a.split;
+    const int tile = slot_tile >> a.split_log2, part_of = slot_tile - (tile << a.split_log2);
     int q, col0;
     bool active;
     if constexpr (WIDE) {
@@ -170,9 +170,10 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C
     // this wave's entries: e0 + [lo, lo + nj) of the chunk; a short chunk may
     // have none for the whole work-group
     int lo, nj;
-    hub_entry_range(C.ne, nw * a.split, part_of * nw, lo, nj);
+    const int parts_log2 = hub_waves_log2(nw) + a.split_log2;
+    hub_entry_range(C.ne, parts_log2, part_of * nw, lo, nj);
     if (nj == 0) return;
-    hub_entry_range(C.ne, nw * a.split, part_of * nw + wave, lo, nj);
+    hub_entry_range(C.ne, parts_log2, part_of * nw + wave, lo, nj);
     // coefficients: the waves split the functions (lanes past the last
     // column compute zeros for column 0 of their set and are then idle)
     for (int f = wave; f < L; f += nw) {
@@ -372,7 +373,7 @@ hipError_t launch_tg(const ApplyArgs& a, int nchunks, int nq, int waves, hipStre
         const int64_t cg = (a.ncol + CPL - 1) / CPL;
         ApplyArgs b = a;
         b.nchunks = nchunks;
-        b.tiles = static_cast<int>(static_cast<int64_t>(nq) * ((cg + HUB_WAVE - 1) / HUB_WAVE)) * a.split;
+        b.tiles = static_cast<int>(static_cast<int64_t>(nq) * ((cg + HUB_WAVE - 1) / HUB_WAVE)) << a.split_log2;
         const dim3 grid(static_cast<unsigned>(hub_slot_grid(nchunks, b.tiles)));
         if (a.pg) {
             // velocity gauge: complex states, merged launch only
@@ -412,7 +413,7 @@ hipError_t launch_t(const ApplyArgs& a, int nchunks, int nq, int waves, hipStrea
     ApplyArgs b = a;
     b.nchunks = nchunks;
     b.tiles = static_cast<int>(a.wide ? static_cast<int64_t>(nq) * ((cg + HUB_WAVE - 1) / HUB_WAVE)
-                                      : (static_cast<int64_t>(nq) * cg + HUB_WAVE - 1) / HUB_WAVE) * a.split;
+                                      : (static_cast<int64_t>(nq) * cg + HUB_WAVE - 1) / HUB_WAVE) << a.split_log2;
     const dim3 grid(static_cast<unsigned>(hub_slot_grid(nchunks, b.tiles)));
     T* h = reinterpret_cast<T*>(b.hpsi);
     if (a.spindep) {

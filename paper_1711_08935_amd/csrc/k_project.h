@@ -57,7 +57,7 @@ __device__ __forceinline__ void project_body(const ProjArgs& a, const HubChunk& 
     const int cpl = NV / NC;
     const int cg = (a.ncol + cpl - 1) / cpl;
 
-    const int tile = slot_tile / a.split, part_of = slot_tile - tile * a.split;
+    const int tile = slot_tile >> a.split_log2, part_of = slot_tile - (tile << a.split_log2);
     int q, col0;
     bool active;
     if constexpr (WIDE) {
@@ -77,7 +77,7 @@ __device__ __forceinline__ void project_body(const ProjArgs& a, const HubChunk& 
     const T* __restrict__ psi_q = reinterpret_cast<const T*>(a.psi) + static_cast<int64_t>(q) * a.qstride;
     // this wave's entries: e0 + [lo, lo + nj) of the chunk
     int lo, nj;
-    hub_entry_range(C.ne, nw * a.split, part_of * nw + wave, lo, nj);
+    hub_entry_range(C.ne, hub_waves_log2(nw) + a.split_log2, part_of * nw + wave, lo, nj);
     const int32_t* __restrict__ gi = gidx + C.e0 + lo;
     const double* __restrict__ tb = tab + (C.phi0 * a.tabmult + static_cast<int64_t>(lo) * NF);
     const int lofs = colc * NC;                                      // lane offset inside a row
@@ -262,14 +262,14 @@ __device__ __forceinline__ void project_body(const ProjArgs& a, const HubChunk& 
     }
     if (wave != 0 || !active) return;
     double* __restrict__ out =
-        part + (static_cast<int64_t>(q) * a.prows + static_cast<int64_t>(C.part0) * a.tabmult * a.split + part_of) *
+        part + (static_cast<int64_t>(q) * a.prows + ((static_cast<int64_t>(C.part0) * a.tabmult) << a.split_log2) + part_of) *
                    a.ncol * NC;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int col = col0 + v / NC;
-            if (col < a.ncol) out[(static_cast<int64_t>(f) * a.split * a.ncol + col0) * NC + v] = acc[f][v];
+            if (col < a.ncol) out[((static_cast<int64_t>(f) << a.split_log2) * a.ncol + col0) * NC + v] = acc[f][v];
         }
     }
 }
@@ -363,7 +363,7 @@ hipError_t launch_t(const ProjArgs& a, int nchunks, int nq, int cpl, int waves, 
         ProjArgs b = a;
         b.nchunks = nchunks;
         b.tiles = static_cast<int>(a.wide ? static_cast<int64_t>(nq) * ((cg + HUB_WAVE - 1) / HUB_WAVE)
-                                          : (static_cast<int64_t>(nq) * cg + HUB_WAVE - 1) / HUB_WAVE) * a.split;
+                                          : (static_cast<int64_t>(nq) * cg + HUB_WAVE - 1) / HUB_WAVE) << a.split_log2;
         const dim3 grid(static_cast<unsigned>(hub_slot_grid(nchunks, b.tiles)));
         if (a.pg) {
             // velocity gauge: complex states, per-site or merged chunk lists
@@ -398,7 +398,7 @@ template <typename T>
 hipError_t launch_project_prec(const ProjArgs& a, int nchunks, int nq, int cplx, int cpl, int waves, int cls,
                                hipStream_t st) {
     if (nchunks <= 0 || nq <= 0 || a.ncol <= 0) return hipSuccess;
-    if (a.split < 1) return hipErrorInvalidValue;
+    if (a.split_log2 < 0 || (waves != 1 && waves != 2 && waves != 4)) return hipErrorInvalidValue;
     if (a.ld < 0 || a.ld * a.ncplx > static_cast<int64_t>(UINT32_MAX)) return hipErrorInvalidValue;
     if (a.tabmult == 3) return cls == 0 ? launch_g<T, 3, 0>(a, nchunks, nq, cplx, cpl, waves, st)
                                         : hipErrorInvalidValue;

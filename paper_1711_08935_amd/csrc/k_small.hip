@@ -83,7 +83,7 @@ __device__ __forceinline__ void reduce_rows(int n, const double* __restrict__ ph
 // walking the chunks one by one took 60 us for 328 dilated chunks, 48 rows and
 // 16 sets of 27 complex columns, 15.6 us now, and 21.7 us for 914 chunks, 480
 // rows of 512 real columns, 14.5 us now.)
-template <int RW, int NC>
+template <int RW, int NC, bool SPLIT>
 __global__ void __launch_bounds__(RW * 64) k_reduce(const ReduceArgs a) {
     const int col = blockIdx.x * 64 + (threadIdx.x & 63);
     const int r = blockIdx.y;
@@ -97,7 +97,7 @@ __global__ void __launch_bounds__(RW * 64) k_reduce(const ReduceArgs a) {
     // spin-dependent orbitals: column 2s + sigma of orbital m is the partial
     // row sigma L + m of the chunk (the orbital of its spin component)
     const int srow = a.spindep ? (col & 1) * a.site_L[site] + local : local;
-    const int sh = a.split_log2, sm = (1 << sh) - 1;               // rows per chunk row
+    const int sh = SPLIT ? a.split_log2 : 0, sm = (1 << sh) - 1;   // rows per chunk row
     const double* __restrict__ base = a.part + ((static_cast<int64_t>(q) * a.prows + (static_cast<int64_t>(srow) << sh)) *
                                                     a.ncol + (active ? col : 0)) * NC;
     const int t0 = a.site_chunk_ptr[site], t1 = a.site_chunk_ptr[site + 1];
@@ -119,7 +119,7 @@ __global__ void __launch_bounds__(RW * 64) k_reduce(const ReduceArgs a) {
 // Grouped work list: out[q][j][col] = dV sum over the workspace rows that
 // belong to orbital j of exp(+i k.T_row) part[q][row][col], a work-group per
 // 64 columns of one (j, q).  RW follows the rows per orbital.
-template <int RW, int NC>
+template <int RW, int NC, bool SPLIT>
 __global__ void __launch_bounds__(RW * 64) k_reduce_grouped(const ReduceGroupedArgs a) {
     const int col = blockIdx.x * 64 + (threadIdx.x & 63);
     const int j = blockIdx.y;
@@ -131,7 +131,7 @@ __global__ void __launch_bounds__(RW * 64) k_reduce_grouped(const ReduceGroupedA
     // spin-dependent orbitals: spinor column 2s + sigma reads the rows of the
     // orbital of its spin component
     const int64_t shift = (a.spin_shift && (col & 1)) ? a.spin_shift[j] : 0;
-    const int sh = a.split_log2, sm = (1 << sh) - 1;               // rows per chunk row
+    const int sh = SPLIT ? a.split_log2 : 0, sm = (1 << sh) - 1;   // rows per chunk row
     const double* __restrict__ base = a.part + comp * a.pplane +
                                       (static_cast<int64_t>(q) * a.prows + (shift << sh)) * a.ncol * NC +
                                       static_cast<int64_t>(active ? col : 0) * NC;
@@ -972,16 +972,30 @@ hipError_t launch_gauge_tables(const GaugeArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
+namespace {
+// split: the launch without a chunk's work-groups keeps its indexes plain
+template <int RW, int NC>
+void reduce_t(const ReduceArgs& a, dim3 grid, hipStream_t st) {
+    if (a.split_log2) hipLaunchKernelGGL((k_reduce<RW, NC, true>), grid, dim3(RW * 64), 0, st, a);
+    else hipLaunchKernelGGL((k_reduce<RW, NC, false>), grid, dim3(RW * 64), 0, st, a);
+}
+template <int RW, int NC>
+void reduce_grouped_t(const ReduceGroupedArgs& a, dim3 grid, hipStream_t st) {
+    if (a.split_log2) hipLaunchKernelGGL((k_reduce_grouped<RW, NC, true>), grid, dim3(RW * 64), 0, st, a);
+    else hipLaunchKernelGGL((k_reduce_grouped<RW, NC, false>), grid, dim3(RW * 64), 0, st, a);
+}
+}  // namespace
+
 hipError_t launch_reduce(const ReduceArgs& a, int nq, hipStream_t st) {
     if (a.nrows <= 0 || nq <= 0 || a.ncol <= 0) return hipSuccess;
     dim3 grid((a.ncol + 63) / 64, a.nrows, nq);
     const bool wide = a.chunks_per_site << a.split_log2 >= 64;
     if (a.ncplx == 2) {
-        if (wide) hipLaunchKernelGGL((k_reduce<16, 2>), grid, dim3(16 * 64), 0, st, a);
-        else hipLaunchKernelGGL((k_reduce<4, 2>), grid, dim3(4 * 64), 0, st, a);
+        if (wide) reduce_t<16, 2>(a, grid, st);
+        else reduce_t<4, 2>(a, grid, st);
     } else {
-        if (wide) hipLaunchKernelGGL((k_reduce<16, 1>), grid, dim3(16 * 64), 0, st, a);
-        else hipLaunchKernelGGL((k_reduce<4, 1>), grid, dim3(4 * 64), 0, st, a);
+        if (wide) reduce_t<16, 1>(a, grid, st);
+        else reduce_t<4, 1>(a, grid, st);
     }
     return hipGetLastError();
 }
@@ -993,11 +1007,11 @@ hipError_t launch_reduce_grouped(const ReduceGroupedArgs& a, int nq, hipStream_t
     // many rows per orbital (overlapping spheres, small chunks): 16 waves
     const bool wide = a.rows_per_orbital << a.split_log2 >= 64;
     if (a.ncplx == 2) {
-        if (wide) hipLaunchKernelGGL((k_reduce_grouped<16, 2>), grid, dim3(16 * 64), 0, st, a);
-        else hipLaunchKernelGGL((k_reduce_grouped<4, 2>), grid, dim3(4 * 64), 0, st, a);
+        if (wide) reduce_grouped_t<16, 2>(a, grid, st);
+        else reduce_grouped_t<4, 2>(a, grid, st);
     } else {
-        if (wide) hipLaunchKernelGGL((k_reduce_grouped<16, 1>), grid, dim3(16 * 64), 0, st, a);
-        else hipLaunchKernelGGL((k_reduce_grouped<4, 1>), grid, dim3(4 * 64), 0, st, a);
+        if (wide) reduce_grouped_t<16, 1>(a, grid, st);
+        else reduce_grouped_t<4, 1>(a, grid, st);
     }
     return hipGetLastError();
 }

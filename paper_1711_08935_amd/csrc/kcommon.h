@@ -24,11 +24,11 @@ struct ProjArgs {
     int tabmult;              // 1: phi, 3: grad phi or position moments
     int wide;                 // 1: one state set per wave; 0: sets packed across lanes
     int nchunks;              // chunks in chunk_list (set by the launcher)
-    int tiles;                // column tiles per chunk times split (set by the launcher)
-    int split;                // work-groups that share a chunk's entries in one tile
+    int tiles;                // column tiles per chunk times the work-groups that share it (set by the launcher)
+    int split_log2;           // 2^split_log2 work-groups share a chunk's entries in one tile
     const double* pg;         // velocity gauge: [G] exp(i A.r_g) (re, im), or null
-    double* part;             // [nq][prows][ncol] (x2 complex): chunk row r, split s in row r split + s
-    int64_t prows;            // rows per state set = part_rows * tabmult * split
+    double* part;             // [nq][prows][ncol] (x2 complex): chunk row r, part s in row (r << split_log2) + s
+    int64_t prows;            // rows per state set = part_rows * tabmult << split_log2
     // position-moment launch (k_project_mom) only: per grouped point the
     // displacement d0[3] from its chunk's first cover, per chunk and function
     // the offset fdel[HUB_GF_MAX][3] to its own cover; component i (0: the
@@ -69,8 +69,8 @@ struct ApplyArgs {
     double alpha;
     int wide;                 // 1: one state set per wave; 0: sets packed across lanes
     int nchunks;              // chunks in chunk_list (set by the launcher)
-    int tiles;                // column tiles per chunk times split (set by the launcher)
-    int split;                // work-groups that share a chunk's entries in one tile
+    int tiles;                // column tiles per chunk times the work-groups that share it (set by the launcher)
+    int split_log2;           // 2^split_log2 work-groups share a chunk's entries in one tile
     int stream;               // overwritten rows start on 128 bytes: non-temporal stores
     const double* pg;         // velocity gauge: [G] exp(i A.r_g) (re, im), or null
     int spindep;              // per-site chunks with 2L functions [sigma][m] (spinor orbitals)
@@ -257,15 +257,18 @@ __device__ __forceinline__ void hub_wave_range(int n, int nw, int w, int& lo, in
     len = hi > lo ? hi - lo : 0;
 }
 
-// Entries [lo, lo + len) of part idx of the parts that share a chunk's n
+// Entries [lo, lo + len) of part idx of the 2^parts_log2 that share a chunk's n
 // entries (n a multiple of HUB_ENTRY_ALIGN): whole batches of the entry loops
-// (at most 8 entries).
-__device__ __forceinline__ void hub_entry_range(int n, int parts, int idx, int& lo, int& len) {
-    const int per = ((n + parts - 1) / parts + 7) & ~7;
+// (at most 8 entries).  Powers of two, because an integer division by a value
+// that only the launch knows costs every wave of a short launch a microsecond.
+__device__ __forceinline__ void hub_entry_range(int n, int parts_log2, int idx, int& lo, int& len) {
+    const int per = (((n + (1 << parts_log2) - 1) >> parts_log2) + 7) & ~7;
     lo = idx * per;
     len = n - lo < per ? n - lo : per;
     if (len < 0) lo = len = 0;
 }
+// log2 of 1, 2 or 4 waves
+__device__ __forceinline__ int hub_waves_log2(int nw) { return nw >> 1; }
 
 // Launchers, one translation unit per storage precision (and work list).
 hipError_t launch_project_f32(const ProjArgs& a, int nchunks, int nq, int cplx, int cpl, int waves, int cls,
