@@ -105,6 +105,7 @@ struct hub_ctx {
     int32_t* d_gall_m = nullptr;             // chunk list of the merged launch, by pass
     int32_t* d_gmom = nullptr;               // work items of the moment projection (k_project_mom.h)
     int nmom = 0;
+    int lmax = 0;                            // orbitals of the largest shell
     int site_longest = 0, grouped_longest = 0;   // entries of the longest chunk of either list
     int32_t* d_gmgidx = nullptr;             // its grid points, runs marked (uploaded with d_gd0)
     std::vector<int> gpass_ptr;              // d_gall_m[gpass_ptr[p], gpass_ptr[p+1]): chunks of pass p
@@ -374,13 +375,39 @@ int64_t proj_groups(const hub_ctx* c, int nchunks, int ncol, int cpl, int wide) 
     return nchunks * (wide ? nq * ((cg + HUB_WAVE - 1) / HUB_WAVE) : (nq * cg + HUB_WAVE - 1) / HUB_WAVE);
 }
 // From this many work-groups a launch fills the chip with one or two waves
-// each; below it the entries of a chunk are split over four.  One wave saves
-// the sum over waves: 64 shells, 1024 FP32 columns (6060 work-groups) 572 us
-// with one and four; 32 d shells, 512 FP32 columns (1830) 191 and 200 us; an
-// eighth of the lattice (792) 89 and 78 us.  Gradient tables (3 L functions)
-// take two: the same 32 d shells 216, 221 and 237 us with one, two and four,
-// p/d/f shells in FP64 (2082) 220, 178 and 171 us.
+// each; below it the entries of a chunk are split over four (an eighth of the
+// lattice, 792 work-groups, 89 us with one and 78 with four).
 constexpr int64_t kFullLaunch = 1536;
+// Waves per work-group of a projection of groups work-groups, cpl columns per
+// lane.  In a full launch one wave saves the sum over waves: 32 d shells, 512
+// real FP32 columns 158 us with one and 168 with four, 200 FP64 columns 137
+// and 144; 64 shells, 800 FP32 columns 232 and 240; 16 sets of 50 complex FP64
+// columns 174 and 180.  Four where a lane holds one value and waits for the
+// tables instead (64 shells, 85 FP32 columns 76 us with one and 43 with four,
+// 32 d shells 78 and 58; FP64 69 and 63, but from 4096 work-groups 208 and 212),
+// and for complex FP64 rows of several tiles (a layered cell, 200 spinor columns
+// 115 and 106; 16 sets of 100 columns 342 and 330).
+int proj_waves(const hub_ctx* c, int64_t groups, int cpl, int wide) {
+    if (c->tune_waves[0]) return c->tune_waves[0];
+    if (groups < kFullLaunch) return 4;
+    const bool f64 = c->precision == HUB_F64;
+    if (cpl * c->ncplx() == 1) return f64 && groups >= 4096 ? 1 : 4;
+    return f64 && c->is_complex && wide ? 4 : 1;
+}
+// Gradient tables (3 L functions) in a full launch take two: 32 d shells, 512
+// FP32 columns 232, 237 and 244 us with one, two and four; 16 sets of 100
+// complex FP32 columns 342, 343 and 358.  Four where a lane holds one value (32
+// d shells, 139 FP32 columns 243, 253 and 231; 64 uneven shells, 129 columns
+// 354, 318 and 283), with the 21 functions of an f shell (64 shells, 210, 450 and
+// 512 FP32 columns 150, 227 and 235 us with two, 125, 210 and 216 with four, 200
+// FP64 columns 170 and 162), and on dilated points where it holds two real FP32
+// values (32 d shells, 210 and 450 columns 178 and 360, 161 and 349).
+int grad_waves(const hub_ctx* c, int64_t groups, int cpl, bool dilated) {
+    if (c->tune_waves[0]) return c->tune_waves[0];
+    const int values = cpl * c->ncplx();
+    if (groups < kFullLaunch || values == 1 || c->lmax == HUB_LMAX) return 4;
+    return dilated && values == 2 && !c->is_complex && c->precision == HUB_F32 ? 4 : 2;
+}
 
 // Work-groups that share a chunk's entries in one column tile: a launch of
 // few work-groups waits for one batch of rows after another, so its chunks
@@ -778,8 +805,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
                 b.chunk_list = list;
                 const int cpl = clamp_cpl(c, pick_cpl(c, psi, ld, 0, ncol), hub_cls_nfmax(k));
                 b.wide = pick_wide(c, ncol, cpl, 0);
-                const int64_t groups = proj_groups(c, nall, ncol, cpl, b.wide);
-                const int waves = c->tune_waves[0] ? c->tune_waves[0] : (groups < kFullLaunch ? 4 : 1);
+                const int waves = proj_waves(c, proj_groups(c, nall, ncol, cpl, b.wide), cpl, b.wide);
                 return launch_project(b, nch, nq, c->precision, c->is_complex, cpl, waves, k, s);
             });
             if (st) return st;
@@ -834,11 +860,9 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
             a.wide = wide;
         }
     }
-    // one value per lane: the waves wait for the tables, so four even where
-    // the launch is full (32 d shells, 139 FP32 columns 243, 253 and 231 us
-    // with one, two and four; 64 uneven shells, 129 columns 354, 318 and 283)
-    const int gw = cpl * c->ncplx() == 1 ? 4 : 2;
-    const int waves = c->tune_waves[0] ? c->tune_waves[0] : (full ? (grad ? gw : 1) : 4);
+    // one site's chunks fill no launch
+    const int64_t groups = per_site ? 0 : proj_groups(c, list, ncol, cpl, a.wide);
+    const int waves = grad ? grad_waves(c, groups, cpl, stencil_table(table)) : proj_waves(c, groups, cpl, a.wide);
     if (!per_site) {
         a.split_log2 = ilog2(proj_split(c, shape, ncol, cpl, a.wide));
         a.prows <<= a.split_log2;
@@ -1103,19 +1127,26 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
             b.chunk_list = list;
             // One column per lane where that gives the chip enough work-groups:
             // the most waves in flight (1024 real FP32 columns, 24 000 groups:
-            // 1260 us, 1272 with four columns; 400 columns, 4865 groups: 232
-            // and 242).  Else, and for rows that are only written, 16 bytes per
+            // 1260 us, 1272 with four columns; 64 shells, 256 columns, 3236
+            // groups: 181 and 195; 210 FP64 columns 330, 348 with two).  Two
+            // where complex rows do not start on 128 bytes and then take fewer
+            // tiles, whose ends share lines (16 sets of 100 columns: FP32 374 us,
+            // 441 with one, FP64 730 and 846).  Else, and for rows that are only written, 16 bytes per
             // lane (four d shells, 512 columns, 944 groups: 53 us, 57 with one
             // column; written rows of 32 d shells 237 and 325), but never with
             // more lanes idle than narrower ones leave (64 complex FP32
             // columns: 377 us with one column, 452 with two; in five passes
             // 1.43 and 2.48 ms).
             auto lanes = [&](int v) { return (ncol + 64 * v - 1) / (64 * v) * v; };
-            const bool full = static_cast<int64_t>(nch) * nq * lanes(1) >= 4096;
+            const bool full = static_cast<int64_t>(nch) * nq * lanes(1) >= 2048;
             int cpl = 1;
             if (c->tune_cpl[1] || store || !full)
                 cpl = clamp_cpl(c, pick_cpl(c, hpsi, ld, 1, ncol), hub_cls_nfmax(k));
             while (!c->tune_cpl[1] && cpl > 1 && lanes(cpl / 2) < lanes(cpl)) cpl /= 2;
+            if (!c->tune_cpl[1] && !store && cpl == 1 && c->is_complex && ncol % 2 == 0 && ld % 2 == 0 &&
+                reinterpret_cast<uintptr_t>(hpsi) % 16 == 0 && ld * static_cast<int64_t>(c->elem()) % 128 != 0 &&
+                lanes(2) == lanes(1))
+                cpl = clamp_cpl(c, 2, hub_cls_nfmax(k));
             b.split_log2 = ilog2(split_of(c->grouped_longest, static_cast<int64_t>(nch) * nq * lanes(cpl) / cpl, 0.0));
             return launch_apply_grouped(b, nch, nq, c->precision, c->is_complex, cpl, apply_waves(c), k, store, s);
         };
@@ -1705,6 +1736,7 @@ int finalize_device(hub_ctx* c, void* stream) {
     auto up = [&](auto** dst, const auto& src) {
         if (e == hipSuccess) e = upload(c, dst, src, b);
     };
+    c->lmax = *std::max_element(T.site_L.begin(), T.site_L.end());
     c->site_longest = longest_chunk(T.chunks);
     c->grouped_longest = longest_chunk(T.grouped.chunks);
     up(&c->d_chunks, T.chunks);
