@@ -419,10 +419,16 @@ int grad_waves(const hub_ctx* c, int64_t groups, int cpl, bool dilated) {
 // 512 columns 109 / 116 / 111 us.
 constexpr int64_t kSplitGroups = 512;
 constexpr int64_t kSplitBytes = 16 << 20;
-int split_of(int longest, int64_t groups, double row_bytes) {
+// Orbital projections (not gradients, with three times the work per row) only
+// until their full waves of columns number this many, by storage: what the
+// reduction reads then costs more than the wait (four d shells: 200 FP64 columns
+// 21.6 us, 23.9 shared by two; 170 FP32 columns 18.9 and 16.2; eight uneven
+// shells: 128 FP64 columns 23.7 and 27.3, 256 FP32 columns 27.6 and 28.6).
+constexpr double kSplitWaves[2] = {256.0, 320.0};        // HUB_F64, HUB_F32
+int split_of(int longest, int64_t groups, double row_bytes, double waves = 0.0, double most = 0.0) {
     int s = 1;
     while (s < 16 && groups * s * 2 <= kSplitGroups && s * 2 * 32 <= longest &&
-           row_bytes * s * 2 <= static_cast<double>(kSplitBytes))
+           row_bytes * s * 2 <= static_cast<double>(kSplitBytes) && waves * s * 2 <= most)
         s *= 2;
     return s;
 }
@@ -438,9 +444,11 @@ ListShape grouped_list(const hub_ctx* c) {
     return {static_cast<int>(c->T.grouped.chunks.size()), c->grouped_longest, c->T.grouped.part_rows};
 }
 ListShape stencil_list(const hub_ctx* c) { return {c->stencil_nchunks, c->stencil_longest, c->stencil_part_rows}; }
-int proj_split(const hub_ctx* c, const ListShape& l, int ncol, int cpl, int wide) {
+int proj_split(const hub_ctx* c, const ListShape& l, int ncol, int cpl, int wide, bool grad) {
     if (c->no_split) return 1;
-    return split_of(l.longest, proj_groups(c, l.nchunks, ncol, cpl, wide), 8.0 * c->nsets() * l.rows * ncol * c->ncplx());
+    return split_of(l.longest, proj_groups(c, l.nchunks, ncol, cpl, wide), 8.0 * c->nsets() * l.rows * ncol * c->ncplx(),
+                    grad ? 0.0 : static_cast<double>(l.nchunks) * c->nsets() * ncol / (cpl * HUB_WAVE),
+                    kSplitWaves[c->precision == HUB_F32]);
 }
 // The same for the Bloch-summed list, whose work-groups are single waves, by
 // the whole list and every state set: two in the projection, whose partial
@@ -667,7 +675,7 @@ size_t part_need(const hub_ctx* c, int ncol, int mult, bool smaller = true) {
     const int64_t nq = c->nsets(), nc = c->ncplx();
     // rows times columns, at the split of the widest lanes, the largest
     auto most = [&](const ListShape& l) {
-        int64_t n = l.rows * ncol * proj_split(c, l, ncol, 4, 0);
+        int64_t n = l.rows * ncol * proj_split(c, l, ncol, 4, 0, true);
         for (int s = 2; smaller && l.rows > 0 && s <= 16 && s * 32 <= l.longest; s *= 2) {
             const int64_t tiles = kSplitGroups / s / l.nchunks;
             const int64_t cols = std::min(4 * (tiles * HUB_WAVE / nq), kSplitBytes / (8 * nq * l.rows * nc * s));
@@ -784,7 +792,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
         const int nall = static_cast<int>(GT.chunks.size());
         if (!mout) {
             const int cpl = clamp_cpl(c, pick_cpl(c, psi, ld, 0, ncol), HUB_GF_MAX);
-            a.split_log2 = ilog2(proj_split(c, grouped_list(c), ncol, cpl, pick_wide(c, ncol, cpl, 0)));
+            a.split_log2 = ilog2(proj_split(c, grouped_list(c), ncol, cpl, pick_wide(c, ncol, cpl, 0), false));
             a.prows = GT.part_rows << a.split_log2;
         }
         if (mout) {
@@ -864,7 +872,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     const int64_t groups = per_site ? 0 : proj_groups(c, list, ncol, cpl, a.wide);
     const int waves = grad ? grad_waves(c, groups, cpl, stencil_table(table)) : proj_waves(c, groups, cpl, a.wide);
     if (!per_site) {
-        a.split_log2 = ilog2(proj_split(c, shape, ncol, cpl, a.wide));
+        a.split_log2 = ilog2(proj_split(c, shape, ncol, cpl, a.wide, grad));
         a.prows <<= a.split_log2;
     }
     {
