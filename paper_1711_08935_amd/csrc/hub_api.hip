@@ -500,21 +500,21 @@ double row_lines(const hub_ctx* c, int64_t ld, int ncol, int w) {
 // whose estimated time is less, for the whole context (a range of sets takes
 // its route).  In microseconds, with what each moves and does:
 // * the passes read every row once per pass (and the apply writes it): row
-//   lines at 5 TB/s, beside a cost per wave, per row and wave in the apply
-//   (one state set per wave, so narrow sets leave lanes idle) and, in the
-//   projection, of the reduction;
+//   lines at 5 TB/s, beside a cost per wave (the projection packs sets of up to
+//   64 columns, the apply has one set per wave), per row and wave in the apply
+//   and, in the projection, of the reduction;
 // * the Bloch-summed list reads every row once (the apply writes it, in tiles
 //   of 16 or 32 columns) and, in the projection, the k-point's table for every
 //   tile, at 30 TB/s from the caches; its products take whole 16-column tiles at
 //   71 TF/s.
-// The factors are fitted to 400 timings of each call: rocksalt cells of 24^3 to
-// 48^3 points, 1 to 125 k-points, rows in passes over rows 1.01 to 3.5, 1 to
-// 128 columns in both precisions.  The chosen route is 0.8 % (projection) and
-// 0.2 % (apply) above the faster one on average, 24 % and 20 % at most.  Passes
-// and this list for projections of 8 FP32 columns: 48^3 points and 16 sets at
-// 1.06 52 and 80 us, at 3.5 181 and 87; 24^3 points and 128 sets at 1.17 143 and
-// 93.  The applies there: 208 and 107, 743 and 115, 334 and 122.  33 columns on
-// 44^3 points at 1.06: 126 and 193, 242 and 281.
+// The factors are fitted to 810 timings of each call: rocksalt cells of 24^3 to
+// 52^3 points and mixed cells, 1 to 125 k-points, rows in passes over rows 1.01
+// to 3.5, 1 to 128 columns in both precisions.  The chosen route is 1.0 %
+// (projection) and 0.3 % (apply) above the faster one on average, 25 % and 20 %
+// at most.  Passes and this list for projections of 8 FP32 columns: 48^3 points
+// and 16 sets at 1.06 52 and 80 us, at 3.5 181 and 87; 24^3 points and 128 sets
+// at 1.17 143 and 93.  The applies there: 208 and 107, 743 and 115, 334 and 122.
+// 33 columns on 44^3 points at 1.06: 126 and 193, 242 and 281.
 bool use_bloch(const hub_ctx* c, int which, int64_t ld, int ncol) {
     if (!have_bloch(c)) return false;
     const double us = 128.0 / 5e6;                           // a line
@@ -525,12 +525,13 @@ bool use_bloch(const hub_ctx* c, int which, int64_t ld, int ncol) {
     const double wide = row_lines(c, ld, ncol, HUB_WAVE), table = sets * static_cast<double>(c->bl_wlen);
     const double products = (ncol + 15) / 16 * 16 * table * 4.0 / 71e6;
     if (which == 0) {
-        const double passes = 16.0 + 0.87 * rows * wide + 0.0044 * nch * std::ceil(sets * ncol / HUB_WAVE) +
-                              0.013 * c->T.J * sets * tiles;
-        return 14.5 + 0.58 * entries * wide + 0.83 * products + 1.1 * ((ncol + w - 1) / w) * table * 8.0 / 30e6 < passes;
+        const double waves = ncol <= HUB_WAVE ? std::ceil(sets * ncol / HUB_WAVE) : sets * tiles;
+        const double passes = 12.8 + 0.87 * rows * wide + 0.0057 * nch * waves + 0.0128 * c->T.J * sets * tiles;
+        return 12.5 + 0.709 * entries * wide + 0.71 * products + 0.654 * ((ncol + w - 1) / w) * table * 8.0 / 30e6 <
+               passes;
     }
-    const double passes = 17.0 + 1.25 * rows * wide + 0.0175 * nch * sets * tiles + 6e-6 * c->g_rows * sets * tiles;
-    return 7.1 + entries * (0.07 * wide + 0.99 * row_lines(c, ld, ncol, w)) + 1.38 * products < passes;
+    const double passes = 13.1 + 1.25 * rows * wide + 0.0196 * nch * sets * tiles + 9.71e-6 * c->g_rows * sets * tiles;
+    return 3.79 + entries * (0.084 * wide + 1.02 * row_lines(c, ld, ncol, w)) + 1.46 * products < passes;
 }
 
 // Columns per lane so that a lane's FP64 accumulators (functions x scalars)
@@ -1121,7 +1122,14 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
     a.site_orb0 = c->d_site_orb0;
     a.site_L = c->d_site_L;
     a.split_log2 = 0;
-    a.stream = (reinterpret_cast<uintptr_t>(hpsi) | static_cast<uintptr_t>(ld) * c->elem()) % 128 == 0;
+    // Written rows past the caches: rows on 64 bytes, and complex rows of one
+    // tile and at least a line, whose few shared lines cost less than the dirty
+    // ones would cost the projection that follows (16 sets of 33 FP32 columns on
+    // 48^3 points: written in 227 us against 210 through the cache, the whole
+    // energy gradient 673 and 700; of 13 columns 474 and 424; of 79, two tiles,
+    // 1646 and 1507).
+    a.stream = (reinterpret_cast<uintptr_t>(hpsi) | static_cast<uintptr_t>(ld) * c->elem()) % 64 == 0 ||
+               (c->is_complex && ncol <= HUB_WAVE && ncol * c->elem() >= 128);
     a.spindep = c->T.spindep ? 1 : 0;
     if (!per_site && grouped(c)) {
         a.wide = 1;
@@ -1151,7 +1159,7 @@ int do_apply(hub_ctx* c, const double* Ueff, const double* n, const double* cc, 
             if (c->tune_cpl[1] || store || !full)
                 cpl = clamp_cpl(c, pick_cpl(c, hpsi, ld, 1, ncol), hub_cls_nfmax(k));
             while (!c->tune_cpl[1] && cpl > 1 && lanes(cpl / 2) < lanes(cpl)) cpl /= 2;
-            if (!c->tune_cpl[1] && !store && cpl == 1 && c->is_complex && ncol % 2 == 0 && ld % 2 == 0 &&
+            if (!c->tune_cpl[1] && !store && full && cpl == 1 && c->is_complex && ncol % 2 == 0 && ld % 2 == 0 &&
                 reinterpret_cast<uintptr_t>(hpsi) % 16 == 0 && ld * static_cast<int64_t>(c->elem()) % 128 != 0 &&
                 lanes(2) == lanes(1))
                 cpl = clamp_cpl(c, 2, hub_cls_nfmax(k));

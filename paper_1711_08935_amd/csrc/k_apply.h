@@ -135,10 +135,11 @@ __device__ __forceinline__ void coefficient(const ApplyArgs& a, const HubFun& F,
 // coefficient is nonzero only in that component's columns.
 // STORE: the rows are overwritten with the update instead of being read and
 // added to (the energy gradient, whose buffer starts at zero), with
-// non-temporal stores where rows start on 128 bytes (16 sets of 64 complex FP32
-// columns: 198 us, 269 with ordinary ones).  Elsewhere rows share lines, which
-// the cache has to put together (249 real FP32 columns of 32 d shells, apply
-// alone 179 us non-temporal, 150 when it added to cleared rows).
+// non-temporal stores where rows start on 64 bytes (16 sets of 64 complex FP32
+// columns: 198 us, 269 with ordinary ones; of 24 columns 117 and 202) or share
+// few lines.  Elsewhere the cache has to put together what neighbouring rows
+// and tiles write of a line (85 columns 481 us with ordinary stores, 652
+// non-temporal; 249 real FP32 columns of 32 d shells, apply alone, 150 and 179).
 template <typename T, bool CPX, bool SPINOR, int CPL, int L, bool WIDE, bool GROUPED, bool GAUGE,
           bool SPINDEP = false, bool STORE = false>
 __device__ __forceinline__ void apply_body(const ApplyArgs& a, const HubChunk& C, int ci, int slot_tile,

@@ -71,7 +71,7 @@ struct ApplyArgs {
     int nchunks;              // chunks in chunk_list (set by the launcher)
     int tiles;                // column tiles per chunk times the work-groups that share it (set by the launcher)
     int split_log2;           // 2^split_log2 work-groups share a chunk's entries in one tile
-    int stream;               // overwritten rows start on 128 bytes: non-temporal stores
+    int stream;               // overwritten rows go past the caches: non-temporal stores
     const double* pg;         // velocity gauge: [G] exp(i A.r_g) (re, im), or null
     int spindep;              // per-site chunks with 2L functions [sigma][m] (spinor orbitals)
     int q0;                   // context index of the first state set of the launch (k-point, spin)
