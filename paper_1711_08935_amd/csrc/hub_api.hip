@@ -385,14 +385,18 @@ constexpr int64_t kFullLaunch = 1536;
 // columns 174 and 180.  Four where a lane holds one value and waits for the
 // tables instead (64 shells, 85 FP32 columns 76 us with one and 43 with four,
 // 32 d shells 78 and 58; FP64 69 and 63, but from 4096 work-groups 208 and 212),
-// and for complex FP64 rows of several tiles (a layered cell, 200 spinor columns
-// 115 and 106; 16 sets of 100 columns 342 and 330).
-int proj_waves(const hub_ctx* c, int64_t groups, int cpl, int wide) {
+// and for complex FP64 rows of several tiles (layered cells, spinor columns: 256
+// in 1760 work-groups 109 and 102, 200 in 2448 138 and 131; 16 sets of 100
+// columns 342 and 330), but for three tiles or more only below 3000 work-groups
+// (230 columns in 3040 196 and 201, 256 in 4096 297 and 306; 16 sets of 200
+// columns 1069 and 1096).
+int proj_waves(const hub_ctx* c, int64_t groups, int cpl, int ncol, int wide) {
     if (c->tune_waves[0]) return c->tune_waves[0];
     if (groups < kFullLaunch) return 4;
     const bool f64 = c->precision == HUB_F64;
     if (cpl * c->ncplx() == 1) return f64 && groups >= 4096 ? 1 : 4;
-    return f64 && c->is_complex && wide ? 4 : 1;
+    const bool few = groups < 3000 || ncol <= 2 * HUB_WAVE;
+    return f64 && c->is_complex && wide && few ? 4 : 1;
 }
 // Gradient tables (3 L functions) in a full launch take two: 32 d shells, 512
 // FP32 columns 232, 237 and 244 us with one, two and four; 16 sets of 100
@@ -814,7 +818,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
                 b.chunk_list = list;
                 const int cpl = clamp_cpl(c, pick_cpl(c, psi, ld, 0, ncol), hub_cls_nfmax(k));
                 b.wide = pick_wide(c, ncol, cpl, 0);
-                const int waves = proj_waves(c, proj_groups(c, nall, ncol, cpl, b.wide), cpl, b.wide);
+                const int waves = proj_waves(c, proj_groups(c, nall, ncol, cpl, b.wide), cpl, ncol, b.wide);
                 return launch_project(b, nch, nq, c->precision, c->is_complex, cpl, waves, k, s);
             });
             if (st) return st;
@@ -871,7 +875,7 @@ int do_project(hub_ctx* c, const void* psi, int64_t ld, int nstates, double* out
     }
     // one site's chunks fill no launch
     const int64_t groups = per_site ? 0 : proj_groups(c, list, ncol, cpl, a.wide);
-    const int waves = grad ? grad_waves(c, groups, cpl, stencil_table(table)) : proj_waves(c, groups, cpl, a.wide);
+    const int waves = grad ? grad_waves(c, groups, cpl, stencil_table(table)) : proj_waves(c, groups, cpl, ncol, a.wide);
     if (!per_site) {
         a.split_log2 = ilog2(proj_split(c, shape, ncol, cpl, a.wide, grad));
         a.prows <<= a.split_log2;
